@@ -35,11 +35,12 @@ PEAK_HBM = 8.0e12
 # dominant kernel of the factorisation per GEMM form: (stats name, kernel,
 # issued MFMA flops per 4M-equivalent flop, MFMA peak)
 DOMINANT = {
-    "3m": ("gemm_3m", "gemm_c32_lds_kernel<3M, 128x128> (LU trailing updates, complex 3M on "
-                      "MFMA f32, operands streamed into LDS)", 0.75, PEAK_F32_MFMA),
+    "3m": ("gemm_f16x3", "gemm_c32_split_kernel<f16> (LU updates of at least 1024 x 1024, float32 "
+                         "products as three f16 MFMA products of split, scaled operands)", 3.0,
+           PEAK_BF16_MFMA),
     "4m": ("gemm_c32", "gemm_c32_lds_kernel<4M, 128x128> (LU trailing updates, complex 4M on "
                        "MFMA f32, operands streamed into LDS)", 1.0, PEAK_F32_MFMA),
-    "b3": ("gemm_b3_packed", "gemm_c32_b3p_kernel (LU trailing updates, bf16x3 split on MFMA "
+    "b3": ("gemm_b3_packed", "gemm_c32_split_kernel<bf16> (LU trailing updates, bf16x3 split on MFMA "
                              "bf16, operands pre-split)", 3.0, PEAK_BF16_MFMA),
 }
 MODES = None     # filled on first use (needs the binding)
@@ -251,7 +252,8 @@ def main():
     ctx.set_profiling(True)
     step()
     torch.cuda.synchronize()
-    split_names = (gname, gname + "_narrow", "gemm_b3", "gemm_b3_narrow", "gemm_small", "pack",
+    f32name = "gemm_c32" if args.mode == "4m" else "gemm_3m"
+    split_names = (gname, f32name, f32name + "_narrow", "gemm_b3", "gemm_b3_narrow", "gemm_small", "pack",
                    "panel", "laswp", "trsm", "assemble", "residual", "getrs", "field", "synth")
     split = {kname: ctx.kernel_stats(kname)[2] for kname in split_names
              if kname in DOMINANT_SPLIT_OK or ctx.kernel_stats(kname)[3] > 0}
@@ -369,7 +371,7 @@ def main():
         "vs_baseline": None,
         "dtype": {"b3": "c64 LU (bf16x3 split products on bf16 MFMA, f32 accumulate)",
                   "4m": "c64 LU (complex 4M on f32 MFMA, f32 accumulate)",
-                  "3m": "c64 LU (complex 3M on f32 MFMA, f32 accumulate)"}[args.mode]
+                  "3m": "c64 LU (f32 products: f16x3 split on f16 MFMA, 3M on f32 MFMA for small updates; f32 accumulate)"}[args.mode]
                  + " + f64 residual refinement",
         "data": "synthetic",
         "config": {"workload": w.name, "n": n, "n_k": n_k, "field_points": m, "T": T,
@@ -399,7 +401,7 @@ def main():
         "roofline": {"kernel": kdesc,
                      "bound": "mfma", "achieved": achieved / 1e12, "peak": peak / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / peak,
-                     "achieved_note": "MFMA flops the kernel issues (3M: 6 MNK, 4M: 8 MNK, bf16x3: "
+                     "achieved_note": "MFMA flops the kernel issues (4M: 8 MNK, f16x3 and bf16x3: "
                                       "24 MNK per complex update) over the HIP-event time of every "
                                       "launch of the run",
                      "traffic": measured_traffic(gname, args.nb or (tuned[0] if tuned else "default"),

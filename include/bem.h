@@ -57,7 +57,7 @@ void bem_ctx_destroy(bem_ctx* ctx);
 const char* bem_last_error(const bem_ctx* ctx);
 /* Upper bound (bytes) of device workspace bem_solve_batched may hold; 0 = 75%
  * of the free device memory at the time of the call.  A nonzero limit also caps
- * the packing buffer of BEM_GEMM_BF16X3 factorisations at a quarter of it. */
+ * the packing buffer of BEM_GEMM_3M and BEM_GEMM_BF16X3 factorisations at a quarter of it. */
 bem_status bem_ctx_set_workspace_limit(bem_ctx* ctx, uint64_t bytes);
 
 /* Per-kernel accounting for roofline reports.  With profiling on, each launch
@@ -67,7 +67,8 @@ bem_status bem_ctx_set_workspace_limit(bem_ctx* ctx, uint64_t bytes);
  * was last switched (set_profiling resets them).  Kernel names: "gemm_c32" and
  * "gemm_3m" (float32 4M / 3M updates of at least 65 columns), "gemm_c32_narrow" and
  * "gemm_3m_narrow" (17 to 64 columns), "gemm_c32_unaligned" and "gemm_3m_unaligned"
- * (operands not 16-byte aligned), "gemm_b3", "gemm_b3_narrow", "gemm_b3_packed",
+ * (operands not 16-byte aligned), "gemm_f16x3" (3M updates
+ * of at least 1024 x 1024 on split operands), "gemm_b3", "gemm_b3_narrow", "gemm_b3_packed",
  * "gemm_small", "pack", "gemm_c64", "panel", "laswp", "trsm", "assemble", "residual",
  * "getrs", "field", "synth".
  * For "assemble"/"residual" the flop slot counts node pairs and for "field"
@@ -175,10 +176,11 @@ bem_status bem_residual_check(bem_ctx* ctx, const bem_surface* s, int32_t n_k, c
 /* ---------------------------------------------------------------- solve
  * One linear system per wavenumber (Sec. IV A: direct solve).  Modes:
  *   BEM_FP64_DIRECT : c128 assembly + float64 LU (MFMA f64) + triangular solves
- *   BEM_FP32_IR_4M  : c64 LU (complex GEMM as 4 real products on MFMA f32,
- *                     float32 accumulation) + iterative refinement with the
+ *   BEM_FP32_IR_4M  : c64 LU (complex GEMM as 4 real products, float32
+ *                     accumulation) + iterative refinement with the
  *                     float64 matrix-free residual, until ||dx||/||x|| <= tol_step
- *   BEM_FP32_IR_3M  : as 4M with the 3-product complex GEMM
+ *   BEM_FP32_IR_3M  : as 4M with the 3-product complex GEMM and, for updates of
+ *                     at least 1024 x 1024, f16x3 split products (bem_gemm_kind)
  *   BEM_FP32_IR_B3  : as 4M with every real product of the GEMM taken as three
  *                     bfloat16 MFMA products of the split operands
  *                     (x = hi + lo; hi hi + hi lo + lo hi, float32 accumulation)
@@ -194,6 +196,13 @@ typedef enum {
 } bem_mode;
 
 /* complex GEMM form of a c64 factorisation (last argument of bem_getrf_batched).
+ * BEM_GEMM_4M and BEM_GEMM_3M: four or three float32 MFMA products per complex
+ * one.  BEM_GEMM_3M runs its updates of at least 1024 x 1024 on MFMA f16, every
+ * real product as three products of operands split into f16 pairs and scaled by
+ * powers of two (error against float64 below that of its float32 MFMA products);
+ * the split operands use the packing buffer described below, and where it
+ * cannot be allocated, or in a caller's stream capture, those updates take the
+ * float32 MFMA products too.
  * BEM_GEMM_BF16X3 runs the updates of at least 512 x 512 (the trailing update
  * of each block column among them) on operands split once into bf16 words by
  * a packing pass (the context keeps a packing

@@ -54,7 +54,7 @@ struct bem_ctx {
   };
   std::vector<LuGraph> lu_graphs;
   hipStream_t capture_stream = nullptr;
-  // operands of the trailing updates split into bf16 words (grown on demand)
+  // operands of the large updates split into 16-bit words (grown on demand)
   void* pack = nullptr;
   size_t pack_size = 0;
   // frequency indices of a sparse synthesis (grown on demand)

@@ -1449,7 +1449,7 @@ __global__ __launch_bounds__(256) void gemm_c32_small_kernel(LuGroups G, int row
 }
 
 // ============================================================== GEMM f32 via bf16 split, packed operands
-// Updates of at least 512 x 512 take their operands split once: a packing
+// Large updates (Fac::pack_min) take their operands split once: a packing
 // pass converts A (a block column of L, e.g. below the block just factored)
 // and B (a block row of U, in the real-part pattern (Re, -Im)) into bf16
 // hi/lo words laid out as the GEMM's LDS stage buffers -- per 128-row (or
@@ -1465,10 +1465,16 @@ constexpr int GP_BLK = 2 * 2 * GB_BM;   // 16-byte words per tile and 8-k block
 // largest packing buffer a context holds; bigger batches are packed in slices
 constexpr size_t kPackLimit = (size_t)4 << 30;
 
+// 16-byte words of one matrix's scale exponents (the f16 form): t_k [K],
+// ea [128 tiles_m], eb [128 tiles_n]
+inline int64_t scale_words(int tiles_m, int tiles_n, int K) {
+  return (4 * ((int64_t)K + GB_BM * tiles_m + GB_BN * tiles_n) + 15) / 16;
+}
 // 16-byte words of the packed A and B of one matrix for an M x N update of depth K
 inline int64_t pack_words(int M, int N, int K) {
   const int64_t S8 = (K + 7) / 8;
-  return ((int64_t)(M + GB_BM - 1) / GB_BM + (N + GB_BN - 1) / GB_BN) * S8 * GP_BLK;
+  const int tm = (M + GB_BM - 1) / GB_BM, tn = (N + GB_BN - 1) / GB_BN;
+  return (int64_t)(tm + tn) * S8 * GP_BLK + scale_words(tm, tn, K);
 }
 
 // A = rows [rowC, min(rowEnd, n)) x cols [colA, colA + K) -> out + y * ms.
@@ -1560,38 +1566,280 @@ __global__ __launch_bounds__(256) void pack_b_kernel(LuGroups G, int rowB, int c
   o[GB_BN + col] = lo;
 }
 
-__device__ inline bf16x8 re_to_im8(bf16x8 b) {
-  const u32x4 r = __builtin_bit_cast(u32x4, b);
-  return __builtin_bit_cast(bf16x8, ((r >> 16) | (r << 16)) ^ 0x8000u);
+// ============================================================== float32 products on f16 MFMA
+// The 3M form takes its updates of at least 1024 x 1024 as three f16 MFMA products
+// per real product (four of those per complex one): x = hi + lo with
+// hi = f16(x) and lo = f16(x - hi) keeps 22 to 24 significant bits (11 + 11 and
+// lo's sign), and x y ~ hi hi + hi lo + lo hi drops only lo lo (2^-22 of the
+// product at most).  MFMA f16 adds sixteen products per rounding of the float32
+// accumulator where MFMA f32 32x32x2 adds two, and there are no sums
+// (a + b)(c + d) - a c - b d to cancel, so the update is closer to the float64
+// product than the float32 3M one: relative error of a 256 x 256 update,
+// Gaussian data, K = 64 / 512 / 1024: 1.4 / 3.6 / 5.0e-7 against 2.1 / 5.8 /
+// 8.1e-7; backward error ||PA - LU|| / ||A|| of Gaussian matrices of n = 1284 and
+// 1600: 1.1e-5 and 1.6e-5 against 1.8e-5 and 2.8e-5.  (The 4M form's is 0.6e-5
+// and 0.8e-5, so it keeps its float32 products.)  24 flops on the 2.5 PFLOP/s unit
+// replace 6 on the 0.157 one: the updates of 64 matrices of n = 5124 take 62 ms
+// and 11 ms of splitting instead of 127 ms.
+//
+// Range: f16 holds 2^-24 .. 2^16, so the operands are scaled by powers of two
+// (exact).  Row k of U is divided by 2^t_k, t_k the exponent of its largest
+// entry, and column k of L multiplied by it; then each row i of L is scaled by
+// 2^(14 - ea_i) and each column j of U by 2^(14 - eb_j), their largest entries
+// in [2^14, 2^15).  Scaling rows or columns of the matrix by powers of two
+// therefore changes no bit of the products, and an entry keeps its full split
+// down to 2^-15 of the largest of its row or column (its error is at most 2^-39
+// of that entry below).  The epilogue takes 2^(ea_i + eb_j - 28) back.
+//
+// Bias: MFMA f16 cuts the products it adds off at the accumulator's last bit
+// towards minus infinity, a mean error of -0.05 of the rms one.  Random errors
+// grow with the square root of the matrix size in the factors' norm but a mean
+// one with the size itself (it tripled the correction left after one
+// refinement sweep at n = 5124), so the accumulators change sign every
+// kFlipK of depth, with L packed negated in every other such range: what the
+// bias adds in one range it takes off in the next (mean error below 0.01).
+constexpr int kFlipK = 128;   // complex depth between sign changes (a multiple of 16)
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+
+// exponent e of a magnitude 2^e <= m < 2^(e + 1), clamped so that every scale
+// 2^(14 - e) and its inverse are normal floats (0 for m = 0, the largest for
+// infinities; NaN entries are not counted by fmaxf)
+__device__ inline int scale_exp(float m) {
+  const int e = (int)((__float_as_uint(m) >> 23) & 0xff) - 127;
+  return m == 0.f ? 0 : min(max(e, -100), 100);
+}
+__device__ inline float exp2i(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
+
+__device__ inline void split8h(const float* x, uint4& hi, uint4& lo) {
+  unsigned hw[4], lw[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const f2v v = {x[2 * p], x[2 * p + 1]};
+    const h2v h = __builtin_convertvector(v, h2v);
+    const f2v r = v - __builtin_convertvector(h, f2v);
+    hw[p] = __builtin_bit_cast(unsigned, h);
+    lw[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(r, h2v));
+  }
+  hi = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+  lo = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
-__global__ __launch_bounds__(256, 2) void gemm_c32_b3p_kernel(LuGroups G, int rowC, int colC,
-                                                              int rowEnd, int colEnd, int K,
-                                                              int tiles_m, int tiles_n,
-                                                              const uint4* __restrict__ Ap,
-                                                              int64_t a_ms,
-                                                              const uint4* __restrict__ Bp,
-                                                              int64_t b_ms) {
+// t_k of row rowB + k of U over the columns [colC, min(colEnd, n)); one
+// workgroup per row
+__global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int colC, int colEnd,
+                                                       int64_t ss, int32_t* __restrict__ ex) {
+  __shared__ float red[4];
+  LuGroup grp;
+  int b = 0;
+  if (!locate(G, blockIdx.y, grp, b)) return;
+  const int N = min(colEnd, grp.n) - colC;
+  const int k = blockIdx.x;
+  float m = 0.f;
+  if (rowB + k < grp.n) {
+    const GLOBAL float2* r = gmat<float2>(grp, b) + (int64_t)(rowB + k) * grp.ld + colC;
+#pragma unroll 4
+    for (int j = threadIdx.x; j < N; j += 256) {
+      const float2 v = r[j];
+      m = fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y)));
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    ex[blockIdx.y * ss + k] = scale_exp(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+}
+
+// L = rows [rowC, min(rowEnd, n)) x cols [colA, colA + K): 32 rows per
+// workgroup, thread (row tid % 32, 8-k block tid / 32 and every eighth after);
+// the rows are read twice (their largest entries first, from cache after), and
+// written as pack_a_kernel's words.
+__global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, int colA, int rowEnd,
+                                                         int K, int tiles_m, int64_t ms, int64_t ss,
+                                                         uint4* __restrict__ out,
+                                                         int32_t* __restrict__ ex) {
+  __shared__ float red[8][32];
+  LuGroup grp;
+  int b = 0;
+  if (!locate(G, blockIdx.y, grp, b)) return;
+  const int M = min(rowEnd, grp.n) - rowC;
+  const int gr = blockIdx.x * 32 + (threadIdx.x & 31), part = threadIdx.x >> 5;
+  if ((int)blockIdx.x * 32 >= (M + GB_BM - 1) / GB_BM * GB_BM) return;
+  const int32_t* tk = ex + blockIdx.y * ss;
+  const int S8 = (K + 7) / 8;
+  const bool vec = ((grp.ld | colA) & 1) == 0;
+  const GLOBAL float2* A = gmat<float2>(grp, b) + (int64_t)(rowC + min(gr, M - 1)) * grp.ld + colA;
+  // the block's 8 values times 2^t_k, zero past the edges
+  auto load = [&](int s8, float* x) {
+    const int k0 = s8 * 8;
+    if (vec && k0 + 8 <= K) {
+      const GLOBAL float4* p4 = (const GLOBAL float4*)(A + k0);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const float4 v = p4[m];
+        x[4 * m] = v.x;
+        x[4 * m + 1] = v.y;
+        x[4 * m + 2] = v.z;
+        x[4 * m + 3] = v.w;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float2 v = A[min(k0 + q, K - 1)];
+        x[2 * q] = v.x;
+        x[2 * q + 1] = v.y;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const bool ok = gr < M && k0 + q < K;
+      const float f = exp2i(tk[min(k0 + q, K - 1)]);
+      x[2 * q] = ok ? x[2 * q] * f : 0.f;
+      x[2 * q + 1] = ok ? x[2 * q + 1] * f : 0.f;
+    }
+  };
+  float m = 0.f, x[16];
+  for (int s8 = part; s8 < S8; s8 += 8) {
+    load(s8, x);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m = fmaxf(m, fabsf(x[q]));
+  }
+  red[part][threadIdx.x & 31] = m;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 8; ++q) m = fmaxf(m, red[q][threadIdx.x & 31]);
+  const int e = scale_exp(m);
+  if (part == 0) ex[blockIdx.y * ss + K + gr] = e;
+  const float sc = exp2i(14 - e);
+  const int tile = gr / GB_BM, row = gr % GB_BM;
+  for (int s8 = part; s8 < S8; s8 += 8) {
+    load(s8, x);
+    const float sg = (s8 / (kFlipK / 8)) & 1 ? -sc : sc;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) x[q] *= sg;
+    uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + s8) * GP_BLK;
+#pragma unroll
+    for (int kg = 0; kg < 2; ++kg) {
+      uint4 hi, lo;
+      split8h(x + 8 * kg, hi, lo);
+      o[kg * 2 * GB_BM + row] = hi;
+      o[kg * 2 * GB_BM + GB_BM + row] = lo;
+    }
+  }
+}
+
+// U = rows [rowB, rowB + K) x cols [colC, min(colEnd, n)): 32 columns per
+// workgroup, thread (column tid % 32, k group of 4 tid / 32 and every eighth
+// after), read twice like pack_a_f16_kernel, written as pack_b_kernel's words.
+__global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, int colC, int colEnd,
+                                                         int K, int tiles_m, int tiles_n, int64_t ms,
+                                                         int64_t ss, uint4* __restrict__ out,
+                                                         int32_t* __restrict__ ex) {
+  __shared__ float red[8][32];
+  LuGroup grp;
+  int b = 0;
+  if (!locate(G, blockIdx.y, grp, b)) return;
+  const int N = min(colEnd, grp.n) - colC;
+  const int gc = blockIdx.x * 32 + (threadIdx.x & 31), part = threadIdx.x >> 5;
+  if ((int)blockIdx.x * 32 >= (N + GB_BN - 1) / GB_BN * GB_BN) return;
+  const int32_t* tk = ex + blockIdx.y * ss;
+  const int S8 = (K + 7) / 8;
+  const GLOBAL float2* B = gmat<float2>(grp, b) + (int64_t)rowB * grp.ld + colC + min(gc, N - 1);
+  auto load = [&](int g, float* x) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 4 * g + q;
+      const float2 v = B[(int64_t)min(k, K - 1) * grp.ld];
+      const bool ok = gc < N && k < K;
+      const float f = exp2i(-tk[min(k, K - 1)]);
+      x[2 * q] = ok ? v.x * f : 0.f;
+      x[2 * q + 1] = ok ? -v.y * f : 0.f;
+    }
+  };
+  float m = 0.f, x[8];
+#pragma unroll 2
+  for (int g = part; g < 2 * S8; g += 8) {
+    load(g, x);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) m = fmaxf(m, fabsf(x[q]));
+  }
+  red[part][threadIdx.x & 31] = m;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 8; ++q) m = fmaxf(m, red[q][threadIdx.x & 31]);
+  const int e = scale_exp(m);
+  if (part == 0) ex[blockIdx.y * ss + K + GB_BM * tiles_m + gc] = e;
+  const float sc = exp2i(14 - e);
+  const int tile = gc / GB_BN, col = gc % GB_BN;
+#pragma unroll 2
+  for (int g = part; g < 2 * S8; g += 8) {
+    load(g, x);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] *= sc;
+    uint4 hi, lo;
+    split8h(x, hi, lo);
+    uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + g / 2) * GP_BLK + (g & 1) * 2 * GB_BN;
+    o[col] = hi;
+    o[GB_BN + col] = lo;
+  }
+}
+
+// (a, -b) pairs of the real-part pattern -> (b, a) of the imaginary-part
+// pattern (both 16-bit formats keep the sign in the top bit)
+__device__ inline u32x4 re_to_im4(u32x4 r) { return ((r >> 16) | (r << 16)) ^ 0x8000u; }
+
+// F16: 16-bit words are f16 and the scale exponents ex apply; else bfloat16.
+// Tile order, work list and edge handling are those of gemm_c32_lds_kernel.
+template <bool F16>
+__global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
+    LuGroups G, GemmList W, int rowC, int colC, int rowEnd, int colEnd, int K,
+    const uint4* __restrict__ Ap, int64_t a_ms, const uint4* __restrict__ Bp, int64_t b_ms,
+    const int32_t* __restrict__ ex, int64_t ss, int tiles_m_all) {
   __shared__ u32x4 As[2][2 * GP_BLK], Bs[2][2 * GP_BLK];
-  const int per = gridDim.x / 8;
-  const int t = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (t >= tiles_m * tiles_n) return;
-  const int grp = t / (GB_GM * tiles_n), first = grp * GB_GM;
-  const int gsz = min(tiles_m - first, GB_GM);
-  const int tm = first + (t % (GB_GM * tiles_n)) % gsz;
-  const int tn = (t % (GB_GM * tiles_n)) / gsz;
-  GemmView<float2> gv;
-  if (!gemm_view(G, rowC, colC, 0, 0, rowEnd, colEnd, gv)) return;
+  const int64_t total = W.start[G.ng];
+  const int64_t item = (int64_t)(blockIdx.x & 7) * ((total + 7) >> 3) + (blockIdx.x >> 3);
+  if (item >= total) return;
+  int gsel = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxGroups; ++i)
+    if (i < G.ng && item >= W.start[i]) gsel = i;
+  int64_t first_item = 0, ld64 = 0, stride = 0;
+  const void* Abase = nullptr;
+  int n = 0, tiles_m = 1, tiles_n = 1, first_mat = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxGroups; ++i) {
+    if (i < gsel) first_mat += G.g[i].count;
+    if (i == gsel) {
+      first_item = W.start[i];
+      Abase = G.g[i].A;
+      ld64 = G.g[i].ld;
+      stride = G.g[i].stride;
+      n = G.g[i].n;
+      tiles_m = W.tm[i];
+      tiles_n = W.tn[i];
+    }
+  }
+  const int64_t local = item - first_item;
+  const int tiles = tiles_m * tiles_n;
+  const int64_t b = local / tiles;
+  const int t = (int)(local - b * tiles);
+  const int strip = GL_GM * tiles_n;
+  const int first = (t / strip) * GL_GM;
+  const int gsz = min(tiles_m - first, GL_GM);
+  const int tcol = (t % strip) / gsz;
+  const int tm = first + (t % strip) % gsz, tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
+  const int64_t mat = first_mat + b;
+  const int M = min(rowEnd, n) - rowC, N = min(colEnd, n) - colC;
   const int m0 = tm * GB_BM, n0 = tn * GB_BN;
-  const int M = gv.M, N = gv.N;
-  if (m0 >= M || n0 >= N) return;
-  const int ld = (int)gv.ld;   // n * ld < 2^31 is checked on the host
-  GLOBAL float2* C = gv.Cm;
+  const int ld = (int)ld64;   // n * ld < 2^31 is checked on the host
+  GLOBAL float2* C = (GLOBAL float2*)Abase + b * stride + (int64_t)rowC * ld + colC;
   const int S8 = (K + 7) / 8, S = (S8 + 1) / 2;
-  const GLOBAL u32x4* Ag = (const GLOBAL u32x4*)Ap + blockIdx.y * a_ms + (int64_t)tm * S8 * GP_BLK;
-  const GLOBAL u32x4* Bg = (const GLOBAL u32x4*)Bp + blockIdx.y * b_ms + (int64_t)tn * S8 * GP_BLK;
+  const GLOBAL u32x4* Ag = (const GLOBAL u32x4*)Ap + mat * a_ms + (int64_t)tm * S8 * GP_BLK;
+  const GLOBAL u32x4* Bg = (const GLOBAL u32x4*)Bp + mat * b_ms + (int64_t)tn * S8 * GP_BLK;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wid = tid >> 6;
+  const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid >> 1, wn = wid & 1;
   const int h = lane >> 5, l32 = lane & 31;
   floatx16 acc_re[2][2], acc_im[2][2];
@@ -1617,49 +1865,85 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_b3p_kernel(LuGroups G, int ro
                   __builtin_amdgcn_readfirstlane(b_lds + boff + q * 4096));
       }
   };
-  load_stage(0);
-  for (int s = 0; s < S; ++s) {
-    // stage s has landed, and every wave is past its reads of stage s - 1,
-    // whose buffer the next load reuses
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    if (s + 1 < S) load_stage(s + 1);
-    const int cur = s & 1;
+  auto mfma = [](u32x4 a, u32x4 bb, floatx16 c) {
+    if constexpr (F16)
+      return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
+                                                    __builtin_bit_cast(f16x8, bb), c, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                     __builtin_bit_cast(bf16x8, bb), c, 0, 0, 0);
+  };
+  bool live_i[2], live_j[2];
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      if (2 * s + s2 >= S8) break;
-      const int base = s2 * GP_BLK + h * 2 * GB_BM;   // lanes 32-63 take the second k group
-      bf16x8 ah[2], al[2], brh[2], brl[2], bih[2], bil[2];
+  for (int i = 0; i < 2; ++i) {
+    live_i[i] = m0 + wm * 64 + 32 * i < M;
+    live_j[i] = n0 + wn * 64 + 32 * i < N;
+  }
+  auto kloop = [&](auto all_live) {
+    constexpr bool ALL = decltype(all_live)::value;
+    load_stage(0);
+    for (int s = 0; s < S; ++s) {
+      // stage s has landed, and every wave is past its reads of stage s - 1,
+      // whose buffer the next load reuses
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      if (s + 1 < S) load_stage(s + 1);
+      const int cur = s & 1;
+      if (F16 && s && s % (kFlipK / 16) == 0) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ah[i] = __builtin_bit_cast(bf16x8, As[cur][base + wm * 64 + i * 32 + l32]);
-        al[i] = __builtin_bit_cast(bf16x8, As[cur][base + GB_BM + wm * 64 + i * 32 + l32]);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            acc_re[i][j] = -acc_re[i][j];
+            acc_im[i][j] = -acc_im[i][j];
+          }
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        brh[j] = __builtin_bit_cast(bf16x8, Bs[cur][base + wn * 64 + j * 32 + l32]);
-        brl[j] = __builtin_bit_cast(bf16x8, Bs[cur][base + GB_BN + wn * 64 + j * 32 + l32]);
-        bih[j] = re_to_im8(brh[j]);
-        bil[j] = re_to_im8(brl[j]);
-      }
+      for (int s2 = 0; s2 < 2; ++s2) {
+        if (2 * s + s2 >= S8) break;
+        const int base = s2 * GP_BLK + h * 2 * GB_BM;   // lanes 32-63 take the second k group
+        u32x4 ah[2], al[2], brh[2], brl[2], bih[2], bil[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+          ah[i] = As[cur][base + wm * 64 + i * 32 + l32];
+          al[i] = As[cur][base + GB_BM + wm * 64 + i * 32 + l32];
+        }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          acc_re[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], brh[j], acc_re[i][j], 0, 0, 0);
-          acc_re[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], brl[j], acc_re[i][j], 0, 0, 0);
-          acc_re[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], brh[j], acc_re[i][j], 0, 0, 0);
-          acc_im[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bih[j], acc_im[i][j], 0, 0, 0);
-          acc_im[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bil[j], acc_im[i][j], 0, 0, 0);
-          acc_im[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bih[j], acc_im[i][j], 0, 0, 0);
+          brh[j] = Bs[cur][base + wn * 64 + j * 32 + l32];
+          brl[j] = Bs[cur][base + GB_BN + wn * 64 + j * 32 + l32];
+          bih[j] = re_to_im4(brh[j]);
+          bil[j] = re_to_im4(brl[j]);
         }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            if (ALL || (live_i[i] && live_j[j])) {
+              acc_re[i][j] = mfma(al[i], brh[j], acc_re[i][j]);
+              acc_re[i][j] = mfma(ah[i], brl[j], acc_re[i][j]);
+              acc_re[i][j] = mfma(ah[i], brh[j], acc_re[i][j]);
+              acc_im[i][j] = mfma(al[i], bih[j], acc_im[i][j]);
+              acc_im[i][j] = mfma(ah[i], bil[j], acc_im[i][j]);
+              acc_im[i][j] = mfma(ah[i], bih[j], acc_im[i][j]);
+            }
+          }
+      }
     }
-  }
+  };
+  if (live_i[1] && live_j[1])
+    kloop(std::true_type{});
+  else
+    kloop(std::false_type{});
+  const int32_t* ea = F16 ? ex + mat * ss + K : nullptr;
+  const int32_t* eb = F16 ? ea + GB_BM * tiles_m_all : nullptr;
+  const float sgn = ((K - 1) / kFlipK) & 1 ? -1.f : 1.f;   // of the accumulators after the last range
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = n0 + wn * 64 + j * 32 + l32;
       if (col >= N) continue;
+      const int ej = F16 ? eb[col] - 28 : 0;
       float2 c[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -1669,7 +1953,13 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_b3p_kernel(LuGroups G, int ro
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (row < M) C[row * ld + col] = make_float2(c[v].x - acc_re[i][j][v], c[v].y - acc_im[i][j][v]);
+        float dr = acc_re[i][j][v], di = acc_im[i][j][v];
+        if constexpr (F16) {
+          const int e = ea[row] + ej;   // (ea covers whole tiles)
+          dr = sgn * ldexpf(dr, e);
+          di = sgn * ldexpf(di, e);
+        }
+        if (row < M) C[row * ld + col] = make_float2(c[v].x - dr, c[v].y - di);
       }
     }
 }
@@ -1958,7 +2248,7 @@ struct Fac {
   int base = 8;
   int gkind = kGemm4M;           // complex GEMM form for c64 (bem_gemm_kind)
   int nmax = 0;
-  bool use_pack = false;         // trailing updates through the packed bf16x3 GEMM
+  bool use_pack = false;         // large updates on operands split into 16-bit words
   void* pack = nullptr;          // packing buffer (context-owned) and its size
   size_t pack_bytes = 0;
 
@@ -2050,16 +2340,8 @@ struct Fac {
     }
   }
   // C = rows [rowC, rowEnd) x cols [colC, colEnd) -= A(rows, [colA, colA+K)) B([rowB, rowB+K), cols)
-  // float32 3M / 4M update through gemm_c32_lds_kernel; false (nothing
-  // launched) when an operand is not 16-byte aligned (odd ld, column offset or
-  // depth)
-  bool gemm_lds(const LuGroups& G, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd,
-                int K, int N) {
-    if ((colA | colC | K) & 1) return false;
-    for (int i = 0; i < G.ng; ++i)
-      if (G.g[i].ld & 1) return false;
-    const bool narrow = N <= std::max(64, plan.gemm_narrow_max);
-    const int BN = narrow ? 64 : 128;
+  // every (matrix, tile) pair of an update, tiles of 128 x BN
+  static GemmList work_list(const LuGroups& G, int rowC, int colC, int rowEnd, int colEnd, int BN) {
     GemmList W{};
     W.start[0] = 0;
     for (int i = 0; i < G.ng; ++i) {
@@ -2070,6 +2352,18 @@ struct Fac {
       W.start[i + 1] = W.start[i] + (m > 0 && nn > 0 ? (int64_t)G.g[i].count * W.tm[i] * W.tn[i] : 0);
     }
     for (int i = G.ng + 1; i <= kMaxGroups; ++i) W.start[i] = W.start[G.ng];
+    return W;
+  }
+  // float32 3M / 4M update through gemm_c32_lds_kernel; false (nothing
+  // launched) when an operand is not 16-byte aligned (odd ld, column offset or
+  // depth)
+  bool gemm_lds(const LuGroups& G, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd,
+                int K, int N) {
+    if ((colA | colC | K) & 1) return false;
+    for (int i = 0; i < G.ng; ++i)
+      if (G.g[i].ld & 1) return false;
+    const bool narrow = N <= std::max(64, plan.gemm_narrow_max);
+    const GemmList W = work_list(G, rowC, colC, rowEnd, colEnd, narrow ? 64 : 128);
     const int64_t total = W.start[G.ng];
     if (total <= 0) return true;
     // persistent form: the resident workgroups (two per CU) when the launch
@@ -2189,6 +2483,11 @@ struct Fac {
     }
     return S;
   }
+  // Smallest update (rows and columns) whose operands are packed.  bfloat16
+  // words: four tiles must read each operand.  f16 words, whose scales take two
+  // more passes: eight (21 matrices of n = 1284: 12.90 ms per 3M solve either
+  // way at 1024, 13.00 from 512 on; 8 of n = 2562: 44.6 against 45.1 ms).
+  int pack_min() const { return (gkind == kGemmBf16x3 ? 4 : 8) * GB_BM; }
   // packing buffer bytes that would let every trailing update run in one slice
   size_t pack_need(int nb) const {
     size_t need = 0;
@@ -2196,7 +2495,7 @@ struct Fac {
       const int e = block_end(c, nb);
       int total, maxn;
       active(e, &total, &maxn);
-      if (total == 0) continue;
+      if (total == 0 || maxn - e < pack_min()) continue;
       need = std::max(need, (size_t)pack_words(maxn - e, maxn - e, e - c) * 16 * total);
     }
     return need;
@@ -2211,19 +2510,20 @@ struct Fac {
     if (total == 0) return true;
     const int M = std::min(rowEnd, maxn) - rowC, N = std::min(colEnd, maxn) - colC;
     if (M <= 0 || N <= 0) return true;
-    // each packed operand must be read by at least four tiles to repay its
-    // pass (measured: at two or three, the pass costs more than it saves)
-    if (M < 4 * GB_BM || N < 4 * GB_BN) return false;
+    // each packed operand must be read by enough tiles to repay its pass
+    const bool f16 = gkind != kGemmBf16x3;
+    if (std::min(M, N) < pack_min()) return false;
+    const int tiles_m = (M + GB_BM - 1) / GB_BM, tiles_n = (N + GB_BN - 1) / GB_BN;
     const size_t per = (size_t)pack_words(M, N, K) * 16;
     const int fit = (int)std::min<size_t>((size_t)total, pack ? pack_bytes / per : 0);
     if (fit <= 0) return false;
-    const int tiles_m = (M + GB_BM - 1) / GB_BM, tiles_n = (N + GB_BN - 1) / GB_BN;
     const int S8 = (K + 7) / 8;
     const int64_t a_ms = (int64_t)tiles_m * S8 * GP_BLK, b_ms = (int64_t)tiles_n * S8 * GP_BLK;
+    const int64_t ss = 4 * scale_words(tiles_m, tiles_n, K);
     uint4* Ap = (uint4*)pack;
     uint4* Bp = Ap + a_ms * fit;
+    int32_t* ex = (int32_t*)(Bp + b_ms * fit);
     const int64_t ta = (int64_t)tiles_m * S8 * GB_BM, tb = (int64_t)tiles_n * S8 * (GP_BLK / 2);
-    const int gx = (tiles_m * tiles_n + 7) / 8 * 8;
     for (int b0 = 0; b0 < total; b0 += fit) {
       const int nbat = std::min(fit, total - b0);
       const LuGroups Gs = slice(G, b0, b0 + nbat, esz());
@@ -2235,17 +2535,34 @@ struct Fac {
         kn += nn * K * Gs.g[i].count;
         mn += m * nn * Gs.g[i].count;
       }
+      const GemmList W = work_list(Gs, rowC, colC, rowEnd, colEnd, GB_BN);
       int pi = prof_begin(ctx, "pack");
-      hipLaunchKernelGGL(pack_a_kernel, dim3((unsigned)((ta + 255) / 256), nbat), dim3(256), 0,
-                         ctx->stream, Gs, rowC, colA, rowEnd, K, tiles_m, a_ms, Ap);
-      hipLaunchKernelGGL(pack_b_kernel, dim3((unsigned)((tb + 255) / 256), nbat), dim3(256), 0,
-                         ctx->stream, Gs, rowB, colC, colEnd, K, tiles_n, b_ms, Bp);
+      if (f16) {
+        hipLaunchKernelGGL(urow_exp_kernel, dim3(K, nbat), dim3(256), 0, ctx->stream, Gs, rowB,
+                           colC, colEnd, ss, ex);
+        hipLaunchKernelGGL(pack_a_f16_kernel, dim3(tiles_m * (GB_BM / 32), nbat), dim3(256), 0,
+                           ctx->stream, Gs, rowC, colA, rowEnd, K, tiles_m, a_ms, ss, Ap, ex);
+        hipLaunchKernelGGL(pack_b_f16_kernel, dim3(tiles_n * (GB_BN / 32), nbat), dim3(256), 0,
+                           ctx->stream, Gs, rowB, colC, colEnd, K, tiles_m, tiles_n, b_ms, ss, Bp,
+                           ex);
+      } else {
+        hipLaunchKernelGGL(pack_a_kernel, dim3((unsigned)((ta + 255) / 256), nbat), dim3(256), 0,
+                           ctx->stream, Gs, rowC, colA, rowEnd, K, tiles_m, a_ms, Ap);
+        hipLaunchKernelGGL(pack_b_kernel, dim3((unsigned)((tb + 255) / 256), nbat), dim3(256), 0,
+                           ctx->stream, Gs, rowB, colC, colEnd, K, tiles_n, b_ms, Bp);
+      }
       // float32 operands read, split words written (8 bytes per complex element each way)
       prof_end(ctx, "pack", pi, 0.0, 16.0 * (mk + kn));
-      pi = prof_begin(ctx, "gemm_b3_packed");
-      hipLaunchKernelGGL(gemm_c32_b3p_kernel, dim3(gx, nbat), dim3(256), 0, ctx->stream, Gs, rowC,
-                         colC, rowEnd, colEnd, K, tiles_m, tiles_n, Ap, a_ms, Bp, b_ms);
-      prof_end(ctx, "gemm_b3_packed", pi, 8.0 * mn * K, 8.0 * (mk + kn + 2.0 * mn));
+      const char* kname = f16 ? "gemm_f16x3" : "gemm_b3_packed";
+      pi = prof_begin(ctx, kname);
+      const dim3 gd((unsigned)((W.start[Gs.ng] + 7) / 8 * 8)), bd(256);
+      if (f16)
+        hipLaunchKernelGGL(gemm_c32_split_kernel<true>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
+                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
+      else
+        hipLaunchKernelGGL(gemm_c32_split_kernel<false>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
+                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
+      prof_end(ctx, kname, pi, 8.0 * mn * K, 8.0 * (mk + kn + 2.0 * mn));
     }
     return true;
   }
@@ -2339,7 +2656,7 @@ static bem_status build_fac(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
   f.prec = prec;
   f.plan = plan;
   f.gkind = prec == BEM_C64 ? (gemm_kind == kGemmBf16x3Unpacked ? kGemmBf16x3 : gemm_kind) : kGemm4M;
-  f.use_pack = prec == BEM_C64 && gemm_kind == kGemmBf16x3;
+  f.use_pack = prec == BEM_C64 && (gemm_kind == kGemmBf16x3 || gemm_kind == kGemm3M);
   for (const LuMatrixSet& s : sets) {
     if (s.count <= 0 || s.n <= 0) continue;
     if (s.n > 24 * kPanelThreads)
@@ -2409,10 +2726,16 @@ bem_status lu_factor_groups(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
     hipLaunchKernelGGL(fill_i32_kernel, dim3((g.count + 255) / 256), dim3(256), 0, ctx->stream,
                        (int64_t)g.count, g.info, 0);
   if (f.use_pack) {
-    // under capture the buffer was reserved before the capture began
-    if (!capturing(ctx->stream)) reserve_pack(ctx, f, nb);
-    f.pack = ctx->pack;
-    f.pack_bytes = std::min(ctx->pack_size, pack_cap(ctx));
+    // under the context's own capture the buffer was reserved before it began;
+    // a caller's capture holds no pointer into the buffer (a later call may
+    // grow it): the 3M form then runs without it, as it does when it cannot
+    // be allocated
+    const bool cap = capturing(ctx->stream);
+    if (!cap) reserve_pack(ctx, f, nb);
+    if (!cap || ctx->stream == ctx->capture_stream || f.gkind == kGemmBf16x3) {
+      f.pack = ctx->pack;
+      f.pack_bytes = std::min(ctx->pack_size, pack_cap(ctx));
+    }
   }
   f.blocked(nb);
   BEM_CHECK_LAUNCH(ctx);
