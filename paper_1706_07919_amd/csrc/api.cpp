@@ -1312,15 +1312,18 @@ extern "C" bem_status bem_field_eval_quadratic(bem_ctx* ctx, const bem_quad_surf
   if (m == 0) return BEM_OK;
   const size_t setup = (quad_setup_bytes(s->n, s->n_elem) + 255) / 256 * 256;
   const size_t interp = ((size_t)n_k * n_rhs * s->n_elem * 7 * 16 + 255) / 256 * 256;
+  const size_t sums = ((size_t)n_k * n_rhs * s->n * 16 + 255) / 256 * 256;
+  const size_t list = 2 * ((((size_t)s->n + 1) * 4 + 255) / 256 * 256);
   void* ws = nullptr;
-  if ((st = workspace(ctx, setup + 2 * interp, &ws)) != BEM_OK) return st;
+  if ((st = workspace(ctx, setup + 2 * interp + sums + list, &ws)) != BEM_OK) return st;
   double* qp = nullptr;
   int32_t* inc = nullptr;
   if ((st = quad_setup(ctx, s, ws, &qp, &inc)) != BEM_OK) return st;
   bem_surface nodal{s->n, s->x, s->nrm, nullptr, s->bc};
   if ((st = launch_closest(ctx, &nodal, m, xp, i0, inside)) != BEM_OK) return st;
   char* base = (char*)ws + setup;
-  return launch_quad_field(ctx, s, qp, n_k, k, n_rhs, phi, psi, base, base + interp, m, xp, i0,
+  return launch_quad_field(ctx, s, qp, n_k, k, n_rhs, phi, psi, base, base + interp,
+                           base + 2 * interp, (int32_t*)(base + 2 * interp + sums), m, xp, i0,
                            inside, U);
 }
 

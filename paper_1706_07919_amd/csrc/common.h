@@ -199,6 +199,22 @@ bem_status launch_closest(bem_ctx*, const bem_surface*, int m, const double* xp,
                           uint8_t* inside);
 bem_status launch_inside(bem_ctx*, const bem_surface*, int m, const double* xp,
                          const int32_t* i0, uint8_t* inside);
+// Sources of the float64 field sums: positions and normals (sx doubles apart),
+// weights (sw apart) and surface data [n_k][n_rhs][n]; nodes: source j is node j
+// (its own term left out)
+struct FieldSources {
+  const double *x, *nrm, *w;
+  int sx, sw, n;
+  bool nodes;
+  const double2 *phi, *psi;
+};
+// Float64 field at the points from the sources' sums; s holds the nodes (x, nrm;
+// phi, psi their data).  Snode: 16 n_rhs n_k n bytes.  list_ws (or NULL: every
+// node's sum): 2 * round_up(4 (n + 1), 256) bytes.
+bem_status launch_field64(bem_ctx*, const FieldSources& src, const bem_surface* s, int n_k,
+                          const double* k, int n_rhs, const void* phi, const void* psi, int m,
+                          const double* xp, const int32_t* i0, const uint8_t* inside, void* Snode,
+                          int32_t* list_ws, void* U);
 // fixed_scratch: node sums in the fixed per-device scratch (no workspace, no
 // profiling events), EINVAL when they do not fit
 bem_status launch_field(bem_ctx*, const bem_surface*, int n_k, const double* k, int n_rhs,
@@ -226,10 +242,12 @@ bem_status launch_quad_assemble(bem_ctx*, const bem_quad_surface*, const double*
 // r = b - A64 x over n_k matrices (stride elements apart) and n_rhs vectors each
 bem_status launch_quad_residual(bem_ctx*, int n, const void* A64, int64_t ld, int64_t stride,
                                 int n_k, int n_rhs, const void* b, const void* x, void* r);
-// phq, psq: [n_k * n_rhs][n_elem * 7] c128 scratch
+// phq, psq: [n_k * n_rhs][n_elem * 7] c128 scratch; sums, list_ws: as Snode and
+// list_ws of launch_field64
 bem_status launch_quad_field(bem_ctx*, const bem_quad_surface*, const double* qp, int n_k,
                              const double* k, int n_rhs, const void* phi, const void* psi,
-                             void* phq, void* psq, int m, const double* xp, const int32_t* i0,
+                             void* phq, void* psq, void* sums, int32_t* list_ws, int m,
+                             const double* xp, const int32_t* i0,
                              const uint8_t* inside, void* U);
 
 }  // namespace bem

@@ -13,7 +13,7 @@
 // side: a workgroup takes NR right-hand sides at once and applies every
 // generated kernel value (w G, w H for one node, point and frequency) to all
 // of them, so NR right-hand sides cost one kernel generation and NR complex
-// multiply-adds per term instead of NR generations.  Float32 kernels take every phase k*r and k*s
+// multiply-adds per term instead of NR generations.  The float32 kernel takes every phase k*r and k*s
 // in float64, reduce it to [-1/2, 1/2) revolutions, and evaluate the
 // trigonometric functions in float32 on the reduced argument.  Each point's
 // sweep is split over kParts lanes (lane q takes every kParts-th node), whose
@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "phase.h"
 
 namespace bem {
 namespace {
@@ -97,30 +98,16 @@ __global__ void inside_kernel(const double* __restrict__ x, const double* __rest
 }
 
 // --------------------------------------------------------------- field sums
-template <typename R> struct CX;
-template <> struct CX<float> { using T = float2; };
-template <> struct CX<double> { using T = double2; };
-
-template <typename R>
-__device__ inline void phase(double theta, R& s, R& c);
-template <>
-__device__ inline void phase<float>(double theta, float& s, float& c) {
-  double t = theta * kInv2Pi;
+// sine and cosine in float32 of a float64 phase, in radians or (phase_rev) in
+// revolutions, reduced in float64
+__device__ inline void phase_rev(double t, float& s, float& c) {
   t -= rint(t);
   const float tf = (float)t;
   s = __builtin_amdgcn_sinf(tf);   // argument in revolutions
   c = __builtin_amdgcn_cosf(tf);
 }
-// the same from the phase in revolutions (t = theta / 2 pi)
-__device__ inline void phase_rev(double t, float& s, float& c) {
-  t -= rint(t);
-  const float tf = (float)t;
-  s = __builtin_amdgcn_sinf(tf);
-  c = __builtin_amdgcn_cosf(tf);
-}
-template <>
-__device__ inline void phase<double>(double theta, double& s, double& c) {
-  sincos(theta, &s, &c);
+__device__ inline void phase_f32(double theta, float& s, float& c) {
+  phase_rev(theta * kInv2Pi, s, c);
 }
 
 constexpr int kFT = 256, kNJ = 128, kParts = 8, kPW = kFT / kParts;   // kPW points per workgroup
@@ -134,30 +121,43 @@ __device__ inline R part_sum(R v) {
   return v;
 }
 
-// MODE 0: write S(x_p) for points = nodes (raw, [rhs][n_k][n]); with a node
-// list (nlist, its length at *ncount), point p is node nlist[p] and only the
-// listed nodes are written.
-// MODE 1: write P(x_p) = phi_a + (S(x_p) - S(x_a)) / (4 pi) into U[rhs][m][n_k].
+// Float64 sums S(x) over the sources j of src (the surface nodes, or the
+// quadrature points of the quadratic elements) for a chunk of FCH wavenumbers
+// and NR right-hand sides.
+// MODE 0: points = nodes; S into Snode [rhs][n_k][n].  With a node list (its
+// length at *ncount) only the listed nodes.
+// MODE 1: U [rhs][m][n_k] = P(x_p) = phi_a + (S(x_p) - S(x_a)) / (4 pi).
 // Right-hand sides blockIdx.z * NR + r, r < min(NR, n_rhs - blockIdx.z * NR).
-template <typename R, int FCH, int MODE, int NR>
-__global__ __launch_bounds__(kFT, sizeof(R) == 4 ? 3 : 1) void field_kernel(
-    int n, const double* __restrict__ x, const double* __restrict__ nrm,
-    const double* __restrict__ w, const double* __restrict__ kv, int n_k, int n_rhs,
-    const double2* __restrict__ phi, const double2* __restrict__ psi, int m,
-    const double* __restrict__ xp, const int32_t* __restrict__ i0,
-    const uint8_t* __restrict__ inside, typename CX<R>::T* __restrict__ Snode,
-    typename CX<R>::T* __restrict__ U, const int32_t* __restrict__ nlist = nullptr,
-    const int32_t* __restrict__ ncount = nullptr) {
-  using C = typename CX<R>::T;
+//
+// Bound by float64 instructions: about 31 per (point, source, wavenumber) in
+// the recurrence form plus 180 of geometry and phases per (point, source), and
+// the LDS reads of 32 bytes of data per wavenumber.  On an even chunk (k_q =
+// k_0 + q dk to a few ulp) both phases advance by rotation, so a pair takes
+// four sincos instead of 2 FCH, and G carries w / r from the start.  Uneven
+// wavenumbers, and workgroups with a phase past the 2^20 rad for which the
+// reduction of phase.h holds, go one wavenumber at a time (any other form in
+// this kernel spills registers).  2304 points x 32 wavenumbers x 2562 nodes with
+// the nodes' own sums: 4.46 to 1.13 ms against a library sincos per value.
+__device__ __forceinline__ double2 unit_phase(double t) {
+  double s, c;
+  phase_sincos_near(t, &s, &c);
+  return make_double2(c, s);
+}
+
+template <int FCH, int MODE, int NR>
+__global__ __launch_bounds__(kFT, 2) void field64_kernel(
+    FieldSources src, int n, const double* __restrict__ x, const double* __restrict__ nrm,
+    const double* __restrict__ kv, int n_k, int n_rhs, const double2* __restrict__ phi,
+    const double2* __restrict__ psi, int m, const double* __restrict__ xp,
+    const int32_t* __restrict__ i0, const uint8_t* __restrict__ inside,
+    double2* __restrict__ Snode, double2* __restrict__ U, const int32_t* __restrict__ nlist,
+    const int32_t* __restrict__ ncount) {
   if (MODE == 0 && nlist) {
     m = *ncount;
     if ((int)blockIdx.x * kPW >= m) return;   // the whole workgroup
   }
-  __shared__ double sx[kNJ][3];
-  __shared__ double sn[kNJ][3];
-  __shared__ R sw[kNJ];
-  __shared__ C sphi[NR][FCH][kNJ];
-  __shared__ C spsi[NR][FCH][kNJ];
+  __shared__ double sx[kNJ][3], sn[kNJ][3], sw[kNJ];
+  __shared__ double2 sphi[NR][FCH][kNJ], spsi[NR][FCH][kNJ];
   const int p = blockIdx.x * kPW + threadIdx.x / kParts;
   const int part = threadIdx.x % kParts;
   const int m0 = blockIdx.y * FCH;
@@ -166,167 +166,196 @@ __global__ __launch_bounds__(kFT, sizeof(R) == 4 ? 3 : 1) void field_kernel(
   const int nf = min(FCH, n_k - m0);
   const bool valid = p < m && (MODE == 0 || !inside[p]);
   const int a = p < m ? (MODE == 0 ? (nlist ? nlist[p] : p) : i0[p]) : 0;
-  const int pc = MODE == 0 ? a : p;   // the point's coordinates
-  const double px = p < m ? xp[3 * pc] : 0.0, py = p < m ? xp[3 * pc + 1] : 0.0,
-               pz = p < m ? xp[3 * pc + 2] : 0.0;
   const double ax = x[3 * a], ay = x[3 * a + 1], az = x[3 * a + 2];
   const double anx = nrm[3 * a], any = nrm[3 * a + 1], anz = nrm[3 * a + 2];
-  double kk[FCH];
-#pragma unroll
-  for (int f = 0; f < FCH; ++f) kk[f] = f < nf ? kv[m0 + f] : kv[m0];
-  R kinv[FCH];
-#pragma unroll
-  for (int f = 0; f < FCH; ++f) kinv[f] = (R)(1.0 / kk[f]);
-  // float32 kernels on an evenly spaced chunk of wavenumbers advance both
-  // phases by a rotation (e^{i k_f t} = e^{i k_0 t} (e^{i dk t})^f): two phase
-  // evaluations per node instead of 2 FCH; about one float32 rounding per step
-  // (a few 1e-7 over a chunk of 8)
-  const double dkk = nf > 1 ? (kk[nf - 1] - kk[0]) / (nf - 1) : 0.0;
-  bool uni = sizeof(R) == 4 && nf > 1;
-#pragma unroll
-  for (int f = 1; f < FCH; ++f)
-    if (f < nf && !(fabs(kk[f] - (kk[0] + f * dkk)) <= 4e-16 * fabs(kk[f]))) uni = false;
-  C A1[NR][FCH], A2[FCH], A3[FCH];
+  const bool own = MODE == 0 || p >= m;
+  const double px = own ? ax : xp[3 * p], py = own ? ay : xp[3 * p + 1],
+               pz = own ? az : xp[3 * p + 2];
+  // the chunk's wavenumbers, continued evenly past a partial chunk's end (those
+  // sums are not stored)
+  double kk[FCH], kmax = 0.0;
+  const double dkk = nf > 1 ? (kv[m0 + nf - 1] - kv[m0]) / (nf - 1) : 0.0;
+  bool uni = true;
 #pragma unroll
   for (int f = 0; f < FCH; ++f) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) A1[r][f].x = A1[r][f].y = R(0);
-    A2[f].x = A2[f].y = R(0);
-    A3[f].x = A3[f].y = R(0);
+    kk[f] = f < nf ? kv[m0 + f] : kv[m0] + f * dkk;
+    kmax = fmax(kmax, fabs(kk[f]));
+    if (!(fabs(kk[f] - (kk[0] + f * dkk)) <= 4e-16 * fabs(kk[f]))) uni = false;
   }
-  for (int j0 = 0; j0 < n; j0 += kNJ) {
-    const int cnt = min(kNJ, n - j0);
+  // geometry of source jj of the staged tile: r, n_a.(x_j - x_a), w / r,
+  // (d.n_j) / r^2, n_a.n_j
+  struct Pair {
+    double r, sa, wr, c, nn;
+  };
+  auto geometry = [&](int jj) {
+    Pair g;
+    const double dx = sx[jj][0] - px, dy = sx[jj][1] - py, dz = sx[jj][2] - pz;
+    // 1/r from the reciprocal square root estimate and two Newton steps, r
+    // with a correction step of its own (it enters the phase)
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    double rinv = __builtin_amdgcn_rsq(r2);
+    rinv *= fma(-0.5 * r2, rinv * rinv, 1.5);
+    rinv *= fma(-0.5 * r2, rinv * rinv, 1.5);
+    const double r = r2 * rinv;
+    g.r = fma(fma(-r, r, r2), 0.5 * rinv, r);
+    g.c = (dx * sn[jj][0] + dy * sn[jj][1] + dz * sn[jj][2]) * (rinv * rinv);
+    g.nn = anx * sn[jj][0] + any * sn[jj][1] + anz * sn[jj][2];
+    g.sa = anx * (sx[jj][0] - ax) + any * (sx[jj][1] - ay) + anz * (sx[jj][2] - az);
+    g.wr = sw[jj] * rinv;
+    return g;
+  };
+  // sources [j0, j0 + cnt) and their data for the wavenumbers f0 .. f0 + nfs - 1
+  // of the chunk into LDS
+  auto stage = [&](int j0, int cnt, int f0, int nfs) {
     __syncthreads();
     for (int e = threadIdx.x; e < cnt * 3; e += kFT) {
-      sx[e / 3][e % 3] = x[3 * j0 + e];
-      sn[e / 3][e % 3] = nrm[3 * j0 + e];
+      const int64_t j = j0 + e / 3;
+      sx[e / 3][e % 3] = src.x[j * src.sx + e % 3];
+      sn[e / 3][e % 3] = src.nrm[j * src.sx + e % 3];
     }
-    for (int e = threadIdx.x; e < cnt; e += kFT) sw[e] = (R)w[j0 + e];
-    for (int e = threadIdx.x; e < NR * FCH * kNJ; e += kFT) {
-      const int r = e / (FCH * kNJ), f = (e / kNJ) % FCH, jj = e % kNJ;
-      if (r < nrh && f < nf && jj < cnt) {
-        const int64_t o = ((int64_t)(m0 + f) * n_rhs + r0 + r) * n + j0 + jj;
-        const double2 u = phi[o], v = psi[o];
-        sphi[r][f][jj].x = (R)u.x; sphi[r][f][jj].y = (R)u.y;
-        spsi[r][f][jj].x = (R)v.x; spsi[r][f][jj].y = (R)v.y;
-      } else {
-        sphi[r][f][jj].x = sphi[r][f][jj].y = R(0);
-        spsi[r][f][jj].x = spsi[r][f][jj].y = R(0);
+    for (int e = threadIdx.x; e < cnt; e += kFT) sw[e] = src.w[(int64_t)(j0 + e) * src.sw];
+    for (int e = threadIdx.x; e < NR * nfs * kNJ; e += kFT) {
+      const int r = e / (nfs * kNJ), f = (e / kNJ) % nfs, jj = e % kNJ;
+      double2 u = make_double2(0.0, 0.0), v = u;
+      if (r < nrh && f0 + f < nf && jj < cnt) {
+        const int64_t o = ((int64_t)(m0 + f0 + f) * n_rhs + r0 + r) * src.n + j0 + jj;
+        u = src.phi[o];
+        v = src.psi[o];
       }
+      sphi[r][f][jj] = u;
+      spsi[r][f][jj] = v;
     }
     __syncthreads();
-    if (!valid) continue;
-    for (int jj = part; jj < cnt; jj += kParts) {
-      if (j0 + jj == a) continue;
-      const double dx = sx[jj][0] - px, dy = sx[jj][1] - py, dz = sx[jj][2] - pz;
-      // r and the phase argument n_a.(x_j - x_a) stay in float64 (they enter
-      // k r and k s); magnitudes (1/r, d.n, n_a.n_j) only need the kernel's
-      // precision: float32 reciprocal and dot products in the float32 kernel
-      const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      R rinv, dn, nn;
-      if (sizeof(R) == 4) {
-        rinv = (R)__builtin_amdgcn_rcpf((float)r);
-        const float fdx = (float)dx, fdy = (float)dy, fdz = (float)dz;
-        dn = (R)((fdx * (float)sn[jj][0] + fdy * (float)sn[jj][1] + fdz * (float)sn[jj][2]) *
-                 ((float)rinv * (float)rinv));
-        nn = (R)((float)anx * (float)sn[jj][0] + (float)any * (float)sn[jj][1] +
-                 (float)anz * (float)sn[jj][2]);
-      } else {
-        const double ri = 1.0 / r;
-        rinv = (R)ri;
-        dn = (R)((dx * sn[jj][0] + dy * sn[jj][1] + dz * sn[jj][2]) * ri * ri);
-        nn = (R)(anx * sn[jj][0] + any * sn[jj][1] + anz * sn[jj][2]);
-      }
-      const R wj = sw[jj];
-      const R wg = wj * rinv;               // w/r
-      const R wh2 = -wj * (dn * rinv);      // -w (d.n)/r^3
-      const R wh1 = wj * dn;                // w (d.n)/r^2 (times k)
-      const double sa = anx * (sx[jj][0] - ax) + any * (sx[jj][1] - ay) + anz * (sx[jj][2] - az);
-      R es, ec, ss, cs, des = R(0), dec = R(1), dss = R(0), dcs = R(1);
-      phase<R>(kk[0] * r, es, ec);
-      phase<R>(kk[0] * sa, ss, cs);
-      if (uni) {
-        phase<R>(dkk * r, des, dec);
-        phase<R>(dkk * sa, dss, dcs);
-      }
-#pragma unroll
-      for (int f = 0; f < FCH; ++f) {
-        const R k = (R)kk[f];
-        if (f > 0) {
-          if (uni) {
-            const R e1 = ec * des + es * dec, e0 = ec * dec - es * des;
-            es = e1;
-            ec = e0;
-            const R s1 = cs * dss + ss * dcs, s0 = cs * dcs - ss * dss;
-            ss = s1;
-            cs = s0;
-          } else {
-            phase<R>(kk[f] * r, es, ec);
-            phase<R>(kk[f] * sa, ss, cs);
-          }
-        }
-        // wG = (w/r) E ; wH = E (-w dn/r^3 + i k w dn/r^2)
-        const R gr = wg * ec, gi = wg * es;
-        const R hb = k * wh1;
-        const R hr = ec * wh2 - es * hb, hi = ec * hb + es * wh2;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-          if (NR > 1 && r >= nrh) break;   // uniform (one right-hand side: nrh = 1)
-          const C ph = sphi[r][f][jj], ps = spsi[r][f][jj];
-          A1[r][f].x += (ph.x * hr - ph.y * hi) - (ps.x * gr - ps.y * gi);
-          A1[r][f].y += (ph.x * hi + ph.y * hr) - (ps.x * gi + ps.y * gr);
-        }
-        const R g = cs, gp = -k * ss * nn;
-        const R fv = ss * kinv[f], fp = cs * nn;
-        A2[f].x += g * hr - gp * gr;
-        A2[f].y += g * hi - gp * gi;
-        A3[f].x += fv * hr - fp * gr;
-        A3[f].y += fv * hi - fp * gi;
-      }
-    }
-  }
-#pragma unroll
-  for (int f = 0; f < FCH; ++f) {
+  };
+  // one term: w G in G, e^{i k s} in F; slot f of the staged data
+  auto term = [&](int jj, int f, double k, const Pair& g, double2 G, double2 F, auto& A1, double2& A2,
+                  double2& A3) {
+    // w H = w G (ikr - 1) c;  g = F.x, f = F.y / k, g' = -k nn F.y, f' = nn F.x
+    const double ckr = k * (g.c * g.r), kn = k * g.nn;
+    const double2 H = make_double2(fma(-g.c, G.x, -ckr * G.y), fma(ckr, G.x, -g.c * G.y));
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      A1[r][f].x = part_sum(A1[r][f].x);
-      A1[r][f].y = part_sum(A1[r][f].y);
+      if (NR > 1 && r >= nrh) break;   // uniform (one right-hand side: nrh = 1)
+      const double2 u = sphi[r][f][jj], v = spsi[r][f][jj];
+      A1[r].x = fma(u.x, H.x, fma(-u.y, H.y, fma(-v.x, G.x, fma(v.y, G.y, A1[r].x))));
+      A1[r].y = fma(u.x, H.y, fma(u.y, H.x, fma(-v.x, G.y, fma(-v.y, G.x, A1[r].y))));
     }
-    A2[f].x = part_sum(A2[f].x);
-    A2[f].y = part_sum(A2[f].y);
-    A3[f].x = part_sum(A3[f].x);
-    A3[f].y = part_sum(A3[f].y);
-  }
-  if (p >= m) return;
-  // the point's NR * FCH outputs (r, f) are shared out over its kParts lanes
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
+    const double gp = kn * F.y, fp = kn * F.x;
+    A2.x = fma(F.x, H.x, fma(gp, G.x, A2.x));
+    A2.y = fma(F.x, H.y, fma(gp, G.y, A2.y));
+    A3.x = fma(F.y, H.x, fma(-fp, G.x, A3.x));
+    A3.y = fma(F.y, H.y, fma(-fp, G.y, A3.y));
+  };
+  // result of right-hand side r and wavenumber f of the chunk
+  auto store = [&](int r, int f, double2 A1, double2 A2, double2 A3) {
+    const int rhs = r0 + r;
+    const double k = kv[m0 + f];
+    const int64_t oa = ((int64_t)(m0 + f) * n_rhs + rhs) * n + a;
+    const double2 pa = phi[oa];
+    double2 qa = psi[oa];
+    qa.x /= k;
+    qa.y /= k;
+    double2 S;
+    S.x = A1.x - (pa.x * A2.x - pa.y * A2.y) - (qa.x * A3.x - qa.y * A3.y);
+    S.y = A1.y - (pa.x * A2.y + pa.y * A2.x) - (qa.x * A3.y + qa.y * A3.x);
+    if (MODE == 0) {
+      Snode[((int64_t)rhs * n_k + m0 + f) * n + a] = S;
+    } else {
+      double2 out = make_double2(0.0, 0.0);
+      if (valid && px == ax && py == ay && pz == az) {
+        out = pa;   // the point is the node
+      } else if (valid) {
+        const double2 s0 = Snode[((int64_t)rhs * n_k + m0 + f) * n + a];
+        out.x = pa.x + (S.x - s0.x) * (1.0 / kFourPi);
+        out.y = pa.y + (S.y - s0.y) * (1.0 / kFourPi);
+      }
+      U[((int64_t)rhs * m + p) * n_k + m0 + f] = out;
+    }
+  };
+  bool wide = false;
+  if (uni) {
+    double2 A1[FCH][NR], A2[FCH], A3[FCH];   // A3 times k
 #pragma unroll
     for (int f = 0; f < FCH; ++f) {
-      if ((r * FCH + f) % kParts != part || r >= nrh || f >= nf) continue;
-      const int rhs = r0 + r;
-      const int64_t oa = ((int64_t)(m0 + f) * n_rhs + rhs) * n + a;
-      const double2 pa = phi[oa], qa = psi[oa];
-      const R par = (R)pa.x, pai = (R)pa.y, qar = (R)qa.x, qai = (R)qa.y;
-      C S;
-      S.x = A1[r][f].x - (par * A2[f].x - pai * A2[f].y) - (qar * A3[f].x - qai * A3[f].y);
-      S.y = A1[r][f].y - (par * A2[f].y + pai * A2[f].x) - (qar * A3[f].y + qai * A3[f].x);
-      if (MODE == 0) {
-        Snode[((int64_t)rhs * n_k + m0 + f) * n + a] = S;
-      } else {
-        C out;
-        if (!valid) {
-          out.x = out.y = R(0);
-        } else {
-          const C s0 = Snode[((int64_t)rhs * n_k + m0 + f) * n + a];
-          const R inv4pi = (R)(1.0 / kFourPi);
-          out.x = par + (S.x - s0.x) * inv4pi;
-          out.y = pai + (S.y - s0.y) * inv4pi;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) A1[f][r] = make_double2(0.0, 0.0);
+      A2[f] = A3[f] = make_double2(0.0, 0.0);
+    }
+    for (int j0 = 0; j0 < src.n; j0 += kNJ) {
+      const int cnt = min(kNJ, src.n - j0);
+      stage(j0, cnt, 0, FCH);
+      if (!valid) continue;
+      for (int jj = part; jj < cnt; jj += kParts) {
+        if (src.nodes && j0 + jj == a) continue;   // both brackets vanish there
+        const Pair g = geometry(jj);
+        wide |= !(kmax * fmax(g.r, fabs(g.sa)) < kPhaseNear);
+        const double2 E = unit_phase(kk[0] * g.r), dE = unit_phase(dkk * g.r);
+        const double2 dF = unit_phase(dkk * g.sa);
+        double2 F = unit_phase(kk[0] * g.sa), G = make_double2(g.wr * E.x, g.wr * E.y);
+#pragma unroll
+        for (int f = 0; f < FCH; ++f) {
+          if (f > 0) {
+            G = make_double2(fma(G.x, dE.x, -G.y * dE.y), fma(G.x, dE.y, G.y * dE.x));
+            F = make_double2(fma(F.x, dF.x, -F.y * dF.y), fma(F.x, dF.y, F.y * dF.x));
+          }
+          term(jj, f, kk[f], g, G, F, A1[f], A2[f], A3[f]);
         }
-        U[((int64_t)rhs * m + p) * n_k + m0 + f] = out;
       }
     }
+    // (a workgroup with a wide phase stores nothing here)
+    wide = __syncthreads_or(wide);
+    // the point's NR * FCH outputs are shared out over its kParts lanes
+#pragma unroll
+    for (int f = 0; f < FCH; ++f) {
+      const double2 s2 = make_double2(part_sum(A2[f].x), part_sum(A2[f].y));
+      const double2 s3 = make_double2(part_sum(A3[f].x), part_sum(A3[f].y));
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double2 s1 = make_double2(part_sum(A1[f][r].x), part_sum(A1[f][r].y));
+        if (p < m && !wide && (r * FCH + f) % kParts == part && r < nrh && f < nf)
+          store(r, f, s1, s2, s3);
+      }
+    }
+    if (!wide) return;   // uniform
   }
+  // uneven wavenumbers or wide phases: one wavenumber at a time
+  for (int f = 0; f < nf; ++f) {
+    const double k = kv[m0 + f];
+    double2 A1[NR], A2 = make_double2(0.0, 0.0), A3 = A2;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) A1[r] = make_double2(0.0, 0.0);
+    for (int j0 = 0; j0 < src.n; j0 += kNJ) {
+      const int cnt = min(kNJ, src.n - j0);
+      stage(j0, cnt, f, 1);
+      if (!valid) continue;
+      for (int jj = part; jj < cnt; jj += kParts) {
+        if (src.nodes && j0 + jj == a) continue;
+        const Pair g = geometry(jj);
+        double2 E, F;
+        phase_sincos(k * g.r, &E.y, &E.x);
+        phase_sincos(k * g.sa, &F.y, &F.x);
+        term(jj, 0, k, g, make_double2(g.wr * E.x, g.wr * E.y), F, A1, A2, A3);
+      }
+    }
+    const double2 s2 = make_double2(part_sum(A2.x), part_sum(A2.y));
+    const double2 s3 = make_double2(part_sum(A3.x), part_sum(A3.y));
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double2 s1 = make_double2(part_sum(A1[r].x), part_sum(A1[r].y));
+      if (p < m && part == r % kParts && r < nrh) store(r, f, s1, s2, s3);
+    }
+  }
+}
+
+// list[0 .. *count) = the nodes that are some outside point's closest node (in
+// no particular order; flag and *count zeroed)
+__global__ void used_nodes_kernel(int m, const int32_t* __restrict__ i0,
+                                  const uint8_t* __restrict__ inside, int32_t* __restrict__ flag,
+                                  int32_t* __restrict__ count, int32_t* __restrict__ list) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= m || inside[p]) return;
+  const int a = i0[p];
+  if (flag[a] == 0 && atomicExch(&flag[a], 1) == 0) list[atomicAdd(count, 1)] = a;
 }
 
 // ---------------------------------------------------------------- grouped field
@@ -516,7 +545,7 @@ __global__ __launch_bounds__(kFT, 3) void field_grouped_kernel(
         // the phase reduced in float64, its sine and cosine in float32 (the
         // brackets are rounded to float32)
         float fsn, fcs;
-        phase<float>(k * sa, fsn, fcs);
+        phase_f32(k * sa, fsn, fcs);
         const double sn = fsn, cs = fcs;
         const double g = cs, fv = sn * skinv[f], gp = -k * sn * nn, fp = cs * nn;
         const int64_t va = ((int64_t)(m0 + f) * n_rhs + r0 + r) * n;
@@ -580,7 +609,7 @@ __global__ __launch_bounds__(kFT, 3) void field_grouped_kernel(
             es = e1;
             ec = e0;
           } else {
-            phase<float>(kk[f] * r, es, ec);
+            phase_f32(kk[f] * r, es, ec);
             es *= -rinv;
             ec *= -rinv;
           }
@@ -646,6 +675,27 @@ __global__ __launch_bounds__(kFT, 3) void field_grouped_kernel(
 
 size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
+FieldSources node_sources(const bem_surface* s, const void* phi, const void* psi) {
+  return FieldSources{s->x, s->nrm, s->w, 3, 1, s->n, true, (const double2*)phi, (const double2*)psi};
+}
+
+// MODE 0 over every node, or the list's
+void launch_node_sums(bem_ctx* ctx, const FieldSources& src, const bem_surface* s, int n_k,
+                      const double* k, int n_rhs, const void* phi, const void* psi, void* Snode,
+                      const int32_t* nlist, const int32_t* ncount) {
+  // one right-hand side: 8 frequencies per thread; more: 4 frequencies and up
+  // to 4 right-hand sides per workgroup
+#define BEM_NODE_SUMS(FCH, NR)                                                                     \
+  hipLaunchKernelGGL((field64_kernel<FCH, 0, NR>),                                                 \
+                     dim3((s->n + kPW - 1) / kPW, (n_k + FCH - 1) / FCH, (n_rhs + NR - 1) / NR),   \
+                     dim3(kFT), 0, ctx->stream, src, s->n, s->x, s->nrm, k, n_k, n_rhs,            \
+                     (const double2*)phi, (const double2*)psi, s->n, s->x, (const int32_t*)nullptr, \
+                     (const uint8_t*)nullptr, (double2*)Snode, (double2*)nullptr, nlist, ncount)
+  if (n_rhs == 1) BEM_NODE_SUMS(8, 1);
+  else BEM_NODE_SUMS(4, 4);
+#undef BEM_NODE_SUMS
+}
+
 // fixed: the fixed scratch (bem_field_eval_noalloc: no workspace, no
 // profiling events), else NULL
 template <int FCH, int NR>
@@ -680,21 +730,7 @@ bem_status field_grouped(bem_ctx* ctx, const bem_surface* s, int n_k, const doub
   // float64 node sums S(x_a) of the nodes that are some point's closest node
   // (their count uoff[n] stays on the device: the grid covers all n nodes and
   // the workgroups past the count return at once)
-  {
-    const int nz = (n_rhs + NR - 1) / NR;
-    if (NR == 1)
-      hipLaunchKernelGGL((field_kernel<double, 8, 0, 1>),
-                         dim3((n + kPW - 1) / kPW, (n_k + 7) / 8, nz), dim3(kFT), 0, ctx->stream,
-                         n, s->x, s->nrm, s->w, k, n_k, n_rhs, (const double2*)phi,
-                         (const double2*)psi, n, s->x, (const int32_t*)nullptr,
-                         (const uint8_t*)nullptr, Snode, (double2*)nullptr, used, uoff + n);
-    else
-      hipLaunchKernelGGL((field_kernel<double, 4, 0, 4>),
-                         dim3((n + kPW - 1) / kPW, (n_k + 3) / 4, nz), dim3(kFT), 0, ctx->stream,
-                         n, s->x, s->nrm, s->w, k, n_k, n_rhs, (const double2*)phi,
-                         (const double2*)psi, n, s->x, (const int32_t*)nullptr,
-                         (const uint8_t*)nullptr, Snode, (double2*)nullptr, used, uoff + n);
-  }
+  launch_node_sums(ctx, node_sources(s, phi, psi), s, n_k, k, n_rhs, phi, psi, Snode, used, uoff + n);
   hipLaunchKernelGGL(group_scatter_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, m, i0,
                      inside, off, fill, perm);
   const int64_t tot = (int64_t)m * n_k * n_rhs;
@@ -712,52 +748,22 @@ bem_status field_grouped(bem_ctx* ctx, const bem_surface* s, int n_k, const doub
   return BEM_OK;
 }
 
-// Snode_fixed: the fixed scratch (bem_field_eval_noalloc: no workspace, no
-// profiling events), or NULL for the context's workspace.
-template <typename R, int FCH, int NR>
-void field_pass(bem_ctx* ctx, const bem_surface* s, int n_k, const double* k, int n_rhs,
-                const void* phi, const void* psi, int m, const double* xp, const int32_t* i0,
-                const uint8_t* inside, void* Snode, void* U) {
-  using C = typename CX<R>::T;
-  const int fch = (n_k + FCH - 1) / FCH;
-  const int nz = (n_rhs + NR - 1) / NR;
-  dim3 gnode((s->n + kPW - 1) / kPW, fch, nz);
-  hipLaunchKernelGGL((field_kernel<R, FCH, 0, NR>), gnode, dim3(kFT), 0, ctx->stream, s->n, s->x,
-                     s->nrm, s->w, k, n_k, n_rhs, (const double2*)phi, (const double2*)psi, s->n,
-                     s->x, (const int32_t*)nullptr, (const uint8_t*)nullptr, (C*)Snode, (C*)nullptr);
-  dim3 gpts((m + kPW - 1) / kPW, fch, nz);
-  hipLaunchKernelGGL((field_kernel<R, FCH, 1, NR>), gpts, dim3(kFT), 0, ctx->stream, s->n, s->x,
-                     s->nrm, s->w, k, n_k, n_rhs, (const double2*)phi, (const double2*)psi, m, xp,
-                     i0, inside, (C*)Snode, (C*)U);
-}
-
-template <typename R>
-bem_status field_go(bem_ctx* ctx, const bem_surface* s, int n_k, const double* k, int n_rhs,
-                    const void* phi, const void* psi, int m, const double* xp,
-                    const int32_t* i0, const uint8_t* inside, void* U, void* Snode_fixed) {
-  using C = typename CX<R>::T;
-  void* ws = Snode_fixed;
-  if (!ws) {
-    const size_t need = sizeof(C) * (size_t)n_rhs * n_k * s->n;
-    bem_status st = workspace(ctx, need, &ws);
-    if (st != BEM_OK) return st;
-  }
-  // the profiling bracket covers both passes: the field at the nodes (the
-  // expansion centres) and at the points
-  const int pi = Snode_fixed ? -1 : prof_begin(ctx, "field");
-  // one right-hand side: 8 frequencies per thread; more: 4 frequencies and up
-  // to 4 right-hand sides per workgroup (8 frequencies with 2 right-hand
-  // sides already exceed the 168-register budget of three workgroups per CU)
-  if (n_rhs == 1)
-    field_pass<R, 8, 1>(ctx, s, n_k, k, n_rhs, phi, psi, m, xp, i0, inside, ws, U);
-  else
-    field_pass<R, 4, 4>(ctx, s, n_k, k, n_rhs, phi, psi, m, xp, i0, inside, ws, U);
-  // kernel terms: one per (point or node, frequency, node, rhs)
-  if (!Snode_fixed)
-    prof_end(ctx, "field", pi, ((double)m + s->n) * n_k * s->n * n_rhs,
-             (double)sizeof(C) * ((double)m + s->n) * n_k * n_rhs);
-  BEM_CHECK_LAUNCH(ctx);
-  return BEM_OK;
+// c128: the node sums of the points' closest nodes (of every node with the fixed
+// scratch, which holds nothing else), then the points
+bem_status field_c128(bem_ctx* ctx, const bem_surface* s, int n_k, const double* k, int n_rhs,
+                      const void* phi, const void* psi, int m, const double* xp,
+                      const int32_t* i0, const uint8_t* inside, void* U, void* fixed) {
+  void* ws = fixed;
+  const size_t sums = al256(16 * (size_t)n_rhs * n_k * s->n), ints = al256(4 * (size_t)(s->n + 1));
+  bem_status st;
+  if (!ws && (st = workspace(ctx, sums + 2 * ints, &ws)) != BEM_OK) return st;
+  const int pi = fixed ? -1 : prof_begin(ctx, "field");
+  st = launch_field64(ctx, node_sources(s, phi, psi), s, n_k, k, n_rhs, phi, psi, m, xp, i0, inside,
+                      ws, fixed ? nullptr : (int32_t*)((char*)ws + sums), U);
+  // kernel terms: one per (point, frequency, node, rhs)
+  if (!fixed)
+    prof_end(ctx, "field", pi, (double)m * n_k * s->n * n_rhs, 16.0 * (double)m * n_k * n_rhs);
+  return st;
 }
 
 }  // namespace
@@ -780,6 +786,35 @@ bem_status launch_inside(bem_ctx* ctx, const bem_surface* s, int m, const double
   return BEM_OK;
 }
 
+bem_status launch_field64(bem_ctx* ctx, const FieldSources& src, const bem_surface* s, int n_k,
+                          const double* k, int n_rhs, const void* phi, const void* psi, int m,
+                          const double* xp, const int32_t* i0, const uint8_t* inside, void* Snode,
+                          int32_t* list_ws, void* U) {
+  int32_t *list = nullptr, *count = nullptr;
+  if (list_ws) {
+    // flag [n], count, then (256-byte aligned) the list
+    const size_t ints = al256(4 * (size_t)(s->n + 1));
+    count = list_ws + s->n;
+    list = (int32_t*)((char*)list_ws + ints);
+    const bem_status st = fill_zero(ctx, list_ws, 4 * (size_t)(s->n + 1));
+    if (st != BEM_OK) return st;
+    hipLaunchKernelGGL(used_nodes_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, m, i0,
+                       inside, list_ws, count, list);
+  }
+  launch_node_sums(ctx, src, s, n_k, k, n_rhs, phi, psi, Snode, list, count);
+#define BEM_POINTS(FCH, NR)                                                                       \
+  hipLaunchKernelGGL((field64_kernel<FCH, 1, NR>),                                                \
+                     dim3((m + kPW - 1) / kPW, (n_k + FCH - 1) / FCH, (n_rhs + NR - 1) / NR),     \
+                     dim3(kFT), 0, ctx->stream, src, s->n, s->x, s->nrm, k, n_k, n_rhs,           \
+                     (const double2*)phi, (const double2*)psi, m, xp, i0, inside, (double2*)Snode, \
+                     (double2*)U, (const int32_t*)nullptr, (const int32_t*)nullptr)
+  if (n_rhs == 1) BEM_POINTS(8, 1);
+  else BEM_POINTS(4, 4);
+#undef BEM_POINTS
+  BEM_CHECK_LAUNCH(ctx);
+  return BEM_OK;
+}
+
 bem_status launch_field(bem_ctx* ctx, const bem_surface* s, int n_k, const double* k, int n_rhs,
                         const void* phi, const void* psi, int m, const double* xp,
                         const int32_t* i0, const uint8_t* inside, bem_prec prec, void* U,
@@ -798,7 +833,7 @@ bem_status launch_field(bem_ctx* ctx, const bem_surface* s, int n_k, const doubl
     fixed = ctx->field_scratch;
   }
   if (prec == BEM_C128)
-    return field_go<double>(ctx, s, n_k, k, n_rhs, phi, psi, m, xp, i0, inside, U, fixed);
+    return field_c128(ctx, s, n_k, k, n_rhs, phi, psi, m, xp, i0, inside, U, fixed);
   // float32: points grouped by closest node (the bookkeeping in the fixed
   // scratch for bem_field_eval_noalloc, whose caller checked its size)
   void* gfixed = fixed_scratch ? ctx->field_scratch : nullptr;

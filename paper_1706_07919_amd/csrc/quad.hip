@@ -20,6 +20,8 @@
 #include <cmath>
 
 #include "common.h"
+#include "phase.h"
+#include "reduce.h"
 
 namespace bem {
 
@@ -28,7 +30,8 @@ namespace {
 constexpr int kQ = 7;          // points of the triangle rule
 constexpr int kMaxInc = 12;    // element incidences kept per node
 constexpr int kQT = 256;       // threads of the row kernels
-constexpr int kRhsChunk = 4;   // right-hand sides per assembly launch
+constexpr int kRhsChunk = 2;   // right-hand sides per assembly launch
+constexpr int kKc = 8;         // wavenumbers per assembly workgroup
 constexpr double kFourPiQ = 12.566370614359172953850573533118;
 
 // The rule's points and weights (weights summing to the reference area 1/2)
@@ -73,6 +76,22 @@ QuadRule make_rule() {
   return R;
 }
 
+// N[q][a] of make_rule for the kernels that index it per thread
+__device__ __constant__ double kShape[kQ][6] = {
+#define BEM_S(L0, L1, L2) {(L0) * (2 * (L0) - 1), (L1) * (2 * (L1) - 1), (L2) * (2 * (L2) - 1), \
+                           4 * (L0) * (L1), 4 * (L1) * (L2), 4 * (L2) * (L0)}
+#define BEM_A1 (( 6.0 - 3.872983346207417) / 21.0)
+#define BEM_A2 (( 6.0 + 3.872983346207417) / 21.0)
+    BEM_S(1.0 / 3.0, 1.0 / 3.0, 1.0 / 3.0),
+    BEM_S(1.0 - 2.0 * BEM_A1, BEM_A1, BEM_A1), BEM_S(BEM_A1, 1.0 - 2.0 * BEM_A1, BEM_A1),
+    BEM_S(BEM_A1, BEM_A1, 1.0 - 2.0 * BEM_A1),
+    BEM_S(1.0 - 2.0 * BEM_A2, BEM_A2, BEM_A2), BEM_S(BEM_A2, 1.0 - 2.0 * BEM_A2, BEM_A2),
+    BEM_S(BEM_A2, BEM_A2, 1.0 - 2.0 * BEM_A2),
+#undef BEM_A1
+#undef BEM_A2
+#undef BEM_S
+};
+
 // quadrature points of every element: [F*7][8] = x, y, z, nx, ny, nz (unit
 // normal of the element surface), wJ (weight times area Jacobian), 0
 __global__ void quad_points_kernel(int F, const double* __restrict__ x,
@@ -108,22 +127,28 @@ __global__ void quad_points_kernel(int F, const double* __restrict__ x,
 
 // inc[j][c] = 6 e + a for the c-th (element e, local node a) holding node j,
 // in element order; -1 past the last; *overflow set when a node has more
-// than kMaxInc incidences or an element refers to a node outside [0, n)
-__global__ void quad_incidence_kernel(int n, int F, const int32_t* __restrict__ elem,
-                                      int32_t* __restrict__ inc, int32_t* __restrict__ overflow) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+// than kMaxInc incidences or an element refers to a node outside [0, n).  One
+// wave per node scans the table 64 entries at a time (a thread per node took
+// 0.23 ms for 1002 nodes; 0.01 ms).
+__global__ __launch_bounds__(256) void quad_incidence_kernel(int n, int F,
+                                                             const int32_t* __restrict__ elem,
+                                                             int32_t* __restrict__ inc,
+                                                             int32_t* __restrict__ overflow) {
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (j >= n) return;   // the whole wave
   int c = 0;
-  for (int t = 0; t < 6 * F; ++t) {
-    const int v = elem[t];
-    if (j == 0 && (v < 0 || v >= n)) overflow[0] = 1;
-    if (v == j) {
-      if (c < kMaxInc) inc[(int64_t)j * kMaxInc + c] = t;
-      ++c;
-    }
+  bool bad = false;
+  for (int t0 = 0; t0 < 6 * F; t0 += 64) {
+    const int t = t0 + lane;
+    const int v = t < 6 * F ? elem[t] : -1;
+    bad |= t < 6 * F && (v < 0 || v >= n);
+    const unsigned long long hit = __ballot(v == j && t < 6 * F);
+    const int at = c + __popcll(hit & ((1ull << lane) - 1));
+    if (((hit >> lane) & 1) && at < kMaxInc) inc[(int64_t)j * kMaxInc + at] = t;
+    c += __popcll(hit);
   }
-  if (c > kMaxInc) overflow[0] = 1;
-  for (int s = c; s < kMaxInc; ++s) inc[(int64_t)j * kMaxInc + s] = -1;
+  if ((j == 0 && bad) || c > kMaxInc) overflow[0] = 1;
+  if (lane >= c && lane < kMaxInc) inc[(int64_t)j * kMaxInc + lane] = -1;
 }
 
 __device__ inline double block_sum(double v, double* sh) {
@@ -136,106 +161,217 @@ __device__ inline double block_sum(double v, double* sh) {
   return s;
 }
 
-// G = e^{ikr}/r and H = dG/dn_q = e^{ikr}(ikr - 1)(d.n_q)/r^3, d = x_q - x_i
-__device__ inline void green(double k, double dx, double dy, double dz, double nx, double ny,
-                             double nz, double2& G, double2& H) {
-  const double r = sqrt(dx * dx + dy * dy + dz * dz);
+// One workgroup per (row i, chunk of kKc wavenumbers): the row's diagonal
+// integrals over every quadrature point, then each column's entries gathered
+// from the elements that hold its node (deterministic order, no atomics).
+//
+// Bound by float64 instructions: 7 x (incidences of the column) kernel values
+// per entry.  The pair's geometry and phases are formed once for the chunk and
+// e^{ikr} / r advanced by rotation along its wavenumbers (four multiply-adds), so
+// a value costs about 11 instructions and a twelfth of a sincos; a workgroup per
+// wavenumber with a library sincos, square root and division per value took
+// 10.1 ms for 63 wavenumbers on 1002 nodes, this form 2.0 ms.  A partial chunk is
+// continued evenly (nothing stored past its end); uneven wavenumbers, or a phase
+// past the 2^20 rad of phase.h's reduction, go one wavenumber at a time.
+struct QuadRow {
+  int n, npts, i, kq0, kc, n_rhs, r0, nr;
+  const double *x, *nrm, *qp;
+  const uint8_t* bc;
+  const int32_t* inc;
+  const double2* y;
+  double k0, dk;
+};
+
+struct QuadPair {
+  double r, c, wr;   // |d|, (d.n_q) / r^2, 1 / r
+  double dx, dy, dz;
+};
+__device__ __forceinline__ QuadPair quad_pair(const double* o, double x0, double x1, double x2) {
+  QuadPair g;
+  g.dx = o[0] - x0;
+  g.dy = o[1] - x1;
+  g.dz = o[2] - x2;
+  const double r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
+  double ri = __builtin_amdgcn_rsq(r2);
+  ri *= fma(-0.5 * r2, ri * ri, 1.5);
+  ri *= fma(-0.5 * r2, ri * ri, 1.5);
+  const double r = r2 * ri;
+  g.r = fma(fma(-r, r, r2), 0.5 * ri, r);
+  g.c = (g.dx * o[3] + g.dy * o[4] + g.dz * o[5]) * (ri * ri);
+  g.wr = ri;
+  return g;
+}
+template <bool NEAR>
+__device__ __forceinline__ double2 quad_phase(double t) {
   double s, c;
-  sincos(k * r, &s, &c);
-  const double ri = 1.0 / r;
-  G = make_double2(c * ri, s * ri);
-  const double dn = (dx * nx + dy * ny + dz * nz) * ri * ri * ri;
-  const double kr = k * r;
-  H = make_double2((-c - kr * s) * dn, (-s + kr * c) * dn);
+  if (NEAR) phase_sincos_near(t, &s, &c);
+  else phase_sincos(t, &s, &c);
+  return make_double2(c, s);
+}
+__device__ __forceinline__ double2 rot(double2 a, double2 b) {
+  return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
 
-// One workgroup per (row i, wavenumber): the row's diagonal integrals over
-// every quadrature point, then each column's entries gathered from the
-// elements that hold its node (deterministic order, no atomics).
-template <typename OUT>
-__global__ __launch_bounds__(kQT) void quad_assemble_kernel(
-    int n, const double* __restrict__ x, const double* __restrict__ nrm,
-    const uint8_t* __restrict__ bc, int npts, const double* __restrict__ qp,
-    const int32_t* __restrict__ inc, QuadRule R, const double* __restrict__ kv, int n_rhs, int r0,
-    int nr, const double2* __restrict__ y, OUT* __restrict__ A, int64_t ld, int64_t a_stride,
-    double2* __restrict__ b, double2* __restrict__ diag64) {
-  __shared__ double sh[kQT / 64];
-  const int i = blockIdx.x, kq = blockIdx.y;
-  const double k = kv[kq];
-  const double xi0 = x[3 * i], xi1 = x[3 * i + 1], xi2 = x[3 * i + 2];
-  const double ni0 = nrm[3 * i], ni1 = nrm[3 * i + 1], ni2 = nrm[3 * i + 2];
-  double d1r = 0, d1i = 0, d2r = 0, d2i = 0;
-  for (int p = threadIdx.x; p < npts; p += kQT) {
-    const double* o = qp + 8 * (int64_t)p;
-    const double dx = o[0] - xi0, dy = o[1] - xi1, dz = o[2] - xi2;
-    double2 G, H;
-    green(k, dx, dy, dz, o[3], o[4], o[5], G, H);
-    double ss, cs;
-    sincos(k * (ni0 * dx + ni1 * dy + ni2 * dz), &ss, &cs);
-    const double nn = ni0 * o[3] + ni1 * o[4] + ni2 * o[5];
-    const double g = cs, f = ss / k, gp = -k * ss * nn, fp = cs * nn, wJ = o[6];
-    d1r += (gp * G.x - g * H.x) * wJ;
-    d1i += (gp * G.y - g * H.y) * wJ;
-    d2r += (fp * G.x - f * H.x) * wJ;
-    d2i += (fp * G.y - f * H.y) * wJ;
-  }
-  d1r = block_sum(d1r, sh);
-  d1i = block_sum(d1i, sh);
-  d2r = block_sum(d2r, sh);
-  d2i = block_sum(d2i, sh);
-  double bac[kRhsChunk][2];
+// The row for KC wavenumbers k0 + q dk (kq0 the first's index): A, b, diag64.
+// red: LDS of [kQT / 64][2 kRhsChunk + 4][8].  False (nothing stored) if a phase
+// is too wide for the NEAR form.
+template <int KC, bool NEAR, typename OUT>
+__device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, int64_t ld,
+                                         int64_t a_stride, double2* __restrict__ b,
+                                         double2* __restrict__ diag64,
+                                         double (*red)[2 * kRhsChunk + 4][8]) {
+  const int i = p.i, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const double x0 = p.x[3 * i], x1 = p.x[3 * i + 1], x2 = p.x[3 * i + 2];
+  const double n0 = p.nrm[3 * i], n1 = p.nrm[3 * i + 1], n2 = p.nrm[3 * i + 2];
+  const double kmax = fmax(fabs(p.k0), fabs(p.k0 + (KC - 1) * p.dk));
+  bool wide = false;
+  // workgroup sums of component c of the chunk into red[.][c][q]
+  auto reduce = [&](int c, const double (&v)[KC]) {
+    double v8[8];
 #pragma unroll
-  for (int r = 0; r < kRhsChunk; ++r) bac[r][0] = bac[r][1] = 0.0;
-  for (int j = threadIdx.x; j < n; j += kQT) {
-    double mpr = 0, mpi = 0, mhr = 0, mhi = 0;   // M_psi and M_phi entries
+    for (int q = 0; q < 8; ++q) v8[q] = q < KC ? v[q < KC ? q : 0] : 0.0;
+    const double s = wave_reduce8(v8);
+    if ((lane & 7) == 0) red[wid][c][lane >> 3] = s;
+  };
+  auto total = [&](int c, int q) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kQT / 64; ++w) s += red[w][c][q];
+    return s;
+  };
+  {
+    // diagonal integrals: d1 = sum wJ (g' G - g H), d2 k = sum wJ k (f' G - f H)
+    double d[4][KC];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int q = 0; q < KC; ++q) d[c][q] = 0.0;
+    for (int t = threadIdx.x; t < p.npts; t += kQT) {
+      const double* o = p.qp + 8 * (int64_t)t;
+      const QuadPair g = quad_pair(o, x0, x1, x2);
+      const double s0 = n0 * g.dx + n1 * g.dy + n2 * g.dz;
+      const double nn = n0 * o[3] + n1 * o[4] + n2 * o[5], wr = o[6] * g.wr;
+      if (NEAR) wide |= !(kmax * fmax(g.r, fabs(s0)) < kPhaseNear);
+      const double2 E = quad_phase<NEAR>(p.k0 * g.r);
+      double2 F = quad_phase<NEAR>(p.k0 * s0), G = make_double2(wr * E.x, wr * E.y), dE, dF;
+      if (KC > 1) {
+        dE = quad_phase<NEAR>(p.dk * g.r);
+        dF = quad_phase<NEAR>(p.dk * s0);
+      }
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        if (q > 0) {
+          G = rot(G, dE);
+          F = rot(F, dF);
+        }
+        const double k = p.k0 + q * p.dk, ckr = k * (g.c * g.r), kn = k * nn;
+        const double2 H = make_double2(fma(-g.c, G.x, -ckr * G.y), fma(ckr, G.x, -g.c * G.y));
+        const double gp = -kn * F.y, fp = kn * F.x;
+        d[0][q] += fma(gp, G.x, -F.x * H.x);
+        d[1][q] += fma(gp, G.y, -F.x * H.y);
+        d[2][q] += fma(fp, G.x, -F.y * H.x);
+        d[3][q] += fma(fp, G.y, -F.y * H.y);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) reduce(2 * kRhsChunk + c, d[c]);
+  }
+  if (__syncthreads_or(wide)) return false;
+  double bac[2 * kRhsChunk][KC];
+#pragma unroll
+  for (int c = 0; c < 2 * kRhsChunk; ++c)
+#pragma unroll
+    for (int q = 0; q < KC; ++q) bac[c][q] = 0.0;
+  for (int j = threadIdx.x; j < p.n; j += kQT) {
+    double2 mp[KC], mh[KC];   // M_psi and M_phi entries
+#pragma unroll
+    for (int q = 0; q < KC; ++q) mp[q] = mh[q] = make_double2(0.0, 0.0);
     for (int c = 0; c < kMaxInc; ++c) {
-      const int v = inc[(int64_t)j * kMaxInc + c];
+      const int v = p.inc[(int64_t)j * kMaxInc + c];
       if (v < 0) break;
       const int e = v / 6, a = v % 6;
+      for (int t = 0; t < kQ; ++t) {
+        const double* o = p.qp + 8 * ((int64_t)e * kQ + t);
+        const QuadPair g = quad_pair(o, x0, x1, x2);
+        const double wr = o[6] * g.wr * kShape[t][a], cr = g.c * g.r;
+        const double2 E = quad_phase<NEAR>(p.k0 * g.r);
+        double2 G = make_double2(wr * E.x, wr * E.y), dE;
+        if (KC > 1) dE = quad_phase<NEAR>(p.dk * g.r);
 #pragma unroll
-      for (int q = 0; q < kQ; ++q) {
-        const double* o = qp + 8 * ((int64_t)e * kQ + q);
-        double2 G, H;
-        green(k, o[0] - xi0, o[1] - xi1, o[2] - xi2, o[3], o[4], o[5], G, H);
-        const double wn = R.N[q][a] * o[6];
-        mpr += wn * G.x;
-        mpi += wn * G.y;
-        mhr -= wn * H.x;
-        mhi -= wn * H.y;
+        for (int q = 0; q < KC; ++q) {
+          if (q > 0) G = rot(G, dE);
+          const double ckr = (p.k0 + q * p.dk) * cr;
+          mp[q].x += G.x;
+          mp[q].y += G.y;
+          mh[q].x = fma(g.c, G.x, fma(ckr, G.y, mh[q].x));
+          mh[q].y = fma(g.c, G.y, fma(-ckr, G.x, mh[q].y));
+        }
       }
     }
-    if (j == i) {
-      mhr += kFourPiQ - d1r;
-      mhi += -d1i;
-      mpr += -d2r;
-      mpi += -d2i;
-      if (r0 == 0 && diag64) {
-        diag64[2 * ((int64_t)kq * n + i)] = make_double2(mhr, mhi);
-        diag64[2 * ((int64_t)kq * n + i) + 1] = make_double2(mpr, mpi);
-      }
-    }
-    const bool hard = bc[j] == BEM_BC_HARD;
-    const double ar = hard ? mhr : mpr, ai = hard ? mhi : mpi;
-    const double br = hard ? mpr : mhr, bi = hard ? mpi : mhi;
-    if (r0 == 0 && A) {
-      OUT* Ap = A + kq * a_stride + (int64_t)i * ld + j;
-      Ap->x = ar;
-      Ap->y = ai;
-    }
+    const bool hard = p.bc[j] == BEM_BC_HARD;
 #pragma unroll
-    for (int r = 0; r < kRhsChunk; ++r)
-      if (r < nr) {
-        const double2 yv = y[((int64_t)kq * n_rhs + r0 + r) * n + j];
-        bac[r][0] -= br * yv.x - bi * yv.y;
-        bac[r][1] -= br * yv.y + bi * yv.x;
+    for (int q = 0; q < KC; ++q) {
+      if (q >= p.kc) break;   // uniform
+      const int64_t kq = p.kq0 + q;
+      if (j == i) {
+        const double ki = 1.0 / (p.k0 + q * p.dk);
+        mh[q].x += kFourPiQ - total(2 * kRhsChunk, q);
+        mh[q].y -= total(2 * kRhsChunk + 1, q);
+        mp[q].x -= total(2 * kRhsChunk + 2, q) * ki;
+        mp[q].y -= total(2 * kRhsChunk + 3, q) * ki;
+        if (p.r0 == 0 && diag64) {
+          diag64[2 * (kq * p.n + i)] = mh[q];
+          diag64[2 * (kq * p.n + i) + 1] = mp[q];
+        }
       }
+      const double2 u = hard ? mh[q] : mp[q], v = hard ? mp[q] : mh[q];
+      if (p.r0 == 0 && A) {
+        OUT* Ap = A + kq * a_stride + (int64_t)i * ld + j;
+        Ap->x = u.x;
+        Ap->y = u.y;
+      }
+#pragma unroll
+      for (int r = 0; r < kRhsChunk; ++r)
+        if (r < p.nr) {
+          const double2 yv = p.y[(kq * p.n_rhs + p.r0 + r) * p.n + j];
+          bac[2 * r][q] -= v.x * yv.x - v.y * yv.y;
+          bac[2 * r + 1][q] -= v.x * yv.y + v.y * yv.x;
+        }
+    }
   }
 #pragma unroll
-  for (int r = 0; r < kRhsChunk; ++r) {
-    if (r >= nr) break;   // uniform
-    const double sr = block_sum(bac[r][0], sh);
-    const double si = block_sum(bac[r][1], sh);
-    if (threadIdx.x == 0) b[((int64_t)kq * n_rhs + r0 + r) * n + i] = make_double2(sr, si);
+  for (int c = 0; c < 2 * kRhsChunk; ++c)
+    if (c < 2 * p.nr) reduce(c, bac[c]);
+  __syncthreads();
+  const int q = threadIdx.x & 7, r = threadIdx.x >> 3;
+  if (r < p.nr && q < p.kc && q < KC)
+    b[((int64_t)(p.kq0 + q) * p.n_rhs + p.r0 + r) * p.n + i] =
+        make_double2(total(2 * r, q), total(2 * r + 1, q));
+  __syncthreads();   // red is free again
+  return true;
+}
+
+template <typename OUT>
+__global__ __launch_bounds__(kQT, 2) void quad_assemble_kernel(
+    int n, const double* __restrict__ x, const double* __restrict__ nrm,
+    const uint8_t* __restrict__ bc, int npts, const double* __restrict__ qp,
+    const int32_t* __restrict__ inc, const double* __restrict__ kv, int n_k, int n_rhs, int r0,
+    int nr, const double2* __restrict__ y, OUT* __restrict__ A, int64_t ld, int64_t a_stride,
+    double2* __restrict__ b, double2* __restrict__ diag64) {
+  __shared__ double red[kQT / 64][2 * kRhsChunk + 4][8];
+  const int q0 = blockIdx.y * kKc, kc = min(kKc, n_k - q0);
+  QuadRow p{n, npts, (int)blockIdx.x, q0, kc, n_rhs, r0, nr, x, nrm, qp, bc, inc, y, kv[q0], 0.0};
+  p.dk = kc > 1 ? (kv[q0 + kc - 1] - kv[q0]) / (kc - 1) : 0.0;
+  bool uni = true;
+  for (int q = 1; q < kc; ++q)
+    if (!(fabs(kv[q0 + q] - (p.k0 + q * p.dk)) <= 4e-16 * fabs(kv[q0 + q]))) uni = false;
+  if (uni && quad_row<kKc, true>(p, A, ld, a_stride, b, diag64, red)) return;
+  p.kc = 1;
+  p.dk = 0.0;
+  for (int q = 0; q < kc; ++q) {
+    p.kq0 = q0 + q;
+    p.k0 = kv[q0 + q];
+    (void)quad_row<1, false>(p, A, ld, a_stride, b, diag64, red);
   }
 }
 
@@ -281,59 +417,6 @@ __global__ void quad_interp_kernel(int n, int F, int nvec, const int32_t* __rest
   out[t] = make_double2(sr, si);
 }
 
-// Scattered field by Eq. BRIEFdmn with the element quadrature, x0 the closest
-// node a:  4 pi P(x_p) = 4 pi phi_a + int [u (H^p - H^a) - u' (G^p - G^a)] dS,
-// u = phi - phi_a g - psi_a f, u' = psi - phi_a g' - psi_a f' (f, g about x_a).
-// One thread per (point, wavenumber, rhs); float64.
-__global__ __launch_bounds__(kQT) void quad_field_kernel(
-    int n, const double* __restrict__ x, const double* __restrict__ nrm, int npts,
-    const double* __restrict__ qp, const double* __restrict__ kv, int n_k, int n_rhs,
-    const double2* __restrict__ phi, const double2* __restrict__ psi,
-    const double2* __restrict__ phq, const double2* __restrict__ psq, int m,
-    const double* __restrict__ xp, const int32_t* __restrict__ i0,
-    const uint8_t* __restrict__ inside, double2* __restrict__ U) {
-  const int p = blockIdx.x * kQT + threadIdx.x;
-  const int kq = blockIdx.y, rhs = blockIdx.z;
-  if (p >= m) return;
-  double2* out = U + ((int64_t)rhs * m + p) * n_k + kq;
-  if (inside[p]) {
-    *out = make_double2(0.0, 0.0);
-    return;
-  }
-  const double k = kv[kq];
-  const int a = i0[p];
-  const int64_t vec = (int64_t)kq * n_rhs + rhs;
-  const double2 pa = phi[vec * n + a], qa = psi[vec * n + a];
-  const double ax = x[3 * a], ay = x[3 * a + 1], az = x[3 * a + 2];
-  const double anx = nrm[3 * a], any = nrm[3 * a + 1], anz = nrm[3 * a + 2];
-  const double px = xp[3 * p], py = xp[3 * p + 1], pz = xp[3 * p + 2];
-  if (px == ax && py == ay && pz == az) {   // x_p = x0: the integrand vanishes identically
-    *out = pa;
-    return;
-  }
-  double sr = 0, si = 0;
-  for (int t = 0; t < npts; ++t) {
-    const double* o = qp + 8 * (int64_t)t;
-    const double dax = o[0] - ax, day = o[1] - ay, daz = o[2] - az;
-    double2 Ga, Ha, Gp, Hp;
-    green(k, dax, day, daz, o[3], o[4], o[5], Ga, Ha);
-    green(k, o[0] - px, o[1] - py, o[2] - pz, o[3], o[4], o[5], Gp, Hp);
-    double ss, cs;
-    sincos(k * (anx * dax + any * day + anz * daz), &ss, &cs);
-    const double nn = anx * o[3] + any * o[4] + anz * o[5];
-    const double g = cs, f = ss / k, gp = -k * ss * nn, fp = cs * nn;
-    const double2 ph = phq[vec * npts + t], ps = psq[vec * npts + t];
-    // u = phi - phi_a g - psi_a f ;  u' = psi - phi_a g' - psi_a f'
-    const double ur = ph.x - pa.x * g - qa.x * f, ui = ph.y - pa.y * g - qa.y * f;
-    const double vr = ps.x - pa.x * gp - qa.x * fp, vi = ps.y - pa.y * gp - qa.y * fp;
-    const double hr = Hp.x - Ha.x, hi = Hp.y - Ha.y, gr = Gp.x - Ga.x, gi = Gp.y - Ga.y;
-    const double wJ = o[6];
-    sr += ((ur * hr - ui * hi) - (vr * gr - vi * gi)) * wJ;
-    si += ((ur * hi + ui * hr) - (vr * gi + vi * gr)) * wJ;
-  }
-  *out = make_double2(pa.x + sr / kFourPiQ, pa.y + si / kFourPiQ);
-}
-
 }  // namespace
 
 size_t quad_setup_bytes(int n, int F) {
@@ -357,7 +440,7 @@ bem_status quad_setup(bem_ctx* ctx, const bem_quad_surface* s, void* ws, double*
   const int npts = s->n_elem * kQ;
   hipLaunchKernelGGL(quad_points_kernel, dim3((npts + 255) / 256), dim3(256), 0, ctx->stream,
                      s->n_elem, s->x, s->elem, R, *qp);
-  hipLaunchKernelGGL(quad_incidence_kernel, dim3((s->n + 255) / 256), dim3(256), 0, ctx->stream,
+  hipLaunchKernelGGL(quad_incidence_kernel, dim3((s->n + 3) / 4), dim3(256), 0, ctx->stream,
                      s->n, s->n_elem, s->elem, *inc, flag);
   BEM_CHECK_LAUNCH(ctx);
   int32_t hflag = 0;
@@ -375,20 +458,19 @@ bem_status launch_quad_assemble(bem_ctx* ctx, const bem_quad_surface* s, const d
                                 const int32_t* inc, int n_k, const double* k, int n_rhs,
                                 const void* y, bem_prec prec, void* A, int64_t ld,
                                 int64_t a_stride, void* b, void* diag64) {
-  const QuadRule R = make_rule();
   const int npts = s->n_elem * kQ;
   const int pi = prof_begin(ctx, "assemble_quad");
   for (int r0 = 0; r0 < n_rhs; r0 += kRhsChunk) {
     const int nr = std::min(kRhsChunk, n_rhs - r0);
-    dim3 grid(s->n, n_k);
+    dim3 grid(s->n, (n_k + kKc - 1) / kKc);
     if (prec == BEM_C128)
       hipLaunchKernelGGL(quad_assemble_kernel<double2>, grid, dim3(kQT), 0, ctx->stream, s->n,
-                         s->x, s->nrm, s->bc, npts, qp, inc, R, k, n_rhs, r0, nr,
+                         s->x, s->nrm, s->bc, npts, qp, inc, k, n_k, n_rhs, r0, nr,
                          (const double2*)y, (double2*)A, ld, a_stride, (double2*)b,
                          (double2*)diag64);
     else
       hipLaunchKernelGGL(quad_assemble_kernel<float2>, grid, dim3(kQT), 0, ctx->stream, s->n,
-                         s->x, s->nrm, s->bc, npts, qp, inc, R, k, n_rhs, r0, nr,
+                         s->x, s->nrm, s->bc, npts, qp, inc, k, n_k, n_rhs, r0, nr,
                          (const double2*)y, (float2*)A, ld, a_stride, (double2*)b,
                          (double2*)diag64);
     BEM_CHECK_LAUNCH(ctx);
@@ -410,8 +492,9 @@ bem_status launch_quad_residual(bem_ctx* ctx, int n, const void* A64, int64_t ld
 
 bem_status launch_quad_field(bem_ctx* ctx, const bem_quad_surface* s, const double* qp,
                              int n_k, const double* k, int n_rhs, const void* phi,
-                             const void* psi, void* phq, void* psq, int m, const double* xp,
-                             const int32_t* i0, const uint8_t* inside, void* U) {
+                             const void* psi, void* phq, void* psq, void* sums, int32_t* list_ws,
+                             int m, const double* xp, const int32_t* i0, const uint8_t* inside,
+                             void* U) {
   const QuadRule R = make_rule();
   const int npts = s->n_elem * kQ;
   const int64_t tot = (int64_t)npts * n_k * n_rhs;
@@ -421,14 +504,16 @@ bem_status launch_quad_field(bem_ctx* ctx, const bem_quad_surface* s, const doub
   hipLaunchKernelGGL(quad_interp_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0,
                      ctx->stream, s->n, s->n_elem, n_k * n_rhs, s->elem, R,
                      (const double2*)psi, (double2*)psq);
+  // Eq. BRIEFdmn by the element quadrature, x0 the closest node a: the field sums
+  // of field64_kernel over the quadrature points instead of the nodes
   const int pi = prof_begin(ctx, "field_quad");
-  hipLaunchKernelGGL(quad_field_kernel, dim3((m + kQT - 1) / kQT, n_k, n_rhs), dim3(kQT), 0,
-                     ctx->stream, s->n, s->x, s->nrm, npts, qp, k, n_k, n_rhs,
-                     (const double2*)phi, (const double2*)psi, (const double2*)phq,
-                     (const double2*)psq, m, xp, i0, inside, (double2*)U);
+  const bem_surface nodal{s->n, s->x, s->nrm, nullptr, s->bc};
+  const FieldSources src{qp, qp + 3, qp + 6, 8, 8, npts, false, (const double2*)phq,
+                         (const double2*)psq};
+  const bem_status st = launch_field64(ctx, src, &nodal, n_k, k, n_rhs, phi, psi, m, xp, i0, inside,
+                                       sums, list_ws, U);
   prof_end(ctx, "field_quad", pi, (double)m * n_k * n_rhs * npts, 0.0);
-  BEM_CHECK_LAUNCH(ctx);
-  return BEM_OK;
+  return st;
 }
 
 }  // namespace bem
