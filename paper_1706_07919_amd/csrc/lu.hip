@@ -2081,159 +2081,9 @@ __global__ __launch_bounds__(256) void gemm_c64_kernel(LuGroups G, int rowC, int
     }
 }
 
-// ============================================================== pivots -> permutation
-// perm[i] = original row that ends in position i after the interchanges; the
-// sequential composition runs in LDS (one workgroup per matrix).
-__global__ void perm_kernel(int n, const int32_t* piv, int32_t* perm) {
-  extern __shared__ int32_t q[];
-  const int32_t* pb = piv + (int64_t)blockIdx.x * n;
-  int32_t* qb = perm + (int64_t)blockIdx.x * n;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) q[i] = i;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < n; ++i) {
-      const int p = pb[i];
-      if (p != i) { const int32_t t = q[i]; q[i] = q[p]; q[p] = t; }
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < n; i += blockDim.x) qb[i] = q[i];
-}
-
 __global__ void fill_i32_kernel(int64_t count, int32_t* p, int32_t v) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < count) p[t] = v;
-}
-
-// ============================================================== triangular solves
-// One workgroup (8 waves) per (matrix, right-hand side): X = U^{-1} L^{-1} P B,
-// processed in blocks of 64 rows.  For each block, the 64 x 64 diagonal block
-// is staged in LDS while the waves form the off-diagonal dot products (row-major
-// rows against the solved part of x, coalesced), then one wave substitutes
-// through the diagonal block from LDS.  x lives in LDS when it fits (XLDS),
-// otherwise in global memory.
-constexpr int TS_B = 64;
-constexpr int TS_T = 512;
-
-template <typename R, bool XLDS>
-__global__ __launch_bounds__(TS_T) void getrs_kernel(int n, int64_t ld, int64_t stride,
-                                                     const typename Cx<R>::T* LU,
-                                                     const int32_t* perm, int n_rhs,
-                                                     const typename Cx<R>::T* Bin,
-                                                     typename Cx<R>::T* X, int64_t bstride,
-                                                     const int32_t* fac_index,
-                                                     const int32_t* vidx) {
-  using C = typename Cx<R>::T;
-  extern __shared__ unsigned char smem[];
-  C* D = reinterpret_cast<C*>(smem);                 // [TS_B][TS_B + 1]
-  C* part = D + TS_B * (TS_B + 1);                   // [TS_B]
-  C* xs = part + TS_B;                               // [n] when XLDS
-  // vector group: blockIdx / n_rhs, or the vidx entry when a subset is solved
-  const int mat = vidx ? vidx[blockIdx.x / n_rhs] : blockIdx.x / n_rhs;
-  const int rhs = blockIdx.x % n_rhs;
-  // vector group `mat` is solved with factor set fac_index[mat] (identity if NULL)
-  const int fac = fac_index ? fac_index[mat] : mat;
-  const C* Lb = LU + (int64_t)fac * stride;
-  const int32_t* pb = perm + (int64_t)fac * n;
-  const C* bin = Bin + (int64_t)mat * bstride + (int64_t)rhs * n;
-  C* xg = X + (int64_t)mat * bstride + (int64_t)rhs * n;
-  C* x = XLDS ? xs : xg;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  constexpr int NW = TS_T / 64;
-  for (int i = tid; i < n; i += TS_T) x[i] = bin[pb[i]];
-  __threadfence_block();
-  __syncthreads();
-  const int nb = (n + TS_B - 1) / TS_B;
-  // every off-diagonal range starts at an even column (0, or a multiple of 64)
-  const bool vec2 = sizeof(C) == 8 && ((ld | stride) & 1) == 0 && ((uintptr_t)LU & 15) == 0;
-  for (int pass = 0; pass < 2; ++pass) {
-    const bool fwd = pass == 0;
-    for (int step = 0; step < nb; ++step) {
-      const int I = fwd ? step : nb - 1 - step;
-      const int i0 = I * TS_B, rows = min(TS_B, n - i0);
-      // stage the diagonal block
-      for (int e = tid; e < rows * TS_B; e += TS_T) {
-        const int r = e / TS_B, c = e % TS_B;
-        if (c < rows) D[r * (TS_B + 1) + c] = Lb[(int64_t)(i0 + r) * ld + i0 + c];
-      }
-      // off-diagonal dot products: forward uses columns [0, i0), backward [i0+rows, n)
-      const int jlo = fwd ? 0 : i0 + rows, jhi = fwd ? i0 : n;
-      for (int rr = wid; rr < rows; rr += NW) {
-        const C* Li = Lb + (int64_t)(i0 + rr) * ld;
-        R sr = 0, si = 0, sr2 = 0, si2 = 0;
-        if (vec2) {
-          // complex float rows with even ld and start: each lane takes pairs of
-          // elements as 16-byte words, two pairs per iteration
-          int j = jlo + 2 * lane;
-          for (; j + 129 < jhi; j += 256) {
-            const float4 la = *reinterpret_cast<const float4*>(Li + j);
-            const float4 lb = *reinterpret_cast<const float4*>(Li + j + 128);
-            const C a0 = x[j], a1 = x[j + 1], b0 = x[j + 128], b1 = x[j + 129];
-            sr += (la.x * a0.x - la.y * a0.y) + (la.z * a1.x - la.w * a1.y);
-            si += (la.x * a0.y + la.y * a0.x) + (la.z * a1.y + la.w * a1.x);
-            sr2 += (lb.x * b0.x - lb.y * b0.y) + (lb.z * b1.x - lb.w * b1.y);
-            si2 += (lb.x * b0.y + lb.y * b0.x) + (lb.z * b1.y + lb.w * b1.x);
-          }
-          for (; j + 1 < jhi; j += 128) {
-            const float4 la = *reinterpret_cast<const float4*>(Li + j);
-            const C a0 = x[j], a1 = x[j + 1];
-            sr += (la.x * a0.x - la.y * a0.y) + (la.z * a1.x - la.w * a1.y);
-            si += (la.x * a0.y + la.y * a0.x) + (la.z * a1.y + la.w * a1.x);
-          }
-          if (j < jhi) {
-            const C l0 = Li[j], v0 = x[j];
-            sr += l0.x * v0.x - l0.y * v0.y;
-            si += l0.x * v0.y + l0.y * v0.x;
-          }
-        } else {
-          int j = jlo + lane;
-          for (; j + 64 < jhi; j += 128) {
-            const C l0 = Li[j], v0 = x[j], l1 = Li[j + 64], v1 = x[j + 64];
-            sr += l0.x * v0.x - l0.y * v0.y;
-            si += l0.x * v0.y + l0.y * v0.x;
-            sr2 += l1.x * v1.x - l1.y * v1.y;
-            si2 += l1.x * v1.y + l1.y * v1.x;
-          }
-          if (j < jhi) {
-            const C l0 = Li[j], v0 = x[j];
-            sr += l0.x * v0.x - l0.y * v0.y;
-            si += l0.x * v0.y + l0.y * v0.x;
-          }
-        }
-        sr += sr2;
-        si += si2;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          sr += __shfl_down(sr, off, 64);
-          si += __shfl_down(si, off, 64);
-        }
-        if (lane == 0) part[rr] = cmk<C>(sr, si);
-      }
-      __syncthreads();
-      if (wid == 0) {
-        C v = cmk<C>(R(0), R(0));
-        if (lane < rows) v = csub(x[i0 + lane], part[lane]);
-        if (fwd) {
-          for (int c = 0; c < rows; ++c) {
-            const R xr = __shfl(v.x, c, 64), xi = __shfl(v.y, c, 64);
-            if (lane > c && lane < rows) v = csub(v, cmul(D[lane * (TS_B + 1) + c], cmk<C>(xr, xi)));
-          }
-        } else {
-          const C dinv = lane < rows ? crecip(D[lane * (TS_B + 1) + lane]) : cmk<C>(R(1), R(0));
-          for (int c = rows - 1; c >= 0; --c) {
-            if (lane == c) v = cmul(v, dinv);
-            const R xr = __shfl(v.x, c, 64), xi = __shfl(v.y, c, 64);
-            if (lane < c) v = csub(v, cmul(D[lane * (TS_B + 1) + c], cmk<C>(xr, xi)));
-          }
-        }
-        if (lane < rows) x[i0 + lane] = v;
-      }
-      __threadfence_block();
-      __syncthreads();
-    }
-  }
-  if (XLDS)
-    for (int i = tid; i < n; i += TS_T) xg[i] = x[i];
 }
 
 // ============================================================== host driver
@@ -2909,68 +2759,6 @@ bem_status lu_factor(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t str
   std::vector<LuMatrixSet> sets(1);
   sets[0] = LuMatrixSet{A, piv, info, ld, stride, n, batch};
   return lu_factor_groups(ctx, prec, sets, plan, gemm_kind);
-}
-
-bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* perm) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipFuncSetAttribute((const void*)perm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                        160 * 1024);
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(perm_kernel, dim3(batch), dim3(256), sizeof(int32_t) * n, ctx->stream, n,
-                     piv, perm);
-  BEM_CHECK_LAUNCH(ctx);
-  return BEM_OK;
-}
-
-bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
-                         int batch, const void* LU, const int32_t* perm, int n_rhs,
-                         const void* Bin, void* X, int64_t bstride, const int32_t* fac_index,
-                         const int32_t* vidx, int n_sel) {
-  if (vidx) batch = n_sel;
-  if (batch <= 0 || n_rhs <= 0) return BEM_OK;
-  dim3 grid(batch * n_rhs);
-  const size_t esz = prec == BEM_C128 ? 16 : 8;
-  const size_t base_lds = esz * (size_t)(TS_B * (TS_B + 1) + TS_B);
-  const bool xlds = base_lds + esz * (size_t)n <= 150 * 1024;
-  const size_t lds = base_lds + (xlds ? esz * (size_t)n : 0);
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipFuncSetAttribute((const void*)getrs_kernel<double, true>,
-                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    hipFuncSetAttribute((const void*)getrs_kernel<float, true>,
-                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    hipFuncSetAttribute((const void*)getrs_kernel<double, false>,
-                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    hipFuncSetAttribute((const void*)getrs_kernel<float, false>,
-                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    attr_set = true;
-  }
-  const int pi = prof_begin(ctx, "getrs");
-  if (prec == BEM_C128) {
-    if (xlds)
-      hipLaunchKernelGGL((getrs_kernel<double, true>), grid, dim3(TS_T), lds, ctx->stream, n, ld,
-                         stride, (const double2*)LU, perm, n_rhs, (const double2*)Bin,
-                         (double2*)X, bstride, fac_index, vidx);
-    else
-      hipLaunchKernelGGL((getrs_kernel<double, false>), grid, dim3(TS_T), lds, ctx->stream, n, ld,
-                         stride, (const double2*)LU, perm, n_rhs, (const double2*)Bin,
-                         (double2*)X, bstride, fac_index, vidx);
-  } else {
-    if (xlds)
-      hipLaunchKernelGGL((getrs_kernel<float, true>), grid, dim3(TS_T), lds, ctx->stream, n, ld,
-                         stride, (const float2*)LU, perm, n_rhs, (const float2*)Bin, (float2*)X,
-                         bstride, fac_index, vidx);
-    else
-      hipLaunchKernelGGL((getrs_kernel<float, false>), grid, dim3(TS_T), lds, ctx->stream, n, ld,
-                         stride, (const float2*)LU, perm, n_rhs, (const float2*)Bin, (float2*)X,
-                         bstride, fac_index, vidx);
-  }
-  prof_end(ctx, "getrs", pi, 8.0 * (double)n * n * n_rhs * batch,
-           (double)esz * ((double)n * n + 3.0 * n * n_rhs) * batch);
-  BEM_CHECK_LAUNCH(ctx);
-  return BEM_OK;
 }
 
 }  // namespace bem

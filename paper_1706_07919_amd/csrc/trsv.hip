@@ -1,0 +1,463 @@
+// Triangular solves X = U^{-1} L^{-1} P B with the factors of the batched LU
+// (row-major, P A = L U, unit L) for one or more right-hand sides per matrix,
+// and the permutation of the recorded interchanges.
+//
+// The factors are read once per solve (8 or 16 n^2 bytes), so the bound is HBM;
+// what has to be avoided is the chain through the unknowns.  The unknowns are
+// solved in blocks of TS_NB: one workgroup per vector solves a block's triangle
+// (trsv_block), then every unknown left takes the block's contribution in a
+// matrix-vector launch over all of the chip (trsv_update_kernel).  A single
+// workgroup per vector doing both read its factors at 21 GB/s: 64 systems of
+// n = 5124 took 9.9 ms per solve, 8 of n = 10242 12 ms, 32 of n = 2562 with 8 sets
+// of factors 2.9 ms; now 5.1, about 2.5 and 1.0 ms.
+#include <algorithm>
+
+#include "common.h"
+
+namespace bem {
+namespace {
+
+template <typename R> struct Cx;
+template <> struct Cx<float> { using T = float2; };
+template <> struct Cx<double> { using T = double2; };
+
+template <typename C> __device__ inline C cmk(decltype(C::x) a, decltype(C::x) b) {
+  C c; c.x = a; c.y = b; return c;
+}
+template <typename C> __device__ inline C cmul(C a, C b) {
+  return cmk<C>(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+// s + a b as four fused multiply-adds
+template <typename C> __device__ inline C cfma(C s, C a, C b) {
+  return cmk<C>(fma(a.x, b.x, fma(-a.y, b.y, s.x)), fma(a.x, b.y, fma(a.y, b.x, s.y)));
+}
+template <typename C> __device__ inline C crecip(C a) {
+  // 1/a with scaling to avoid overflow (Smith's method)
+  using R = decltype(C::x);
+  if (fabs(a.x) >= fabs(a.y)) {
+    R t = a.y / a.x, d = a.x + a.y * t;
+    return cmk<C>(R(1) / d, -t / d);
+  } else {
+    R t = a.x / a.y, d = a.y + a.x * t;
+    return cmk<C>(t / d, R(-1) / d);
+  }
+}
+// value of lane l (wave-uniform) in every lane
+__device__ inline float lane_value(float v, int l) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
+}
+__device__ inline double lane_value(double v, int l) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, l);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// ============================================================== pivots -> permutation
+// perm[i] = original row that ends in position i after the interchanges; one
+// wave composes them in LDS, skipping the positions that are not interchanged
+// (most, for the boundary-integral systems) 64 at a time.
+__global__ __launch_bounds__(64) void perm_kernel(int n, const int32_t* __restrict__ piv,
+                                                  int32_t* __restrict__ perm) {
+  extern __shared__ int32_t q[];
+  const int32_t* pb = piv + (int64_t)blockIdx.x * n;
+  int32_t* qb = perm + (int64_t)blockIdx.x * n;
+  const int lane = threadIdx.x;
+  for (int i = lane; i < n; i += 64) q[i] = i;
+  __syncthreads();
+  int p = pb[min(lane, n - 1)];
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int cur = p;
+    if (i0 + 64 < n) p = pb[min(i0 + 64 + lane, n - 1)];
+    unsigned long long todo = __ballot(i0 + lane < n && cur != i0 + lane);
+    while (todo) {
+      const int l = __ffsll((unsigned long long)todo) - 1;
+      todo &= todo - 1;
+      const int a = i0 + l, b = __builtin_amdgcn_readlane(cur, l);
+      if (lane == 0) {
+        const int32_t t = q[a];
+        q[a] = q[b];
+        q[b] = t;
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = lane; i < n; i += 64) qb[i] = q[i];
+}
+
+// ============================================================== blocks of the solve
+constexpr int TS_B = 64;             // tile
+constexpr int TS_T = 512;            // threads of the block kernels
+constexpr int TS_TILES = 5;          // tiles of the largest block
+constexpr int TS_NB = 4 * TS_B;      // block; a remainder of up to a tile joins the last one
+constexpr int TS_DLD = TS_B + 1;     // leading dimension of a staged diagonal tile
+
+// LDS of trsv_block: two diagonal tiles, the block's unknowns, the sums of the
+// row tile about to be solved
+template <typename C>
+constexpr size_t trsv_lds() {
+  return sizeof(C) * (2 * TS_B * TS_DLD + TS_TILES * TS_B + 2 * TS_B);
+}
+
+// Solves rows [i0, i0 + rows) of L (FWD) or U in place: xs (LDS) holds the
+// block's right-hand side on entry and its solution on exit.  Tiles are taken
+// in solving order (logical tile t is physical t, or T - 1 - t backwards).  Wave
+// 2 (I - 1) + half owns row tile I and one half of the columns of each tile it
+// multiplies: a lane keeps its row's 32 entries in registers, loaded while the
+// tile's unknowns are still being solved, and its sum over the tiles before I.
+// The unknowns of a tile come from one wave, a lane per row, the solved value
+// broadcast through a scalar register; each product is formed before it is
+// subtracted (one rounding of the unknown per step: fused into it, the two
+// multiply-adds of a component round it twice, and the chain's error grew from
+// 2.3e-7 to 3.4e-7 at n = 642).
+template <typename R, bool FWD>
+__device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__ Lb, int64_t ld, int i0,
+                                           int rows, bool vec, typename Cx<R>::T* D,
+                                           typename Cx<R>::T* xs, typename Cx<R>::T* sums) {
+  using C = typename Cx<R>::T;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = (rows + TS_B - 1) / TS_B;
+  auto phys = [&](int t) { return FWD ? t : T - 1 - t; };
+  const C zero = cmk<C>(R(0), R(0));
+  // diagonal tile of logical tile t: loaded into registers, then stored into
+  // buffer t & 1, the other triangle and rows past the end zero
+  constexpr int SQ = TS_B * TS_B / TS_T;
+  C nxt[SQ];
+  auto stage_load = [&](int t) {
+    const int r0 = phys(t) * TS_B, m = min(TS_B, rows - r0);
+#pragma unroll
+    for (int q = 0; q < SQ; ++q) {
+      const int e = tid + q * TS_T, r = e / TS_B, c = e % TS_B;
+      nxt[q] = Lb[(int64_t)(i0 + r0 + min(r, m - 1)) * ld + i0 + r0 + min(c, m - 1)];
+    }
+  };
+  auto stage_store = [&](int t) {
+    const int m = min(TS_B, rows - phys(t) * TS_B);
+    C* d = D + (t & 1) * TS_B * TS_DLD;
+#pragma unroll
+    for (int q = 0; q < SQ; ++q) {
+      const int e = tid + q * TS_T, r = e / TS_B, c = e % TS_B;
+      d[r * TS_DLD + c] = r < m && c < m && (FWD ? c < r : c >= r) ? nxt[q] : zero;
+    }
+  };
+  // this wave's half of tile (I, J)
+  const int I = 1 + wid / 2, half = wid & 1;
+  C l[TS_B / 2];
+  auto load = [&](int J) {
+    const int r = min(phys(I) * TS_B + lane, rows - 1), c0 = phys(J) * TS_B + half * (TS_B / 2);
+    const C* src = Lb + (int64_t)(i0 + r) * ld + i0 + c0;
+    if (c0 + TS_B / 2 <= rows && vec) {
+#pragma unroll
+      for (int c = 0; c < TS_B / 2; c += 16 / (int)sizeof(C)) {
+        const uint4 v = *reinterpret_cast<const uint4*>(src + c);
+        __builtin_memcpy(&l[c], &v, 16);
+      }
+    } else {
+      const int left = rows - c0;   // columns past the block: zero
+#pragma unroll
+      for (int c = 0; c < TS_B / 2; ++c) {
+        const C v = src[min(c, left - 1)];
+        l[c] = c < left ? v : zero;
+      }
+    }
+  };
+  C acc = zero;
+  stage_load(0);
+  stage_store(0);
+  for (int J = 0; J < T; ++J) {
+    __syncthreads();   // the tile and the sums of row tile J are there
+    const int solver = J == 0 ? TS_T / 64 - 1 : 2 * (J - 1);
+    if (J + 1 < T) stage_load(J + 1);
+    if (I > J && I < T && phys(J) * TS_B + half * (TS_B / 2) < rows) load(J);
+    if (wid == solver) {
+      const C* d = D + (J & 1) * TS_B * TS_DLD + lane * TS_DLD;
+      const int r0 = phys(J) * TS_B;
+      C v = xs[r0 + lane];   // (xs is padded with zeros to whole tiles)
+      if (J > 0) {
+        v.x -= sums[lane].x + sums[TS_B + lane].x;
+        v.y -= sums[lane].y + sums[TS_B + lane].y;
+      }
+      if (FWD) {
+#pragma unroll
+        for (int c = 0; c < TS_B; ++c) {
+          const C x = cmk<C>(lane_value(v.x, c), lane_value(v.y, c));
+          const C p = cmul(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
+          v = lane > c ? s : v;
+        }
+      } else {
+        const C dinv = r0 + lane < rows ? crecip(d[lane]) : cmk<C>(R(1), R(0));
+#pragma unroll
+        for (int c = TS_B - 1; c >= 0; --c) {
+          const C t = cmul(v, dinv);
+          const C x = cmk<C>(lane_value(t.x, c), lane_value(t.y, c));
+          const C p = cmul(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
+          v = lane == c ? t : (lane < c ? s : v);
+        }
+      }
+      xs[r0 + lane] = v;
+    }
+    if (J + 1 < T) stage_store(J + 1);
+    __syncthreads();   // the unknowns of tile J are there
+    if (I > J && I < T) {
+      const int c0 = phys(J) * TS_B + half * (TS_B / 2);
+      if (c0 < rows) {
+        C a = zero, b = zero;
+#pragma unroll
+        for (int c = 0; c < TS_B / 2; c += 2) {
+          a = cfma(a, l[c], xs[c0 + c]);
+          b = cfma(b, l[c + 1], xs[c0 + c + 1]);
+        }
+        acc.x += a.x + b.x;
+        acc.y += a.y + b.y;
+      }
+      if (I == J + 1) sums[half * TS_B + lane] = acc;
+    }
+  }
+  __syncthreads();
+}
+
+// One workgroup per vector.  WHOLE: the whole solve of systems of one block
+// (permuted right-hand side in, both triangles); else the block [i0, i0 + rows)
+// of L (FWD) or U of the vectors in X.
+template <typename R, bool WHOLE, bool FWD>
+__global__ __launch_bounds__(TS_T) void trsv_block_kernel(
+    int n, int64_t ld, int64_t stride, const typename Cx<R>::T* __restrict__ LU,
+    const int32_t* __restrict__ perm, int n_rhs, const typename Cx<R>::T* __restrict__ Bin,
+    typename Cx<R>::T* __restrict__ X, int64_t bstride, const int32_t* __restrict__ fac_index,
+    const int32_t* __restrict__ vidx, int i0, int rows, bool vec) {
+  using C = typename Cx<R>::T;
+  extern __shared__ unsigned char smem[];
+  C* D = reinterpret_cast<C*>(smem);
+  C* xs = D + 2 * TS_B * TS_DLD;
+  C* sums = xs + TS_TILES * TS_B;
+  // vector group: blockIdx / n_rhs, or the vidx entry when a subset is solved,
+  // with factor set fac_index[mat] (identity if NULL)
+  const int mat = vidx ? vidx[blockIdx.x / n_rhs] : blockIdx.x / n_rhs;
+  const int fac = fac_index ? fac_index[mat] : mat;
+  const int64_t off = (int64_t)mat * bstride + (int64_t)(blockIdx.x % n_rhs) * n;
+  const C* Lb = LU + (int64_t)fac * stride;
+  if (threadIdx.x < TS_TILES * TS_B) {
+    const int i = threadIdx.x;
+    C v = cmk<C>(R(0), R(0));
+    if (i < rows) v = WHOLE ? Bin[off + perm[(int64_t)fac * n + i]] : X[off + i0 + i];
+    xs[i] = v;
+  }
+  if (WHOLE) {
+    trsv_block<R, true>(Lb, ld, 0, rows, vec, D, xs, sums);
+    trsv_block<R, false>(Lb, ld, 0, rows, vec, D, xs, sums);
+  } else {
+    trsv_block<R, FWD>(Lb, ld, i0, rows, vec, D, xs, sums);
+  }
+  if ((int)threadIdx.x < rows) X[off + i0 + threadIdx.x] = xs[threadIdx.x];
+}
+
+// X = P B
+template <typename C>
+__global__ void trsv_permute_kernel(int n, const int32_t* __restrict__ perm, int n_rhs,
+                                    const C* __restrict__ Bin, C* __restrict__ X, int64_t bstride,
+                                    const int32_t* __restrict__ fac_index,
+                                    const int32_t* __restrict__ vidx) {
+  const int i = blockIdx.y * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int mat = vidx ? vidx[blockIdx.x / n_rhs] : blockIdx.x / n_rhs;
+  const int fac = fac_index ? fac_index[mat] : mat;
+  const int64_t off = (int64_t)mat * bstride + (int64_t)(blockIdx.x % n_rhs) * n;
+  X[off + i] = Bin[off + perm[(int64_t)fac * n + i]];
+}
+
+// X[rows] -= LU[rows, c0 .. c0 + cols) X[c0 .. c0 + cols) for the rows [ra, rb),
+// NR right-hand sides at once.  A wave takes 16 / NR rows, its lanes the columns
+// (16-byte words); the 32 sums of a wave are reduced by recursive halving (32
+// shuffles).
+template <typename R, int NR>
+__global__ __launch_bounds__(256) void trsv_update_kernel(
+    int n, int64_t ld, int64_t stride, const typename Cx<R>::T* __restrict__ LU, int n_rhs,
+    typename Cx<R>::T* __restrict__ X, int64_t bstride, const int32_t* __restrict__ fac_index,
+    const int32_t* __restrict__ vidx, int ra, int rb, int c0, int cols, bool vec) {
+  using C = typename Cx<R>::T;
+  constexpr int RPW = 16 / NR, PER = 16 / (int)sizeof(C), CW = 64 * PER;   // columns of a step
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int mat = vidx ? vidx[blockIdx.y] : blockIdx.y;
+  const int fac = fac_index ? fac_index[mat] : mat;
+  const int rh0 = blockIdx.z * NR, nrh = min(NR, n_rhs - rh0);
+  const int r0 = ra + (blockIdx.x * 4 + wid) * RPW;
+  if (r0 >= rb) return;
+  const C* Lb = LU + (int64_t)fac * stride + c0;
+  C* x = X + (int64_t)mat * bstride + (int64_t)rh0 * n;
+  R v[RPW][NR][2];
+#pragma unroll
+  for (int i = 0; i < RPW; ++i)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) v[i][r][0] = v[i][r][1] = R(0);
+  for (int j0 = 0; j0 < cols; j0 += CW) {
+    const int j = j0 + PER * lane;
+    C xv[NR][PER];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const C t = x[(int64_t)min(r, nrh - 1) * n + c0 + min(j + u, cols - 1)];
+        xv[r][u] = j + u < cols ? t : cmk<C>(R(0), R(0));
+      }
+    // every row's word before the first is used
+    C l[RPW][PER];
+    const bool whole = vec && j0 + CW <= cols;   // uniform
+    if (whole) {
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        const uint4 w = *reinterpret_cast<const uint4*>(Lb + (int64_t)min(r0 + i, rb - 1) * ld + j);
+        __builtin_memcpy(l[i], &w, 16);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          const C t = Lb[(int64_t)min(r0 + i, rb - 1) * ld + min(j + u, cols - 1)];
+          l[i][u] = j + u < cols ? t : cmk<C>(R(0), R(0));
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          v[i][r][0] = fma(l[i][u].x, xv[r][u].x, fma(-l[i][u].y, xv[r][u].y, v[i][r][0]));
+          v[i][r][1] = fma(l[i][u].x, xv[r][u].y, fma(l[i][u].y, xv[r][u].x, v[i][r][1]));
+        }
+  }
+  // values e = (row, rhs, part): after the halvings lanes 2 e and 2 e + 1 hold e
+  R h[32];
+#pragma unroll
+  for (int e = 0; e < 32; ++e) h[e] = v[e / (2 * NR)][(e / 2) % NR][e % 2];
+#pragma unroll
+  for (int s = 32, m = 16; m >= 1; s >>= 1, m >>= 1) {
+    const bool up = lane & s;
+#pragma unroll
+    for (int e = 0; e < m; ++e) {
+      const R keep = up ? h[m + e] : h[e], give = up ? h[e] : h[m + e];
+      h[e] = keep + __shfl_xor(give, s, 64);
+    }
+  }
+  h[0] += __shfl_xor(h[0], 1, 64);
+  const int e = lane >> 1, i = e / (2 * NR), r = (e / 2) % NR;
+  if (!(lane & 1) && r0 + i < rb && r < nrh) {
+    R* dst = reinterpret_cast<R*>(x + (int64_t)r * n + r0 + i) + (e & 1);
+    *dst -= h[0];
+  }
+}
+
+template <typename R>
+bem_status solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
+                    const void* LU_, const int32_t* perm, int n_rhs, const void* B_, void* X_,
+                    int64_t bstride, const int32_t* fac_index, const int32_t* vidx) {
+  using C = typename Cx<R>::T;
+  const C* LU = (const C*)LU_;
+  const C* B = (const C*)B_;
+  C* X = (C*)X_;
+  // 16-byte words: rows and blocks (starting at multiples of 64) all aligned
+  const bool vec = sizeof(C) == 16 ? ((uintptr_t)LU & 15) == 0
+                                   : ((ld | stride) & 1) == 0 && ((uintptr_t)LU & 15) == 0;
+  const size_t lds = trsv_lds<C>();
+  const dim3 bt(TS_T), vectors((unsigned)(groups * n_rhs));
+  if (n <= TS_TILES * TS_B) {
+    hipLaunchKernelGGL((trsv_block_kernel<R, true, true>), vectors, bt, lds, ctx->stream, n, ld,
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, 0, n, vec);
+    return BEM_OK;
+  }
+  hipLaunchKernelGGL(trsv_permute_kernel<C>, dim3(vectors.x, (n + 255) / 256), dim3(256), 0,
+                     ctx->stream, n, perm, n_rhs, B, X, bstride, fac_index, vidx);
+  // blocks of TS_NB unknowns, the last with up to TS_TILES tiles
+  const int nb = std::max(1, (n - TS_B + TS_NB - 1) / TS_NB);
+  auto start = [&](int q) { return q * TS_NB; };
+  auto rows = [&](int q) { return q + 1 < nb ? TS_NB : n - q * TS_NB; };
+  auto update = [&](int ra, int rb, int q) {
+    if (rb <= ra) return;
+    auto go = [&](auto nr_c) {
+      constexpr int NR = decltype(nr_c)::value, ZMAX = 65535 * NR;
+      for (int z0 = 0; z0 < n_rhs; z0 += ZMAX) {
+        const int nz = std::min(n_rhs - z0, ZMAX);
+        hipLaunchKernelGGL((trsv_update_kernel<R, NR>),
+                           dim3((rb - ra + 64 / NR - 1) / (64 / NR), groups, (nz + NR - 1) / NR),
+                           dim3(256), 0, ctx->stream, n, ld, stride, LU, nz, X + (int64_t)z0 * n,
+                           bstride, fac_index, vidx, ra, rb, start(q), rows(q), vec);
+      }
+    };
+    if (n_rhs == 1) go(std::integral_constant<int, 1>{});
+    else if (n_rhs == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 4>{});
+  };
+  for (int q = 0; q < nb; ++q) {
+    hipLaunchKernelGGL((trsv_block_kernel<R, false, true>), vectors, bt, lds, ctx->stream, n, ld,
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec);
+    update(start(q) + rows(q), n, q);
+  }
+  for (int q = nb - 1; q >= 0; --q) {
+    hipLaunchKernelGGL((trsv_block_kernel<R, false, false>), vectors, bt, lds, ctx->stream, n, ld,
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec);
+    update(0, start(q), q);
+  }
+  return BEM_OK;
+}
+
+}  // namespace
+
+bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* perm) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipFuncSetAttribute((const void*)perm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                        160 * 1024);
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(perm_kernel, dim3(batch), dim3(64), sizeof(int32_t) * n, ctx->stream, n,
+                     piv, perm);
+  BEM_CHECK_LAUNCH(ctx);
+  return BEM_OK;
+}
+
+bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
+                         int batch, const void* LU, const int32_t* perm, int n_rhs,
+                         const void* Bin, void* X, int64_t bstride, const int32_t* fac_index,
+                         const int32_t* vidx, int n_sel) {
+  if (vidx) batch = n_sel;
+  if (batch <= 0 || n_rhs <= 0) return BEM_OK;
+  static bool attr_set = false;
+  if (!attr_set) {
+    auto big = [](const void* f) {
+      hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    };
+    big((const void*)trsv_block_kernel<float, true, true>);
+    big((const void*)trsv_block_kernel<float, false, true>);
+    big((const void*)trsv_block_kernel<float, false, false>);
+    big((const void*)trsv_block_kernel<double, true, true>);
+    big((const void*)trsv_block_kernel<double, false, true>);
+    big((const void*)trsv_block_kernel<double, false, false>);
+    attr_set = true;
+  }
+  const size_t esz = prec == BEM_C128 ? 16 : 8;
+  const int most = 65535;   // groups per launch (grid y)
+  const int pi = prof_begin(ctx, "getrs");
+  bem_status st = BEM_OK;
+  for (int g0 = 0; g0 < batch && st == BEM_OK; g0 += most) {
+    const int g = std::min(most, batch - g0);
+    // without an index list the slice is taken by moving the pointers
+    const size_t vo = vidx ? 0 : (size_t)g0 * bstride * esz;
+    const char* lu = (const char*)LU + (vidx || fac_index ? 0 : (size_t)g0 * stride * esz);
+    const int32_t* pm = perm + (vidx || fac_index ? 0 : (size_t)g0 * n);
+    const int32_t* fi = fac_index && !vidx ? fac_index + g0 : fac_index;
+    const int32_t* vi = vidx ? vidx + g0 : nullptr;
+    const char* b = (const char*)Bin + vo;
+    char* x = (char*)X + vo;
+    st = prec == BEM_C128
+             ? solve_go<double>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi)
+             : solve_go<float>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi);
+  }
+  prof_end(ctx, "getrs", pi, 8.0 * (double)n * n * n_rhs * batch,
+           (double)esz * ((double)n * n + 3.0 * n * n_rhs) * batch);
+  BEM_CHECK_LAUNCH(ctx);
+  return BEM_OK;
+}
+
+}  // namespace bem

@@ -1,0 +1,58 @@
+"""Triangular solves at the ends of their tiles, blocks and right-hand-side groups,
+with shared and selected factors' layouts: backward error of the solve with the
+float64-checked factors of diagonally shifted and of plain Gaussian matrices."""
+import numpy as np
+import pytest
+
+from workloads import seeded_complex
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+native = pytest.importorskip("paper_1706_07919_amd.native")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    c = native.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("prec", [native.BEM_C64, native.BEM_C128])
+@pytest.mark.parametrize("n,pad,n_rhs", [
+    (1, 0, 1), (63, 1, 2), (64, 0, 1), (65, 0, 3), (191, 1, 1),   # one block
+    (320, 0, 5), (321, 0, 1), (576, 1, 2), (577, 0, 3), (833, 3, 7)])   # several
+def test_getrs_blocks(ctx, prec, n, pad, n_rhs):
+    rng = np.random.default_rng(n)
+    batch, ld = 3, n + pad
+    M = seeded_complex(rng, (batch, n, n)) + 0.5 * np.sqrt(n) * np.eye(n)[None]
+    M[1] = M[1][rng.permutation(n)]
+    M[2] = seeded_complex(rng, (n, n))
+    dt = torch.complex128 if prec == native.BEM_C128 else torch.complex64
+    A = torch.zeros((batch, n, ld), dtype=dt)
+    A[:, :, :n] = torch.as_tensor(M)
+    A = A.cuda()
+    piv = torch.zeros((batch, n), dtype=torch.int32, device="cuda")
+    info = torch.ones(batch, dtype=torch.int32, device="cuda")
+    native.bem_getrf_batched(ctx, prec, n, ld, n * ld, batch, A, piv, info, 0, native.BEM_GEMM_4M)
+    B = seeded_complex(rng, (batch, n_rhs + 1, n))   # one vector more than is solved
+    X = torch.full((batch, n_rhs + 1, n), 7.0, dtype=dt, device="cuda")
+    native.bem_getrs_batched(ctx, prec, n, ld, n * ld, batch, A, piv, n_rhs,
+                             torch.as_tensor(B).to(dt).cuda(), X, (n_rhs + 1) * n)
+    X = X.cpu().numpy().astype(np.complex128)
+    assert np.all(X[:, n_rhs] == 7.0)
+    LU, p = A.cpu().numpy()[:, :, :n].astype(np.complex128), piv.cpu().numpy()
+    u = 2.0 ** (-53 if prec == native.BEM_C128 else -24)
+    for b in range(batch):
+        L, U = np.tril(LU[b], -1) + np.eye(n), np.triu(LU[b])
+        perm = np.arange(n)
+        for i in range(n):
+            perm[[i, p[b, i]]] = perm[[p[b, i], i]]
+        for r in range(n_rhs):
+            x, rhs = X[b, r], B[b, r][perm].astype(dt.__str__().split(".")[1])
+            # substitution is backward stable entry by entry: |L U x - P b| is within
+            # 2 gamma_n |L||U||x|, gamma_n = n u up to a small factor for complex products
+            bound = 4 * (n + 4) * u * (np.abs(L) @ (np.abs(U) @ np.abs(x)))
+            assert np.all(np.abs(L @ (U @ x) - rhs) <= bound)
