@@ -20,7 +20,7 @@ ROOT = os.path.dirname(HERE)
 OUT = os.path.join(HERE, "libbem.so")
 OBJ = os.path.join(HERE, "_build")
 
-HIP_SOURCES = ["operator.hip", "lu.hip", "trsv.hip", "ir.hip", "field.hip", "synth.hip", "mlp.hip", "quad.hip",
+HIP_SOURCES = ["operator.hip", "lu.hip", "panel.hip", "trsv.hip", "ir.hip", "field.hip", "synth.hip", "mlp.hip", "quad.hip",
                "chief.hip", "api.cpp"]
 HOST_SOURCES = ["mesh.cpp", "pulse.cpp"]
 

@@ -129,7 +129,7 @@ enum { kGemm4M = 0, kGemm3M = 1, kGemmBf16x3 = 2, kGemmBf16x3Unpacked = 3 };
 
 struct LuPlan {
   int nb = 0;          // top-level panel width (0 = recursive halving)
-  int base = 8;        // width of the register-held base panel
+  int base = 32;       // most columns of a register-held panel
   // float32 MFMA updates: the 128 x 64 tile for updates of at most this many
   // columns (128 x 128 above), and the launch form (0: a workgroup per tile,
   // 1: persistent workgroups drawing tiles from a per-XCD counter)

@@ -15,270 +15,15 @@
 #include <type_traits>
 
 #include "common.h"
+#include "lu_types.h"
 
 namespace bem {
+using namespace lud;
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-// Pointers into the matrices are qualified with the global address space so
-// that loads and stores compile to global (not flat) memory instructions: flat
-// accesses also count against the LDS wait counter and would make every LDS
-// wait in the GEMM loop wait for the global prefetch as well.  (The qualifier
-// only exists in the device pass; the host pass sees plain pointers.)
-#if defined(__HIP_DEVICE_COMPILE__)
-#define GLOBAL __attribute__((address_space(1)))
-#define LDS_AS __attribute__((address_space(3)))
-#else
-#define GLOBAL
-#define LDS_AS
-#endif
-
-template <typename R> struct Cx;
-template <> struct Cx<float> { using T = float2; };
-template <> struct Cx<double> { using T = double2; };
-
-template <typename C> __device__ inline C cmk(decltype(C::x) a, decltype(C::x) b) {
-  C c; c.x = a; c.y = b; return c;
-}
-template <typename C> __device__ inline C cmul(C a, C b) {
-  return cmk<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-template <typename C> __device__ inline C csub(C a, C b) { return cmk<C>(a.x - b.x, a.y - b.y); }
-// s - a b as four fused multiply-adds (one rounding per real product-sum
-// instead of a rounded product then a subtraction)
-template <typename C> __device__ inline C cfms(C s, C a, C b) {
-  return cmk<C>(fma(-a.x, b.x, fma(a.y, b.y, s.x)), fma(-a.x, b.y, fma(-a.y, b.x, s.y)));
-}
-template <typename C> __device__ inline C crecip(C a) {
-  // 1/a with scaling to avoid overflow (Smith's method)
-  using R = decltype(C::x);
-  if (fabs(a.x) >= fabs(a.y)) {
-    R t = a.y / a.x, d = a.x + a.y * t;
-    return cmk<C>(R(1) / d, -t / d);
-  } else {
-    R t = a.x / a.y, d = a.y + a.x * t;
-    return cmk<C>(t / d, R(-1) / d);
-  }
-}
-
-// ============================================================== matrix groups
-// The matrices of one launch come in up to kMaxGroups size classes (uneven
-// batches: bodies of different node counts, each with many wavenumbers).  The
-// table travels by value in the kernel arguments; the flattened matrix index
-// of a workgroup selects its group, and every range is clipped to the group's
-// own n, so one recursion over the largest n factors every matrix.
-constexpr int kMaxGroups = 8;
-struct LuGroup {
-  void* A;          // matrix 0 of the group (row-major, element type of the launch)
-  int32_t* piv;     // [count][n]
-  int32_t* info;    // [count]
-  int64_t ld;       // leading dimension (elements)
-  int64_t stride;   // elements between consecutive matrices
-  int n;
-  int count;
-};
-struct LuGroups {
-  LuGroup g[kMaxGroups];
-  int ng;
-};
-
-// q: flattened matrix index -> its group (copied out) and index li inside it.
-// Both loops run over constant indices and copy field by field, so the table
-// is read with uniform loads from the kernel arguments (a dynamic index or a
-// whole-struct copy would place the table in scratch memory).
-__device__ inline bool locate(const LuGroups& G, int q, LuGroup& out, int& li) {
-  int sel = -1;
-#pragma unroll
-  for (int i = 0; i < kMaxGroups; ++i) {
-    if (sel < 0 && i < G.ng) {
-      if (q < G.g[i].count) { sel = i; li = q; }
-      else q -= G.g[i].count;
-    }
-  }
-  if (sel < 0) return false;
-#pragma unroll
-  for (int i = 0; i < kMaxGroups; ++i)
-    if (i == sel) {
-      out.A = G.g[i].A;
-      out.piv = G.g[i].piv;
-      out.info = G.g[i].info;
-      out.ld = G.g[i].ld;
-      out.stride = G.g[i].stride;
-      out.n = G.g[i].n;
-      out.count = G.g[i].count;
-    }
-  return true;
-}
-
-// matrix b of a group, as a global pointer
-template <typename C> __device__ inline GLOBAL C* gmat(const LuGroup& g, int b) {
-  return (GLOBAL C*)g.A + (int64_t)b * g.stride;
-}
-
-// ============================================================== base panel
-// Factor columns [c0, c0+w) of rows [c0, n) in place; w <= W.  Thread t owns
-// rows c0 + t + q*NT (q < RPT).  Pivot = max |re|+|im| (lowest row on ties).
-constexpr int kPanelThreads = 512;
-
-template <typename R, int W, int RPT>
-__global__ __launch_bounds__(kPanelThreads) void panel_kernel(LuGroups G, int c0, int w_all) {
-  using C = typename Cx<R>::T;
-  constexpr int NT = kPanelThreads, NW = NT / 64;
-  // pivot and top rows are double-buffered by column parity, so one column's
-  // readers never race the next column's writers; two barriers per column
-  __shared__ C pivrow[2][W];
-  __shared__ C toprow[2][W];
-  __shared__ R rv[NW];
-  __shared__ int ri[NW];
-  LuGroup grp;
-  int b = 0;
-  if (!locate(G, blockIdx.x, grp, b)) return;
-  const int n = grp.n;
-  const int64_t ld = grp.ld;
-  if (c0 >= n) return;
-  const int w = min(w_all, n - c0);
-  GLOBAL C* Ab = gmat<C>(grp, b);
-  GLOBAL int32_t* piv = (GLOBAL int32_t*)grp.piv;
-  GLOBAL int32_t* info = (GLOBAL int32_t*)grp.info;
-  const int t = threadIdx.x;
-  const int lane = t & 63, wid = t >> 6;
-  C a[RPT][W];
-  // full-width panels with 16-byte aligned rows move whole rows as 16-byte
-  // words; rows past n are read clamped and zeroed, never stored
-  const bool vec = w == W && (sizeof(C) == 16 || ((ld | c0) & 1) == 0);
-  if (vec) {
-    constexpr int PER = 16 / sizeof(C);   // complex values per 16-byte word
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int r = c0 + t + q * NT;
-      const GLOBAL uint4* src = (const GLOBAL uint4*)(Ab + (int64_t)min(r, n - 1) * ld + c0);
-      uint4 v[W / PER];
-#pragma unroll
-      for (int m = 0; m < W / PER; ++m) v[m] = src[m];
-#pragma unroll
-      for (int m = 0; m < W / PER; ++m) {
-        C e[PER];
-        __builtin_memcpy(e, &v[m], 16);
-#pragma unroll
-        for (int u = 0; u < PER; ++u) a[q][m * PER + u] = r < n ? e[u] : cmk<C>(R(0), R(0));
-      }
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int r = c0 + t + q * NT;
-#pragma unroll
-      for (int c = 0; c < W; ++c)
-        a[q][c] = (r < n && c < w) ? Ab[(int64_t)r * ld + c0 + c] : cmk<C>(R(0), R(0));
-    }
-  }
-  // The column loop is unrolled so that every register index is static.  Row
-  // c0 + c is held by thread c in slot 0; a row r > c0 + c is below the
-  // diagonal unless it sits in slot 0 of a thread t <= c.
-#pragma unroll
-  for (int c = 0; c < W; ++c) {
-    if (c >= w) break;
-    const int pr = c0 + c;
-    const int buf = c & 1;
-    // candidate of this thread, then of its wave
-    R best = R(-1);
-    int bidx = 0x7fffffff;
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int r = c0 + t + q * NT;
-      const R m = fabs(a[q][c].x) + fabs(a[q][c].y);
-      if ((q > 0 || t >= c) && r < n && m > best) { best = m; bidx = r; }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const R ob = __shfl_down(best, off, 64);
-      const int oi = __shfl_down(bidx, off, 64);
-      if (ob > best || (ob == best && oi < bidx)) { best = ob; bidx = oi; }
-    }
-    if (lane == 0) { rv[wid] = best; ri[wid] = bidx; }
-    __syncthreads();
-    // every thread reduces the wave partials (same order, same result)
-    R bb = rv[0];
-    int bi = ri[0];
-#pragma unroll
-    for (int q = 1; q < NW; ++q)
-      if (rv[q] > bb || (rv[q] == bb && ri[q] < bi)) { bb = rv[q]; bi = ri[q]; }
-    const bool singular = !(bb > R(0));   // exactly zero (or NaN) column: no interchange
-    const int p = singular ? pr : bi;
-    if (t == 0) {
-      if (singular && info[b] == 0) info[b] = pr + 1;
-      piv[(int64_t)b * n + pr] = p;
-    }
-    // the owners of rows p and pr publish them
-    const int op = (p - c0) % NT, qp = (p - c0) / NT;
-    if (t == op) {
-#pragma unroll
-      for (int q = 0; q < RPT; ++q)
-        if (q == qp)
-#pragma unroll
-          for (int cc = 0; cc < W; ++cc) pivrow[buf][cc] = a[q][cc];
-    }
-    if (t == c && p != pr)
-#pragma unroll
-      for (int cc = 0; cc < W; ++cc) toprow[buf][cc] = a[0][cc];
-    __syncthreads();
-    if (p != pr) {
-      if (t == op) {
-#pragma unroll
-        for (int q = 0; q < RPT; ++q)
-          if (q == qp)
-#pragma unroll
-            for (int cc = 0; cc < W; ++cc) a[q][cc] = toprow[buf][cc];
-      }
-      if (t == c)
-#pragma unroll
-        for (int cc = 0; cc < W; ++cc) a[0][cc] = pivrow[buf][cc];
-    }
-    if (!singular) {
-      C u[W];
-#pragma unroll
-      for (int cc = c; cc < W; ++cc) u[cc] = pivrow[buf][cc];
-      const C inv = crecip(u[c]);
-      // rows past n hold zeros and are never stored
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        if (q == 0 && t <= c) continue;
-        const C l = cmul(a[q][c], inv);
-        a[q][c] = l;
-#pragma unroll
-        for (int cc = c + 1; cc < W; ++cc) a[q][cc] = cfms(a[q][cc], l, u[cc]);
-      }
-    }
-  }
-  if (vec) {
-    constexpr int PER = 16 / sizeof(C);
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int r = c0 + t + q * NT;
-      if (r < n) {
-        GLOBAL uint4* dst = (GLOBAL uint4*)(Ab + (int64_t)r * ld + c0);
-#pragma unroll
-        for (int m = 0; m < W / PER; ++m) {
-          uint4 v;
-          __builtin_memcpy(&v, &a[q][m * PER], 16);
-          dst[m] = v;
-        }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int r = c0 + t + q * NT;
-      if (r < n)
-#pragma unroll
-        for (int c = 0; c < W; ++c)
-          if (c < w) Ab[(int64_t)r * ld + c0 + c] = a[q][c];
-    }
-  }
-}
 
 // ============================================================== row swaps
 // Interchanges t <-> piv[t] for t in [r0, r1) (r1 - r0 <= kSwapRows), applied
@@ -2095,7 +1840,6 @@ struct Fac {
   bem_prec prec;
   std::vector<LuGroup> groups;   // sorted by n, descending
   LuPlan plan;
-  int base = 8;
   int gkind = kGemm4M;           // complex GEMM form for c64 (bem_gemm_kind)
   int nmax = 0;
   bool use_pack = false;         // large updates on operands split into 16-bit words
@@ -2127,38 +1871,12 @@ struct Fac {
     return s;
   }
 
-  template <typename R, int W, int RPT>
-  void panel_go(const LuGroups& G, int total, int c0, int w) {
-    hipLaunchKernelGGL((panel_kernel<R, W, RPT>), dim3(total), dim3(kPanelThreads), 0,
-                       ctx->stream, G, c0, w);
-  }
-  template <typename R, int W>
-  void panel_w(const LuGroups& G, int total, int rows, int c0, int w) {
-    const int rpt = (rows + kPanelThreads - 1) / kPanelThreads;
-    if (rpt <= 1) panel_go<R, W, 1>(G, total, c0, w);
-    else if (rpt <= 2) panel_go<R, W, 2>(G, total, c0, w);
-    else if (rpt <= 4) panel_go<R, W, 4>(G, total, c0, w);
-    else if (rpt <= 6) panel_go<R, W, 6>(G, total, c0, w);
-    else if (rpt <= 8) panel_go<R, W, 8>(G, total, c0, w);
-    else if (rpt <= 10) panel_go<R, W, 10>(G, total, c0, w);
-    else if (rpt <= 11) panel_go<R, W, 11>(G, total, c0, w);
-    else if (rpt <= 12) panel_go<R, W, 12>(G, total, c0, w);
-    else if (W <= 4 && sizeof(R) == 4) panel_go<R, (W <= 4 ? W : 4), 24>(G, total, c0, w);
-    else panel_go<R, (W <= 2 ? W : 2), 24>(G, total, c0, w);
-  }
   void panel(int c0, int w) {
     int total, maxn;
     const LuGroups G = active(c0, &total, &maxn);
     if (total == 0) return;
     const int pi = prof_begin(ctx, "panel");
-    const int rows = maxn - c0;
-    if (prec == BEM_C128) {
-      if (base >= 4) panel_w<double, 4>(G, total, rows, c0, w);
-      else panel_w<double, 2>(G, total, rows, c0, w);
-    } else {
-      if (base >= 8) panel_w<float, 8>(G, total, rows, c0, w);
-      else panel_w<float, 4>(G, total, rows, c0, w);
-    }
+    launch_panel(ctx, prec, G, total, maxn - c0, c0, w);
     // a panel of w columns over m rows: ~ 8 m w^2 / 2 flops, m w elements read and written
     const double es = (double)esz();
     prof_end(ctx, "panel", pi,
@@ -2441,15 +2159,17 @@ struct Fac {
     gemm(r0 + h1, col0, r0, r0, r0 + m1, col1, h1);
     trsm(r0 + h1, m1 - h1, col0, col1);
   }
-  int split(int w) const {
+  // width of the panels starting at column c
+  int base(int c) const { return std::min(plan.base, panel_width(prec, nmax - c)); }
+  static int split(int w, int base) {
     int h = (w / 2 + base - 1) / base * base;
     if (h >= w) h = w - base;
     return h;
   }
   void rec(int c0, int c1) {
     const int w = c1 - c0;
-    if (w <= base) { panel(c0, w); return; }
-    const int h = split(w);
+    if (w <= base(c0)) { panel(c0, w); return; }
+    const int h = split(w, base(c0));
     rec(c0, c0 + h);
     laswp(c0, c0 + h, c0 + h, c1);
     trsm(c0, h, c0 + h, c1);
@@ -2509,9 +2229,8 @@ static bem_status build_fac(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
   f.use_pack = prec == BEM_C64 && (gemm_kind == kGemmBf16x3 || gemm_kind == kGemm3M);
   for (const LuMatrixSet& s : sets) {
     if (s.count <= 0 || s.n <= 0) continue;
-    if (s.n > 24 * kPanelThreads)
-      return fail(ctx, BEM_EUNSUPPORTED, "lu_factor: n=%d above the supported %d", s.n,
-                  24 * kPanelThreads);
+    if (s.n > kPanelRows)
+      return fail(ctx, BEM_EUNSUPPORTED, "lu_factor: n=%d above the supported %d", s.n, kPanelRows);
     if ((int64_t)s.n * s.ld >= ((int64_t)1 << 31))
       return fail(ctx, BEM_EUNSUPPORTED, "lu_factor: n*ld = %lld must stay below 2^31",
                   (long long)s.n * s.ld);
@@ -2530,10 +2249,6 @@ static bem_status build_fac(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
     return fail(ctx, BEM_EUNSUPPORTED, "lu_factor: more than %d matrix sizes in one batch", kMaxGroups);
   std::sort(f.groups.begin(), f.groups.end(), [](const LuGroup& a, const LuGroup& b) { return a.n > b.n; });
   f.nmax = f.groups[0].n;
-  const int rows_per_thread = (f.nmax + kPanelThreads - 1) / kPanelThreads;
-  if (prec == BEM_C128) f.base = rows_per_thread <= 10 ? 4 : 2;
-  else f.base = rows_per_thread <= 11 ? 8 : 4;
-  if (plan.base > 0 && plan.base < f.base) f.base = plan.base;
   // block width (the interchange passes are split into ranges of kSwapRows rows)
   nb = plan.nb > 0 ? std::min(plan.nb, 4 * kSwapRows) : kSwapRows;
   return BEM_OK;
