@@ -11,6 +11,7 @@
 // complex products on the f64 MFMA.
 #include <algorithm>
 #include <climits>
+#include <utility>
 
 #include <type_traits>
 
@@ -39,10 +40,18 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // piv[t].  A row below r1 ends holding c(u) of the last step u that targets
 // it.  The touched rows are then gathered into LDS and scattered back.
 constexpr int kSwapRows = 256;
+constexpr int kSwapJobs = 12;   // a panel's ancestors in a block of 512 columns, and the block
+struct SwapJob {
+  int r0, r1, ca0, ca1, cb0, cb1;
+};
+struct SwapJobs {
+  SwapJob job[kSwapJobs];
+  int strip0[kSwapJobs + 1];   // first strip of each job; strip0[count] of them in all
+  int count;
+};
 
 template <typename C, int LW>
-__global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, int r0, int r1_all, int ca0,
-                                                    int ca1_all, int cb0, int cb1_all) {
+__global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, SwapJobs J) {
   __shared__ int P[kSwapRows];
   __shared__ int root[kSwapRows];
   __shared__ int dst[2 * kSwapRows], src[2 * kSwapRows];
@@ -53,11 +62,26 @@ __global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, int r0, int r1_a
   if (!locate(G, blockIdx.y, grp, b)) return;
   const int n = grp.n;
   const int64_t ld = grp.ld;
-  const int r1 = min(r1_all, n);
+  // (constant indices into the kernel arguments)
+  SwapJob job = J.job[0];
+  int strip0 = 0;
+#pragma unroll
+  for (int i = 1; i < kSwapJobs; ++i)
+    if (i < J.count && (int)blockIdx.x >= J.strip0[i]) {
+      job.r0 = J.job[i].r0;
+      job.r1 = J.job[i].r1;
+      job.ca0 = J.job[i].ca0;
+      job.ca1 = J.job[i].ca1;
+      job.cb0 = J.job[i].cb0;
+      job.cb1 = J.job[i].cb1;
+      strip0 = J.strip0[i];
+    }
+  const int r0 = job.r0, ca0 = job.ca0, cb0 = job.cb0;
+  const int r1 = min(job.r1, n);
   if (r1 <= r0) return;
-  const int ca1 = min(ca1_all, n), cb1 = min(cb1_all, n);
+  const int ca1 = min(job.ca1, n), cb1 = min(job.cb1, n);
   const int na = max(0, ca1 - ca0), nbc = max(0, cb1 - cb0);
-  const int s0 = blockIdx.x * LW;
+  const int s0 = ((int)blockIdx.x - strip0) * LW;
   if (s0 >= na + nbc) return;
   const int L = r1 - r0;
   const int tid = threadIdx.x;
@@ -80,7 +104,7 @@ __global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, int r0, int r1_a
   if (tid < L && root[tid] < 0) root[tid] = tid;
   __syncthreads();
   // pointer jumping to the chain roots (root[i] == i marks a root)
-  for (int it = 0; it < 9; ++it) {
+  for (int len = 1; len < L; len *= 2) {   // a chain has at most L links
     int rr = 0;
     if (tid < L) rr = root[root[tid]];
     __syncthreads();
@@ -131,50 +155,80 @@ __global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, int r0, int r1_a
 }
 
 // ============================================================== small TRSM
-// X = L^{-1} B, L = unit lower triangle of rows/cols [r0, r0+m1) (m1 <= 32),
-// B = rows [r0, r0+m1) x cols [col0, col0+ncol); one column per thread.
-template <typename C>
+// X = L^{-1} B, L = unit lower triangle of rows/cols [r0, r0+m1) (m1 <= M),
+// B = rows [r0, r0+m1) x cols [col0, col1).  The chain of M unknowns bounds it:
+// four neighbouring lanes share a column (lane g holds rows 4k + g), so a step
+// hands one unknown round the quad and updates M/4 rows per lane at most, and
+// a workgroup of 64 columns spreads over the four SIMDs.  One lane per column and
+// 32 unknowns took 12 us at 162 columns where this takes 7 us, and 64 unknowns (16 us)
+// took two such launches and a product between them.  Wide block rows (64
+// matrices, 2500 columns: 49 us) are bound by the FMA rate and the reads of L.
+template <int Q>
+__device__ __forceinline__ float quad_value(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * Q, 0xf, 0xf, true));
+}
+template <int Q>
+__device__ __forceinline__ double quad_value(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, 0x55 * Q, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0x55 * Q, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// unknown 4 K0 + Q of every column, out of the rows below it
+template <typename C, int KR, int K0, int Q, typename LM>
+__device__ __forceinline__ void trsm_step(C (&x)[KR], const LM& L, int g) {
+  const C xj = cmk<C>(quad_value<Q>(x[K0].x), quad_value<Q>(x[K0].y));
+  const auto* l = L[4 * K0 + Q][g];
+  if (Q < 3) {   // the rest of its own four rows
+    const C s = cfms(x[K0], l[K0], xj);
+    x[K0].x = g > Q ? s.x : x[K0].x;
+    x[K0].y = g > Q ? s.y : x[K0].y;
+  }
+#pragma unroll
+  for (int k = K0 + 1; k < KR; ++k) x[k] = cfms(x[k], l[k], xj);
+}
+template <typename C, int KR, typename LM, int... K>
+__device__ __forceinline__ void trsm_steps(C (&x)[KR], const LM& L, int g,
+                                           std::integer_sequence<int, K...>) {
+  ((trsm_step<C, KR, K, 0>(x, L, g), trsm_step<C, KR, K, 1>(x, L, g),
+    trsm_step<C, KR, K, 2>(x, L, g), trsm_step<C, KR, K, 3>(x, L, g)), ...);
+}
+
+template <typename C, int M>
 __global__ __launch_bounds__(256) void trsm_kernel(LuGroups G, int r0, int m1_all, int col0,
                                                    int col1) {
-  __shared__ C L[32][33];
+  constexpr int KR = M / 4;                       // rows per lane
+  constexpr int KP = KR + 16 / (int)sizeof(C);    // padded: the quad's lanes read other banks
+  __shared__ C L[M][4][KP];                       // column j: rows 4k + g at [j][g][k]
   LuGroup grp;
   int b = 0;
   if (!locate(G, blockIdx.y, grp, b)) return;
   const int n = grp.n;
   const int64_t ld = grp.ld;
   const int m1 = min(m1_all, n - r0);
-  if (m1 <= 1) return;
+  const int cend = min(col1, n);
+  if (m1 <= 1 || col0 + (int)blockIdx.x * 64 >= cend) return;
   GLOBAL C* Ab = gmat<C>(grp, b);
-  for (int e = threadIdx.x; e < m1 * m1; e += blockDim.x) {
-    const int i = e / m1, j = e % m1;
-    L[i][j] = Ab[(int64_t)(r0 + i) * ld + r0 + j];
+  const int t = threadIdx.x, g = t & 3;
+  const int col = col0 + blockIdx.x * 64 + (t >> 2);
+  // rows past m1 and columns past the last are read clamped and never stored
+  C x[KR];
+#pragma unroll
+  for (int k = 0; k < KR; ++k)
+    x[k] = Ab[(int64_t)(r0 + min(4 * k + g, m1 - 1)) * ld + min(col, cend - 1)];
+#pragma unroll
+  for (int e = t; e < M * M; e += 256) {
+    const int i = e / M, j = e % M;
+    const C v = Ab[(int64_t)(r0 + min(i, m1 - 1)) * ld + r0 + min(j, m1 - 1)];
+    if (j < i) L[j][i & 3][i >> 2] = i < m1 ? v : cmk<C>(0, 0);
   }
   __syncthreads();
-  const int col = col0 + blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= min(col1, n)) return;
-  C x[32];
-  // rows past m1 are read clamped and never stored, so the loads and stores
-  // carry no per-row branches
+  trsm_steps<C, KR>(x, L, g, std::make_integer_sequence<int, KR>{});
+  if (col >= cend) return;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) x[i] = Ab[(int64_t)(r0 + min(i, m1 - 1)) * ld + col];
-#pragma unroll
-  for (int i = 1; i < 32; ++i) {
-    if (i < m1) {
-      C s = x[i];
-#pragma unroll
-      for (int j = 0; j < 32; ++j)
-        if (j < i) s = cfms(s, L[i][j], x[j]);
-      x[i] = s;
-    }
-  }
-  if (m1 == 32) {
-#pragma unroll
-    for (int i = 1; i < 32; ++i) Ab[(int64_t)(r0 + i) * ld + col] = x[i];
-  } else {
-#pragma unroll
-    for (int i = 1; i < 32; ++i)
-      if (i < m1) Ab[(int64_t)(r0 + i) * ld + col] = x[i];
-  }
+  for (int k = 0; k < KR; ++k)
+    if (4 * k + g < m1 && 4 * k + g > 0) Ab[(int64_t)(r0 + 4 * k + g) * ld + col] = x[k];
 }
 
 // ============================================================== GEMM f32 (4M)
@@ -1845,6 +1899,7 @@ struct Fac {
   bool use_pack = false;         // large updates on operands split into 16-bit words
   void* pack = nullptr;          // packing buffer (context-owned) and its size
   size_t pack_bytes = 0;
+  std::vector<SwapJob> left;     // interchanges put off by swap_left
 
   size_t esz() const { return prec == BEM_C128 ? 16 : 8; }
 
@@ -1884,28 +1939,53 @@ struct Fac {
              work(c0, [&](int n) { const double m = n - c0, ww = std::min(w, n - c0); return 2.0 * es * m * ww; }));
   }
   // interchanges of rows [r0, r1) applied to columns [ca0, ca1) and [cb0, cb1)
+  // and, with them, those put off by swap_left
   void laswp(int r0, int r1, int ca0, int ca1, int cb0 = 0, int cb1 = 0) {
-    for (int q0 = r0; q0 < r1; q0 += kSwapRows) {
-      const int q1 = std::min(r1, q0 + kSwapRows);
-      int total, maxn;
-      const LuGroups G = active(q0, &total, &maxn);
-      if (total == 0) return;
-      const int na = std::max(0, std::min(ca1, maxn) - ca0);
-      const int nbc = std::max(0, std::min(cb1, maxn) - cb0);
-      if (na + nbc == 0) return;
-      const int pi = prof_begin(ctx, "laswp");
-      if (prec == BEM_C128) {
-        constexpr int LW = 8;
-        hipLaunchKernelGGL((laswp_kernel<double2, LW>), dim3((na + nbc + LW - 1) / LW, total),
-                           dim3(256), 0, ctx->stream, G, q0, q1, ca0, ca1, cb0, cb1);
-      } else {
-        constexpr int LW = 16;
-        hipLaunchKernelGGL((laswp_kernel<float2, LW>), dim3((na + nbc + LW - 1) / LW, total),
-                           dim3(256), 0, ctx->stream, G, q0, q1, ca0, ca1, cb0, cb1);
+    left.push_back({r0, r1, ca0, ca1, cb0, cb1});
+    swap_pending();
+  }
+  // interchanges of rows [r0, r1) for columns [ca0, ca1), needed only when an
+  // update reads those columns, which a laswp of columns right of them precedes
+  void swap_left(int r0, int r1, int ca0, int ca1) {
+    left.push_back({r0, r1, ca0, ca1, 0, 0});
+    if (left.size() == (size_t)kSwapJobs) swap_pending();
+  }
+  void swap_pending() {
+    // (the columns of the jobs are disjoint; ranges of more than kSwapRows go in turns)
+    for (bool more = true; more && !left.empty();) {
+      more = false;
+      SwapJobs J{};
+      int total = 0, first = INT32_MAX;
+      double moved = 0.0;
+      const int lw = prec == BEM_C128 ? 8 : 16;
+      for (SwapJob& j : left) {
+        if (j.r0 >= j.r1) continue;
+        SwapJob q = j;
+        q.r1 = std::min(j.r1, j.r0 + kSwapRows);
+        j.r0 = q.r1;
+        more |= j.r0 < j.r1;
+        const int cols = std::max(0, std::min(q.ca1, nmax) - q.ca0) + std::max(0, std::min(q.cb1, nmax) - q.cb0);
+        if (cols == 0) continue;
+        J.job[J.count] = q;
+        J.strip0[J.count + 1] = J.strip0[J.count] + (cols + lw - 1) / lw;
+        ++J.count;
+        first = std::min(first, q.r0);
+        moved += (double)(q.r1 - q.r0) * cols;
       }
+      if (J.count == 0) continue;
+      int maxn;
+      const LuGroups G = active(first, &total, &maxn);
+      if (total == 0) continue;
+      const int pi = prof_begin(ctx, "laswp");
+      const dim3 grid(J.strip0[J.count], total), bd(256);
+      if (prec == BEM_C128)
+        hipLaunchKernelGGL((laswp_kernel<double2, 8>), grid, bd, 0, ctx->stream, G, J);
+      else
+        hipLaunchKernelGGL((laswp_kernel<float2, 16>), grid, bd, 0, ctx->stream, G, J);
       // at most every row of the range moves once (read and write)
-      prof_end(ctx, "laswp", pi, 0.0, 2.0 * esz() * (double)(q1 - q0) * (na + nbc) * total);
+      prof_end(ctx, "laswp", pi, 0.0, 2.0 * esz() * moved * total);
     }
+    left.clear();
   }
   // C = rows [rowC, rowEnd) x cols [colC, colEnd) -= A(rows, [colA, colA+K)) B([rowB, rowB+K), cols)
   // every (matrix, tile) pair of an update, tiles of 128 x BN
@@ -2134,27 +2214,34 @@ struct Fac {
     }
     return true;
   }
+  template <typename C>
+  void trsm_go(dim3 grid, const LuGroups& G, int r0, int m1, int col0, int col1) {
+    const dim3 bd(256);
+    if (m1 <= 16)
+      hipLaunchKernelGGL((trsm_kernel<C, 16>), grid, bd, 0, ctx->stream, G, r0, m1, col0, col1);
+    else if (m1 <= 32)
+      hipLaunchKernelGGL((trsm_kernel<C, 32>), grid, bd, 0, ctx->stream, G, r0, m1, col0, col1);
+    else
+      hipLaunchKernelGGL((trsm_kernel<C, 64>), grid, bd, 0, ctx->stream, G, r0, m1, col0, col1);
+  }
   // X = L^{-1} X for rows [r0, r0+m1) and columns [col0, col1)
   void trsm(int r0, int m1, int col0, int col1) {
     if (col1 <= col0 || m1 <= 1) return;
-    if (m1 <= 32) {
+    if (m1 <= 64) {
       int total, maxn;
       const LuGroups G = active(r0 + 1, &total, &maxn);
       if (total == 0) return;
       const int ncol = std::min(col1, maxn) - col0;
       if (ncol <= 0) return;
-      dim3 grid((ncol + 255) / 256, total);
+      const dim3 grid((ncol + 63) / 64, total);
       const int pi = prof_begin(ctx, "trsm");
-      if (prec == BEM_C128)
-        hipLaunchKernelGGL(trsm_kernel<double2>, grid, dim3(256), 0, ctx->stream, G, r0, m1, col0, col1);
-      else
-        hipLaunchKernelGGL(trsm_kernel<float2>, grid, dim3(256), 0, ctx->stream, G, r0, m1, col0, col1);
+      if (prec == BEM_C128) trsm_go<double2>(grid, G, r0, m1, col0, col1);
+      else trsm_go<float2>(grid, G, r0, m1, col0, col1);
       prof_end(ctx, "trsm", pi, 4.0 * m1 * m1 * (double)ncol * total,
                2.0 * esz() * m1 * (double)ncol * total);
       return;
     }
-    int h1 = ((m1 / 2) + 31) / 32 * 32;
-    if (h1 >= m1) h1 = m1 - 32;
+    const int h1 = ((m1 / 2) + 63) / 64 * 64;
     trsm(r0, h1, col0, col1);
     gemm(r0 + h1, col0, r0, r0, r0 + m1, col1, h1);
     trsm(r0 + h1, m1 - h1, col0, col1);
@@ -2175,7 +2262,7 @@ struct Fac {
     trsm(c0, h, c0 + h, c1);
     gemm(c0 + h, c0 + h, c0, c0, INT32_MAX, c1, h);
     rec(c0 + h, c1);
-    laswp(c0 + h, c1, c0, c0 + h);
+    swap_left(c0 + h, c1, c0, c0 + h);
   }
   // Right-looking blocked top level: factor a block of nb columns (recursively),
   // apply its interchanges to every column left and right of it in one pass,
