@@ -43,33 +43,6 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
-// Block-wide sum of a [R][C] array held per thread; result valid in thread 0.
-template <int R, int C>
-__device__ inline void block_sum_2d(double (&v)[R][C]) {
-  __shared__ double red[kThreads / 64][R][C];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int a = 0; a < R; ++a)
-#pragma unroll
-    for (int c = 0; c < C; ++c) v[a][c] = wave_sum(v[a][c]);
-  if (lane == 0)
-#pragma unroll
-    for (int a = 0; a < R; ++a)
-#pragma unroll
-      for (int c = 0; c < C; ++c) red[wid][a][c] = v[a][c];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int a = 0; a < R; ++a)
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        double t = 0.0;
-        for (int q = 0; q < kThreads / 64; ++q) t += red[q][a][c];
-        v[a][c] = t;
-      }
-  }
-}
-
 // ---------------------------------------------------------------- wavenumber chunks
 // A workgroup owns one row i and a chunk of consecutive
 // wavenumbers.  The pair geometry (d, r, 1/r, d.n_j, n_i.d, n_i.n_j) is formed
@@ -112,32 +85,6 @@ __device__ inline KChunk<KC> load_chunk(const double* __restrict__ kv, int nk,
     if (q < c.kc && !(fabs(c.k[q] - (c.k[0] + q * c.dk)) <= 4e-16 * fabs(c.k[q]))) c.uniform = false;
   return c;
 }
-
-// Phase e^{i k_q t} stepped along the chunk: start() gives q = 0, next(q)
-// advances to wavenumber q (by the recurrence, or a fresh sincos).
-struct Phase {
-  double2 e, d;
-  template <int KC>
-  __device__ inline void start(const KChunk<KC>& c, double t) {
-    double s, co;
-    phase_sincos(c.k[0] * t, &s, &co);
-    e = make_double2(co, s);
-    if (c.uniform) {
-      phase_sincos(c.dk * t, &s, &co);
-      d = make_double2(co, s);
-    }
-  }
-  template <int KC>
-  __device__ inline void next(const KChunk<KC>& c, int q, double t) {
-    if (c.uniform) {
-      e = make_double2(e.x * d.x - e.y * d.y, e.x * d.y + e.y * d.x);
-    } else {
-      double s, co;
-      phase_sincos(c.k[q] * t, &s, &co);
-      e = make_double2(co, s);
-    }
-  }
-};
 
 // ---------------------------------------------------------------- assembly
 // One workgroup owns row i and a chunk of kKcAssemble wavenumbers, for one
@@ -434,65 +381,157 @@ __global__ __launch_bounds__(kThreads, 2) void assemble_kc_kernel(
   }
 }
 
-// r = -(M_phi phi + M_psi psi) for one row, a chunk of wavenumbers and one
-// right-hand side, with (phi, psi) from the unknowns xs and data y.
-__global__ __launch_bounds__(kThreads) void residual_kc_kernel(
+// ---------------------------------------------------------------- residual
+// r = -(M_phi phi + M_psi psi) for kResRows rows, a chunk of wavenumbers and one
+// right-hand side, with (phi, psi) from the unknowns xs and data y.  A pair costs
+// its geometry and two sincos per chunk and, per wavenumber, one phase step and
+// e (w/r psi + w (d.n)/r^3 (1 - i k r) phi): 15 float64 operations.  Two rows
+// share the loads of (xs, y), 32 bytes per column and wavenumber.  32 scattered
+// wavenumbers of n = 2562, a sincos each, take 400 us, most of it arithmetic (570
+// with the library's square root and division and one row a workgroup); 21 of
+// n = 1284 take 112 us (166).
+constexpr int kResRows = 2;
+
+struct ResArgs {
+  int n, i0;
+  const double *x, *nrm, *w;
+  const uint8_t* bc;
+  const double2 *xs, *y;
+};
+
+// The thread's columns; acc[row][re, im][wavenumber].  base[q]: first value of
+// wavenumber q in xs and y.  Returns whether a phase of one of its pairs reaches
+// 2^20 rad (the near forms are then invalid).
+template <int KC, int PH>
+__device__ __forceinline__ bool residual_terms(const ResArgs& p, const KChunk<KC>& kc,
+                                               const int64_t (&base)[KC], double kmax,
+                                               double (&acc)[kResRows][2][KC]) {
+  bool wide = false;
+  double xi[kResRows][3];
+#pragma unroll
+  for (int m = 0; m < kResRows; ++m)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) xi[m][c] = p.x[3 * min(p.i0 + m, p.n - 1) + c];
+  for (int j = threadIdx.x; j < p.n; j += kThreads) {
+    const double nx = p.nrm[3 * j], ny = p.nrm[3 * j + 1], nz = p.nrm[3 * j + 2];
+    const double wj = p.w[j];
+    const bool hard = p.bc[j] == BEM_BC_HARD;
+    double r[kResRows], wr[kResRows], wq[kResRows];
+    double2 e[kResRows], d[kResRows];
+#pragma unroll
+    for (int m = 0; m < kResRows; ++m) {
+      const double dx = p.x[3 * j] - xi[m][0], dy = p.x[3 * j + 1] - xi[m][1],
+                   dz = p.x[3 * j + 2] - xi[m][2];
+      const bool self = j == p.i0 + m;
+      double rinv;
+      dist_and_inverse(self ? 1.0 : dx * dx + dy * dy + dz * dz, r[m], rinv);
+      wr[m] = self ? 0.0 : wj * rinv;
+      wq[m] = wj * ((dx * nx + dy * ny + dz * nz) * (rinv * rinv * rinv));   // (0 for itself)
+      if (PH != kPhWide) wide |= !(kmax * r[m] < kPhaseNear);
+      e[m] = phase_e<PH>(kc.k[0] * r[m]);
+      if (PH == kPhRec) d[m] = phase_e<PH>(kc.dk * r[m]);
+    }
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      // (the recurrence runs through whole chunks, its loads then have no exits
+      // between them)
+      if (PH != kPhRec && q >= kc.kc) break;
+      const double2 u = p.xs[base[q] + j], v = p.y[base[q] + j];
+      const double2 phi = hard ? u : v, psi = hard ? v : u;
+#pragma unroll
+      for (int m = 0; m < kResRows; ++m) {
+        if (q > 0) {
+          if (PH == kPhRec)
+            e[m] = make_double2(fma(e[m].x, d[m].x, -(e[m].y * d[m].y)),
+                                fma(e[m].x, d[m].y, e[m].y * d[m].x));
+          else
+            e[m] = phase_e<PH>(kc.k[q] * r[m]);
+        }
+        const double kr = kc.k[q] * r[m];
+        const double zx = fma(wq[m], fma(kr, phi.y, phi.x), wr[m] * psi.x);
+        const double zy = fma(wq[m], fma(-kr, phi.x, phi.y), wr[m] * psi.y);
+        acc[m][0][q] = fma(e[m].x, zx, fma(-e[m].y, zy, acc[m][0][q]));
+        acc[m][1][q] = fma(e[m].x, zy, fma(e[m].y, zx, acc[m][1][q]));
+      }
+    }
+  }
+  return wide;
+}
+
+__global__ __launch_bounds__(kThreads, 2) void residual_kc_kernel(
     int n, const double* __restrict__ x, const double* __restrict__ nrm,
     const double* __restrict__ w, const uint8_t* __restrict__ bc, const double* __restrict__ kv,
     int nk, int n_rhs, int rhs, const double2* __restrict__ y, const double2* __restrict__ xs,
     const double2* __restrict__ diag64, double2* __restrict__ r_out,
     const int32_t* __restrict__ kidx) {
-  const int i = blockIdx.x;
-  const KChunk<kKcResidual> kc = load_chunk<kKcResidual>(kv, nk, kidx);
-  const int q0 = blockIdx.y * kKcResidual;
-  int64_t kq_of[kKcResidual];
+  constexpr int KC = kKcResidual, NW = kThreads / 64;
+  static_assert(KC == 8, "the reduction sums 8 wavenumbers per wave");
+  __shared__ double red[NW][kResRows][2][KC];
+  const KChunk<KC> kc = load_chunk<KC>(kv, nk, kidx);
+  const int q0 = blockIdx.y * KC;
+  int64_t base[KC];
+  double kmax = 0.0;
 #pragma unroll
-  for (int q = 0; q < kKcResidual; ++q) kq_of[q] = q < kc.kc ? (kidx ? kidx[q0 + q] : q0 + q) : 0;
-  const double xi = x[3 * i], yi = x[3 * i + 1], zi = x[3 * i + 2];
-  double acc[kKcResidual][2];
+  for (int q = 0; q < KC; ++q) {
+    const int64_t kq = q < kc.kc ? (kidx ? kidx[q0 + q] : q0 + q) : 0;
+    base[q] = (kq * n_rhs + rhs) * n;
+    kmax = fmax(kmax, fabs(kc.k[q]));
+  }
+  const ResArgs p{n, (int)blockIdx.x * kResRows, x, nrm, w, bc, xs, y};
+  double acc[kResRows][2][KC] = {};
+  // half a chunk or less on an even grid costs less with its own sincos
+  const bool rec = kc.uniform && 2 * kc.kc > KC;
+  const bool wide = rec ? residual_terms<KC, kPhRec>(p, kc, base, kmax, acc)
+                        : residual_terms<KC, kPhNear>(p, kc, base, kmax, acc);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-  for (int q = 0; q < kKcResidual; ++q) { acc[q][0] = 0.0; acc[q][1] = 0.0; }
-  for (int j = threadIdx.x; j < n; j += kThreads) {
-    if (j == i) continue;
-    const double dx = x[3 * j] - xi, dy = x[3 * j + 1] - yi, dz = x[3 * j + 2] - zi;
-    const double r = sqrt(dx * dx + dy * dy + dz * dz);
-    const double rinv = 1.0 / r;
-    const double qn = (dx * nrm[3 * j] + dy * nrm[3 * j + 1] + dz * nrm[3 * j + 2]) * (rinv * rinv * rinv);
-    const double wj = w[j];
-    const bool hard = bc[j] == BEM_BC_HARD;
-    Phase E;
-    E.start(kc, r);
+  for (int m = 0; m < kResRows; ++m)
 #pragma unroll
-    for (int q = 0; q < kKcResidual; ++q) {
-      if (q < kc.kc) {
-        if (q > 0) E.next(kc, q, r);
-        const double kr = kc.k[q] * r;
-        const double2 G = make_double2(E.e.x * rinv, E.e.y * rinv);
-        const double2 H = make_double2(qn * (-E.e.x - kr * E.e.y), qn * (kr * E.e.x - E.e.y));
-        const int64_t o = (kq_of[q] * n_rhs + rhs) * n + j;
-        const double2 u = xs[o], v = y[o];
-        const double2 phi = hard ? u : v, psi = hard ? v : u;
-        // -w H phi + w G psi
-        acc[q][0] += wj * ((G.x * psi.x - G.y * psi.y) - (H.x * phi.x - H.y * phi.y));
-        acc[q][1] += wj * ((G.x * psi.y + G.y * psi.x) - (H.x * phi.y + H.y * phi.x));
-      }
+    for (int c = 0; c < 2; ++c) {
+      const double v = wave_reduce8(acc[m][c]);
+      if ((lane & 7) == 0) red[wid][m][c][lane >> 3] = v;
+    }
+  if (__syncthreads_or(wide)) {
+    // a phase reaches past the near range: the rows again, one wavenumber at a
+    // time with the library sincos
+    for (int q = 0; q < kc.kc; ++q) {
+      const int kq = kidx ? kidx[q0 + q] : q0 + q;
+      const int64_t b1[1] = {((int64_t)kq * n_rhs + rhs) * n};
+      KChunk<1> k1;
+      k1.k[0] = kv[kq];
+      k1.dk = 0.0;
+      k1.kc = 1;
+      k1.uniform = false;
+      double a1[kResRows][2][1] = {};
+      (void)residual_terms<1, kPhWide>(p, k1, b1, kmax, a1);
+#pragma unroll
+      for (int m = 0; m < kResRows; ++m)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const double v = wave_sum(a1[m][c][0]);
+          if (lane == 0) red[wid][m][c][q] = v;
+        }
     }
   }
-  block_sum_2d(acc);
-  if (threadIdx.x == 0) {
-    const bool hard = bc[i] == BEM_BC_HARD;
+  __syncthreads();
+  const int m = threadIdx.x / KC, q = threadIdx.x % KC;
+  const int i = p.i0 + m;
+  if (m < kResRows && q < kc.kc && i < n) {
+    double s[2] = {0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < kKcResidual; ++q) {
-      if (q >= kc.kc) break;
-      const int64_t kq = kq_of[q];
-      const double2 dphi = diag64[(kq * n + i) * 2];
-      const double2 dpsi = diag64[(kq * n + i) * 2 + 1];
-      const int64_t o = (kq * n_rhs + rhs) * n + i;
-      const double2 u = xs[o], v = y[o];
-      const double2 phi = hard ? u : v, psi = hard ? v : u;
-      const double2 t1 = cmul(dphi, phi), t2 = cmul(dpsi, psi);
-      r_out[o] = make_double2(-(acc[q][0] + t1.x + t2.x), -(acc[q][1] + t1.y + t2.y));
+    for (int v = 0; v < NW; ++v) {
+      s[0] += red[v][m][0][q];
+      s[1] += red[v][m][1][q];
     }
+    const int64_t kq = kidx ? kidx[q0 + q] : q0 + q;
+    const bool hard = bc[i] == BEM_BC_HARD;
+    const double2 dphi = diag64[(kq * n + i) * 2];
+    const double2 dpsi = diag64[(kq * n + i) * 2 + 1];
+    const int64_t o = (kq * n_rhs + rhs) * n + i;
+    const double2 u = xs[o], v = y[o];
+    const double2 phi = hard ? u : v, psi = hard ? v : u;
+    const double2 t1 = cmul(dphi, phi), t2 = cmul(dpsi, psi);
+    r_out[o] = make_double2(-(s[0] + t1.x + t2.x), -(s[1] + t1.y + t2.y));
   }
 }
 
@@ -743,7 +782,7 @@ bem_status launch_residual(bem_ctx* ctx, const bem_surface* s, int n_k, const do
     if (n_sel <= 0) return BEM_OK;
     if (n_sel > 65535 * kKcResidual)
       return fail(ctx, BEM_EUNSUPPORTED, "residual: %d selected wavenumbers in one call", n_sel);
-    dim3 grid(s->n, (n_sel + kKcResidual - 1) / kKcResidual);
+    dim3 grid((s->n + kResRows - 1) / kResRows, (n_sel + kKcResidual - 1) / kKcResidual);
     for (int rh = 0; rh < n_rhs; ++rh) {
       const int pi = prof_begin(ctx, "residual");
       hipLaunchKernelGGL(residual_kc_kernel, grid, dim3(kThreads), 0, ctx->stream, s->n, s->x,
@@ -759,7 +798,7 @@ bem_status launch_residual(bem_ctx* ctx, const bem_surface* s, int n_k, const do
   const int kmax = 65535 * kKcResidual;
   for (int k0 = 0; k0 < n_k; k0 += kmax) {
     const int nk = std::min(kmax, n_k - k0);
-    dim3 grid(s->n, (nk + kKcResidual - 1) / kKcResidual);
+    dim3 grid((s->n + kResRows - 1) / kResRows, (nk + kKcResidual - 1) / kKcResidual);
     const int64_t off = (int64_t)k0 * n_rhs * s->n;
     for (int rh = 0; rh < n_rhs; ++rh) {
       const int pi = prof_begin(ctx, "residual");
