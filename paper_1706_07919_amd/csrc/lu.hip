@@ -1765,10 +1765,15 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
 
 // ============================================================== GEMM f64
 // Same contraction in float64 on MFMA 16x16x4 f64: one MFMA covers two
-// complex k (four interleaved real k).  64 x 64 tile, 4 waves of 32 x 32.
+// complex k (four interleaved real k).  64 x 64 tile, 4 waves of 32 x 32.  The launch
+// bound of two waves per SIMD keeps the accumulators out of the accumulation
+// registers, into and out of which the compiler otherwise copied them at every step:
+// 16 updates of 1028 x 1028 x 256 took 878 us (39 TFLOP/s), now 760 (46).  (Measured
+// without gain: runs of tiles per XCD, LDS planes free of bank conflicts, unmasked
+// loads.)
 constexpr int G64_BM = 64, G64_BN = 64, G64_BK = 8;
 
-__global__ __launch_bounds__(256) void gemm_c64_kernel(LuGroups G, int rowC, int colC, int colA,
+__global__ __launch_bounds__(256, 2) void gemm_c64_kernel(LuGroups G, int rowC, int colC, int colA,
                                                        int rowB, int rowEnd, int colEnd, int K,
                                                        int tiles_n) {
   __shared__ double As[2][G64_BK][2 * G64_BM + 4];

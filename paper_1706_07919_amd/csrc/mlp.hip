@@ -22,13 +22,15 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // own part of the depth, straight from global memory (operands of 32 k in
 // registers while the next 32 are in flight, no barrier in the loop), and the
 // partial tiles are summed through LDS at the end: about 80 us for that product,
-// 2.86 to 0.37 ms for the training step of 5124 nodes at batch 256.  MFMA s of an 8-k group takes
+// 2.86 to 0.36 ms for the training step of 5124 nodes at batch 256 (0.37 without the
+// launch bound of the 64 x 64 tiles, which keeps accumulators from being copied to
+// the accumulation registers and back).  MFMA s of an 8-k group takes
 // k = 4 h + s (h the lane half), so an operand with contiguous k is read as
 // 16-byte words (VA, VB: alignment checked on the host).
 constexpr int kGemmK = 32;   // depth held in registers
 
 template <bool TA, bool TB, int EPI, int T, bool VA, bool VB>
-__global__ __launch_bounds__(T == 1 ? 1024 : 256) void gemm_r32_kernel(
+__global__ __launch_bounds__(T == 1 ? 1024 : 256, T == 1 ? 1 : 2) void gemm_r32_kernel(
     int M, int N, int K, int kpart, const float* __restrict__ A, int lda,
     const float* __restrict__ B, int ldb, const float* __restrict__ bias, float* __restrict__ C,
     int ldc, float* __restrict__ Y) {
