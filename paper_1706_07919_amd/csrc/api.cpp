@@ -134,39 +134,66 @@ bool surface_ok(bem_ctx* ctx, const bem_surface* s, bem_status* st) {
   return true;
 }
 
-// Host-side checks of the surface data (normals unit, weights > 0, finite
-// coordinates, flags in {0,1}); copies n*7 doubles to the host.
-bem_status check_surface_values(bem_ctx* ctx, const bem_surface* s) {
-  const int n = s->n;
-  std::vector<double> x(3 * n), nr(3 * n), w(n);
-  std::vector<uint8_t> bc(n);
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(x.data(), s->x, 24 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(nr.data(), s->nrm, 24 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(w.data(), s->w, 8 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(bc.data(), s->bc, (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
+// Host copies of a call's wavenumbers and surface data for its checks, through the
+// context's pinned buffer: one wait for all of them (copies into pageable memory
+// waited one by one, 6 of them in a solve).
+struct HostInputs {
+  const double *k, *x, *nr, *w;
+  const uint8_t* bc;
+};
+
+bem_status fetch_inputs(bem_ctx* ctx, const bem_surface* s, int n_k, const double* k,
+                        HostInputs& h) {
+  if (n_k <= 0 || !k) return fail(ctx, BEM_EINVAL, "n_k must be > 0 and k non-NULL");
+  const size_t n = s ? s->n : 0;
+  void* p = nullptr;
+  bem_status st = pinned(ctx, 8 * ((size_t)n_k + 7 * n) + n, &p);
+  if (st != BEM_OK) return st;
+  double* d = (double*)p;
+  auto copy = [&](const double*& to, const double* from, size_t count) {
+    to = d;
+    d += count;
+    return hipMemcpyAsync((void*)to, from, 8 * count, hipMemcpyDeviceToHost, ctx->stream);
+  };
+  BEM_HIP_TRY(ctx, copy(h.k, k, n_k));
+  if (s) {
+    BEM_HIP_TRY(ctx, copy(h.x, s->x, 3 * n));
+    BEM_HIP_TRY(ctx, copy(h.nr, s->nrm, 3 * n));
+    BEM_HIP_TRY(ctx, copy(h.w, s->w, n));
+    h.bc = (const uint8_t*)d;
+    BEM_HIP_TRY(ctx, hipMemcpyAsync(d, s->bc, n, hipMemcpyDeviceToHost, ctx->stream));
+  }
   BEM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  return BEM_OK;
+}
+
+// Normals unit, weights > 0, finite coordinates, flags in {0,1}.
+bem_status check_surface_values(bem_ctx* ctx, const HostInputs& h, int n) {
   for (int i = 0; i < n; ++i) {
-    const double l = nr[3 * i] * nr[3 * i] + nr[3 * i + 1] * nr[3 * i + 1] + nr[3 * i + 2] * nr[3 * i + 2];
+    const double l = h.nr[3 * i] * h.nr[3 * i] + h.nr[3 * i + 1] * h.nr[3 * i + 1] +
+                     h.nr[3 * i + 2] * h.nr[3 * i + 2];
     if (!(std::fabs(std::sqrt(l) - 1.0) <= 1e-12))
       return fail(ctx, BEM_EINVAL, "surface: normal %d is not a unit vector", i);
-    if (!(w[i] > 0.0) || !std::isfinite(w[i]))
+    if (!(h.w[i] > 0.0) || !std::isfinite(h.w[i]))
       return fail(ctx, BEM_EINVAL, "surface: weight %d is not positive and finite", i);
-    if (!std::isfinite(x[3 * i]) || !std::isfinite(x[3 * i + 1]) || !std::isfinite(x[3 * i + 2]))
+    if (!std::isfinite(h.x[3 * i]) || !std::isfinite(h.x[3 * i + 1]) || !std::isfinite(h.x[3 * i + 2]))
       return fail(ctx, BEM_EINVAL, "surface: node %d has a non-finite coordinate", i);
-    if (bc[i] > 1) return fail(ctx, BEM_EINVAL, "surface: bc[%d] = %d not in {0,1}", i, bc[i]);
+    if (h.bc[i] > 1) return fail(ctx, BEM_EINVAL, "surface: bc[%d] = %d not in {0,1}", i, h.bc[i]);
   }
   return BEM_OK;
 }
 
-bem_status check_k(bem_ctx* ctx, int n_k, const double* k) {
-  if (n_k <= 0 || !k) return fail(ctx, BEM_EINVAL, "n_k must be > 0 and k non-NULL");
-  std::vector<double> h(n_k);
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(h.data(), k, 8 * (size_t)n_k, hipMemcpyDeviceToHost, ctx->stream));
-  BEM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+bem_status check_k_values(bem_ctx* ctx, const HostInputs& h, int n_k) {
   for (int i = 0; i < n_k; ++i)
-    if (!(h[i] > 0.0) || !std::isfinite(h[i]))
-      return fail(ctx, BEM_EINVAL, "k[%d] = %g must be positive and finite", i, h[i]);
+    if (!(h.k[i] > 0.0) || !std::isfinite(h.k[i]))
+      return fail(ctx, BEM_EINVAL, "k[%d] = %g must be positive and finite", i, h.k[i]);
   return BEM_OK;
+}
+
+bem_status check_k(bem_ctx* ctx, int n_k, const double* k) {
+  HostInputs h{};
+  const bem_status st = fetch_inputs(ctx, nullptr, n_k, k, h);
+  return st != BEM_OK ? st : check_k_values(ctx, h, n_k);
 }
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
@@ -212,7 +239,6 @@ Chunk carve(void* base, int n, int64_t ld, int nr, int kc, bool c128, size_t* us
   c.A = take((size_t)kc * n * ld * (c128 ? 16 : 8));
   c.piv = (int32_t*)take((size_t)kc * n * 4);
   c.perm = (int32_t*)take((size_t)kc * n * 4);
-  c.info = (int32_t*)take((size_t)kc * 4);
   c.diag = (double2*)take((size_t)kc * n * 32);
   c.b = (double2*)take(v * 16);
   c.x = (double2*)take(v * 16);
@@ -220,9 +246,11 @@ Chunk carve(void* base, int n, int64_t ld, int nr, int kc, bool c128, size_t* us
   c.r32 = (float2*)take(v * 8);
   c.d32 = (float2*)take(v * 8);
   c.scale = (double*)take((size_t)kc * nr * 8);
+  // (read back together: dn2 .. info)
   c.dn2 = (double*)take((size_t)kc * nr * 8);
   c.xn2 = (double*)take((size_t)kc * nr * 8);
   c.rn2 = (double*)take((size_t)kc * nr * 8);
+  c.info = (int32_t*)take((size_t)kc * 4);
   c.active = (uint8_t*)take((size_t)kc * nr);
   c.rparts = c128 ? nullptr : take(residual_parts_bytes(n, kc, nr));
   if (used) *used = (size_t)(p - (char*)base);
@@ -352,8 +380,10 @@ extern "C" bem_status bem_assemble(bem_ctx* ctx, const bem_surface* s, int32_t n
       (prec != BEM_C64 && prec != BEM_C128))
     return fail(ctx, BEM_EINVAL, "bem_assemble: bad argument (n_k, k, n_rhs, y, b, A, ld, prec)");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
-  if ((st = check_surface_values(ctx, s)) != BEM_OK) return st;
-  if ((st = check_k(ctx, n_k, k)) != BEM_OK) return st;
+  HostInputs in{};
+  if ((st = fetch_inputs(ctx, s, n_k, k, in)) != BEM_OK) return st;
+  if ((st = check_surface_values(ctx, in, s->n)) != BEM_OK) return st;
+  if ((st = check_k_values(ctx, in, n_k)) != BEM_OK) return st;
   return launch_assemble(ctx, s, n_k, k, n_rhs, y, prec, A, ld, (int64_t)s->n * ld, b, diag64);
 }
 
@@ -604,39 +634,45 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
   if ((st = lu_perm(ctx, n, kc, c.piv, c.perm)) != BEM_OK) return st;
   if ((st = fill_zero(ctx, c.x, (size_t)nv * n * 16)) != BEM_OK) return st;
   if ((st = launch_norm2(ctx, nv, n, c.b, c.rn2)) != BEM_OK) return st;   // r_0 = b
+  // host image of dn2, xn2, rn2 and info, copied as one range
   void* hp = nullptr;
-  if ((st = pinned(ctx, (size_t)nv * 24 + (size_t)kc * 4 + 2 * (size_t)nv, &hp)) != BEM_OK) return st;
-  double* h_dn = (double*)hp;
-  double* h_xn = h_dn + nv;
-  double* h_rn = h_xn + nv;
-  int32_t* h_info = (int32_t*)(h_rn + nv);
+  const size_t back = (size_t)((char*)c.info - (char*)c.dn2) + (size_t)kc * 4;
+  if ((st = pinned(ctx, back + 2 * (size_t)nv, &hp)) != BEM_OK) return st;
+  const double* h_dn = (const double*)hp;
+  const double* h_xn = h_dn + (c.xn2 - c.dn2);
+  const double* h_rn = h_dn + (c.rn2 - c.dn2);
+  const int32_t* h_info = (const int32_t*)((char*)hp + ((char*)c.info - (char*)c.dn2));
   // two staging slots for the flags: the upload before the correction solve
   // (h_act) completes at the synchronisation that follows it; the upload
   // before the update (h_act2) is only known to be done at the next sweep's
   // synchronisation, so the next sweep's first upload must not reuse its slot
-  uint8_t* h_act = (uint8_t*)(h_info + kc);
+  uint8_t* h_act = (uint8_t*)hp + back;
   uint8_t* h_act2 = h_act + nv;
   // act: takes another sweep; fin: stops once the current correction is applied;
   // fresh: the float64 residual of the current x has been evaluated
   std::vector<uint8_t> act(nv, 1), fin(nv, 0), fresh(nv, 1);
   std::vector<double> step(nv, 1.0), bn(nv, 0.0), dprev(nv, 0.0);
   std::vector<int> iters(nv, 0);
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(h_info, c.info, 4 * kc, hipMemcpyDeviceToHost, ctx->stream));
+  // the kernels' flags (none while every item is active), through slot h
+  const uint8_t* active = nullptr;
+  auto upload = [&](uint8_t* h) -> bem_status {
+    active = std::find(act.begin(), act.end(), 0) == act.end() ? nullptr : c.active;
+    if (!active) return BEM_OK;
+    std::memcpy(h, act.data(), nv);
+    BEM_HIP_TRY(ctx, hipMemcpyAsync(c.active, h, nv, hipMemcpyHostToDevice, ctx->stream));
+    return BEM_OK;
+  };
   const double2* rsrc = c.b;
   const int max_it = std::max(1, R.o->max_iter);
   for (int it = 0; it < max_it; ++it) {
-    std::memcpy(h_act, act.data(), nv);
-    BEM_HIP_TRY(ctx, hipMemcpyAsync(c.active, h_act, nv, hipMemcpyHostToDevice, ctx->stream));
+    if ((st = upload(h_act)) != BEM_OK) return st;
     if ((st = launch_ir_scale(ctx, nv, n, rsrc, c.r32, c.scale)) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, (int64_t)n * ld, kc, c.A, c.perm, nr, c.r32,
                             c.d32, (int64_t)nr * n)) != BEM_OK)
       return st;
-    if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, c.active, c.x, c.dn2, c.xn2, 0)) != BEM_OK)
+    if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, active, c.x, c.dn2, c.xn2, 0)) != BEM_OK)
       return st;
-    BEM_HIP_TRY(ctx, hipMemcpyAsync(h_dn, c.dn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
-    BEM_HIP_TRY(ctx, hipMemcpyAsync(h_xn, c.xn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
-    if (it == 0)
-      BEM_HIP_TRY(ctx, hipMemcpyAsync(h_rn, c.rn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
+    BEM_HIP_TRY(ctx, hipMemcpyAsync(hp, c.dn2, back, hipMemcpyDeviceToHost, ctx->stream));
     BEM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     int more = 0, nfin = 0;
     for (int v = 0; v < nv; ++v) {
@@ -665,9 +701,8 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
     }
     if (more + nfin == 0) break;
     // take the corrections, then the residual of the new iterates
-    std::memcpy(h_act2, act.data(), nv);
-    BEM_HIP_TRY(ctx, hipMemcpyAsync(c.active, h_act2, nv, hipMemcpyHostToDevice, ctx->stream));
-    if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, c.active, c.x, c.dn2, c.xn2, 1)) != BEM_OK)
+    if ((st = upload(h_act2)) != BEM_OK) return st;
+    if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, active, c.x, c.dn2, c.xn2, 1)) != BEM_OK)
       return st;
     for (int v = 0; v < nv; ++v)
       if (act[v]) fresh[v] = 0;
@@ -692,7 +727,7 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
     if ((st = launch_norm2(ctx, nv, n, c.r, c.rn2)) != BEM_OK) return st;
   }
   // c.rn2 now holds |b - A x|^2 of every item's returned x
-  BEM_HIP_TRY(ctx, hipMemcpyAsync(h_rn, c.rn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
+  BEM_HIP_TRY(ctx, hipMemcpyAsync(hp, c.dn2, back, hipMemcpyDeviceToHost, ctx->stream));
   double2* xo = R.xout + (size_t)k0 * nr * n;
   BEM_HIP_TRY(ctx, hipMemcpyAsync(xo, c.x, (size_t)nv * n * 16, hipMemcpyDeviceToDevice, ctx->stream));
   BEM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -734,19 +769,20 @@ extern "C" bem_status bem_solve_batched(bem_ctx* ctx, const bem_problem* probs, 
     return fail(ctx, BEM_EINVAL, "bem_solve_batched: bad options");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
   bem_status st;
+  std::vector<std::vector<double>> hk(n_probs);   // the wavenumbers, host copies
   for (int p = 0; p < n_probs; ++p) {
     const bem_problem& P = probs[p];
     if (!surface_ok(ctx, P.s, &st)) return st;
     if (P.n_rhs <= 0 || !P.y || !x_out[p]) return fail(ctx, BEM_EINVAL, "problem %d: n_rhs, y or x_out", p);
-    if ((st = check_k(ctx, P.n_k, P.k)) != BEM_OK) return st;
-    if ((st = check_surface_values(ctx, P.s)) != BEM_OK) return st;
+    HostInputs in{};
+    if ((st = fetch_inputs(ctx, P.s, P.n_k, P.k, in)) != BEM_OK) return st;
+    if ((st = check_k_values(ctx, in, P.n_k)) != BEM_OK) return st;
+    if ((st = check_surface_values(ctx, in, P.s->n)) != BEM_OK) return st;
+    hk[p].assign(in.k, in.k + P.n_k);
     if (P.s->n > 12288) return fail(ctx, BEM_EUNSUPPORTED, "problem %d: n = %d > 12288", p, P.s->n);
   }
   const bool fp64 = o.mode == BEM_FP64_DIRECT;
   const bem_prec prec = fp64 ? BEM_C128 : BEM_C64;
-  size_t free_b = 0, total_b = 0;
-  BEM_HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
-  const size_t limit = ctx->ws_limit ? ctx->ws_limit : (size_t)(0.75 * (double)(free_b + ctx->ws_size));
   std::vector<int64_t> ld(n_probs);
   std::vector<size_t> info_off(n_probs, 0);
   size_t fallback_bytes = 0;
@@ -767,6 +803,13 @@ extern "C" bem_status bem_solve_batched(bem_ctx* ctx, const bem_problem* probs, 
     }
     return s;
   };
+  // (the free memory is asked for only where the limit it gives could bind)
+  size_t limit = ctx->ws_limit ? ctx->ws_limit : (size_t)(0.75 * (double)ctx->ws_size);
+  if (!ctx->ws_limit && round_bytes(1) > limit) {
+    size_t free_b = 0, total_b = 0;
+    BEM_HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
+    limit = (size_t)(0.75 * (double)(free_b + ctx->ws_size));
+  }
   int rounds = 1;
   while (rounds < max_nk && round_bytes(rounds) > limit) rounds = std::min(max_nk, rounds * 2);
   void* ws = nullptr;
@@ -779,12 +822,9 @@ extern "C" bem_status bem_solve_batched(bem_ctx* ctx, const bem_problem* probs, 
   }
   std::vector<SolveRun> runs;
   for (int p = 0; p < n_probs; ++p) {
-    runs.push_back(SolveRun{ctx, &probs[p], &o, (double2*)x_out[p], info ? info + info_off[p] : nullptr, {}});
-    runs.back().hk.resize(probs[p].n_k);
-    BEM_HIP_TRY(ctx, hipMemcpyAsync(runs.back().hk.data(), probs[p].k, 8 * (size_t)probs[p].n_k,
-                                    hipMemcpyDeviceToHost, ctx->stream));
+    runs.push_back(SolveRun{ctx, &probs[p], &o, (double2*)x_out[p], info ? info + info_off[p] : nullptr,
+                            std::move(hk[p])});
   }
-  BEM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
 
   for (int r = 0; r < rounds; ++r) {
     struct Slice { int p, k0, kc; Chunk c; };
@@ -1341,8 +1381,10 @@ extern "C" bem_status bem_solve_chief(bem_ctx* ctx, const bem_surface* s, int32_
     return fail(ctx, BEM_EINVAL, "bem_solve_chief: bad argument");
   if (s->n > 12288) return fail(ctx, BEM_EUNSUPPORTED, "bem_solve_chief: n = %d > 12288", s->n);
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
-  if ((st = check_surface_values(ctx, s)) != BEM_OK) return st;
-  if ((st = check_k(ctx, n_k, k)) != BEM_OK) return st;
+  HostInputs in{};
+  if ((st = fetch_inputs(ctx, s, n_k, k, in)) != BEM_OK) return st;
+  if ((st = check_surface_values(ctx, in, s->n)) != BEM_OK) return st;
+  if ((st = check_k_values(ctx, in, n_k)) != BEM_OK) return st;
   const int n = s->n, nr = n_rhs, naug = n + nr;
   const int64_t ld = round_up(naug, 16);
   const int64_t sa = (int64_t)n * ld, sc = (int64_t)n_c * ld, sm = (int64_t)naug * ld;
