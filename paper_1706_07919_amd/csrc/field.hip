@@ -14,7 +14,7 @@
 // generated kernel value (w G, w H for one node, point and frequency) to all
 // of them, so NR right-hand sides cost one kernel generation and NR complex
 // multiply-adds per term instead of NR generations.  The float32 kernel takes every phase k*r and k*s
-// in float64, reduce it to [-1/2, 1/2) revolutions, and evaluate the
+// in float64, reduces it to [-1/2, 1/2) revolutions, and evaluates the
 // trigonometric functions in float32 on the reduced argument.  Each point's
 // sweep is split over kParts lanes (lane q takes every kParts-th node), whose
 // partial sums are combined by a butterfly at the end: the float32 sums then

@@ -56,3 +56,31 @@ def test_getrs_blocks(ctx, prec, n, pad, n_rhs):
             # 2 gamma_n |L||U||x|, gamma_n = n u up to a small factor for complex products
             bound = 4 * (n + 4) * u * (np.abs(L) @ (np.abs(U) @ np.abs(x)))
             assert np.all(np.abs(L @ (U @ x) - rhs) <= bound)
+
+
+@pytest.mark.parametrize("prec", [native.BEM_C64, native.BEM_C128])
+@pytest.mark.parametrize("n,pad", [(321, 0), (322, 1), (449, 1)])
+def test_getrs_many_matrices(ctx, prec, n, pad):
+    """As many matrices as fill the chip, one right-hand side each."""
+    rng = np.random.default_rng(n)
+    batch, ld = 330, n + pad
+    dt = torch.complex128 if prec == native.BEM_C128 else torch.complex64
+    A = torch.zeros((batch, n, ld), dtype=dt, device="cuda")
+    A[:, :, :n] = torch.as_tensor(seeded_complex(rng, (batch, n, n))).to(dt).cuda()
+    piv = torch.zeros((batch, n), dtype=torch.int32, device="cuda")
+    info = torch.ones(batch, dtype=torch.int32, device="cuda")
+    native.bem_getrf_batched(ctx, prec, n, ld, n * ld, batch, A, piv, info, 0, native.BEM_GEMM_4M)
+    B = torch.as_tensor(seeded_complex(rng, (batch, 1, n))).to(dt)
+    X = torch.zeros((batch, 1, n), dtype=dt, device="cuda")
+    native.bem_getrs_batched(ctx, prec, n, ld, n * ld, batch, A, piv, 1, B.cuda(), X, n)
+    X, B, piv = X.cpu().numpy().astype(np.complex128), B.numpy().astype(np.complex128), piv.cpu().numpy()
+    u = 2.0 ** (-53 if prec == native.BEM_C128 else -24)
+    for b in (0, 1, 255, 256, 257, 329):
+        LU = A[b, :, :n].cpu().numpy().astype(np.complex128)
+        L, U = np.tril(LU, -1) + np.eye(n), np.triu(LU)
+        perm = np.arange(n)
+        for i in range(n):
+            perm[[i, piv[b, i]]] = perm[[piv[b, i], i]]
+        x = X[b, 0]
+        bound = 4 * (n + 4) * u * (np.abs(L) @ (np.abs(U) @ np.abs(x)))   # as above
+        assert np.all(np.abs(L @ (U @ x) - B[b, 0][perm]) <= bound)
