@@ -463,7 +463,8 @@ extern "C" bem_status bem_getrf_batched(bem_ctx* ctx, bem_prec prec, int32_t n, 
       gemm_kind > BEM_GEMM_BF16X3_UNPACKED)
     return fail(ctx, BEM_EINVAL, "bem_getrf_batched: bad argument");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
-  const LuPlan plan = lu_plan_for(ctx, prec, prec == BEM_C64 ? gemm_kind : 0, n, nb);
+  const LuPlan plan = lu_plan_for(ctx, prec, prec == BEM_C64 ? gemm_kind : 0, n, nb,
+                                  (int64_t)n * n * batch);
   return lu_factor(ctx, prec, n, ld, stride, batch, A, piv, info, plan, gemm_kind);
 }
 
@@ -603,7 +604,8 @@ bem_status solve_fp64_chunk(SolveRun& R, const Chunk& c, int k0, int kc, int64_t
   bem_status st;
   if ((st = chunk_assemble(R, c, k0, kc, ld, BEM_C128)) != BEM_OK) return st;
   LuPlan plan;
-  plan.nb = R.o->nb > 0 ? R.o->nb : lu_plan_nb(R.ctx, BEM_C128, 0, R.pr->s->n);
+  plan.nb = R.o->nb > 0 ? R.o->nb : lu_plan_nb(R.ctx, BEM_C128, 0, R.pr->s->n,
+                                                    (int64_t)R.pr->s->n * R.pr->s->n * kc);
   std::vector<LuMatrixSet> sets(1, chunk_set(R, c, kc, ld));
   if ((st = lu_factor_groups(R.ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
   return chunk_finish_fp64(R, c, k0, kc, ld);
@@ -818,7 +820,10 @@ extern "C" bem_status bem_solve_batched(bem_ctx* ctx, const bem_problem* probs, 
   {
     const int gk0 = o.mode == BEM_FP32_IR_3M ? BEM_GEMM_3M
                     : o.mode == BEM_FP32_IR_B3 ? BEM_GEMM_BF16X3 : BEM_GEMM_4M;
-    plan = lu_plan_for(ctx, prec, fp64 ? 0 : gk0, nmax, o.nb);
+    int64_t entries = 0;   // of a round
+    for (int p = 0; p < n_probs; ++p)
+      entries += (int64_t)probs[p].s->n * probs[p].s->n * ((probs[p].n_k + rounds - 1) / rounds);
+    plan = lu_plan_for(ctx, prec, fp64 ? 0 : gk0, nmax, o.nb, entries);
   }
   std::vector<SolveRun> runs;
   for (int p = 0; p < n_probs; ++p) {
@@ -1259,7 +1264,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
       if (chunk_fp64) {
         BEM_HIP_TRY(ctx, hipMemcpyAsync(c.LU, c.A64, (size_t)cur * stride * 16,
                                         hipMemcpyDeviceToDevice, ctx->stream));
-        plan.nb = o.nb > 0 ? o.nb : lu_plan_nb(ctx, BEM_C128, 0, n);
+        plan.nb = o.nb > 0 ? o.nb : lu_plan_nb(ctx, BEM_C128, 0, n, (int64_t)n * n * cur);
         if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
         if ((st = lu_perm(ctx, n, cur, c.piv, c.perm)) != BEM_OK) return st;
         if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, stride, cur, c.LU, c.perm, nr, c.b, c.x,
@@ -1267,7 +1272,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
           return st;
       } else {
         if ((st = launch_c128_to_c64(ctx, (int64_t)cur * stride, c.A64, c.LU)) != BEM_OK) return st;
-        plan = lu_plan_for(ctx, BEM_C64, gk, n, o.nb);
+        plan = lu_plan_for(ctx, BEM_C64, gk, n, o.nb, (int64_t)n * n * cur);
         if ((st = lu_factor_groups(ctx, BEM_C64, sets, plan, gk)) != BEM_OK) return st;
         if ((st = lu_perm(ctx, n, cur, c.piv, c.perm)) != BEM_OK) return st;
         if ((st = fill_zero(ctx, c.x, (size_t)nv * n * 16)) != BEM_OK) return st;
@@ -1441,7 +1446,7 @@ extern "C" bem_status bem_solve_chief(bem_ctx* ctx, const bem_surface* s, int32_
     if ((st = launch_extract_rhs(ctx, n, cur, nr, P[2], ld, sm, P[7])) != BEM_OK) return st;
     std::vector<LuMatrixSet> sets(1, LuMatrixSet{P[2], (int32_t*)P[3], (int32_t*)P[5], ld, sm, n, cur});
     LuPlan plan;
-    plan.nb = lu_plan_nb(ctx, BEM_C128, 0, n);
+    plan.nb = lu_plan_nb(ctx, BEM_C128, 0, n, (int64_t)n * n * cur);
     if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
     if ((st = lu_perm(ctx, n, cur, (const int32_t*)P[3], (int32_t*)P[4])) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, sm, cur, P[2], (const int32_t*)P[4], nr, P[7],

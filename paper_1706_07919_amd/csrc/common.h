@@ -157,14 +157,14 @@ void drop_graphs(bem_ctx* ctx);
 // Solve A_b X = B_b in place for B_b = B + b*bstride (n_rhs vectors of length n, stride n).
 bem_status lu_solve(bem_ctx*, bem_prec, int n, int64_t ld, int64_t stride, int batch,
                     const void* LU, const int32_t* piv, int n_rhs, void* B, int64_t bstride);
-int lu_default_nb(bem_prec prec, int n);
 // block width for a factorisation: the measured one of this context when
-// bem_autotune_lu has run for the size class, else the default
-int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n);
+// bem_autotune_lu has run for the size class, else the default for the largest n
+// and the entries (n^2, summed) of the matrices factored together
+int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int64_t entries);
 // a factorisation's plan: block width nb (> 0) or the measured / default one,
 // and the measured GEMM tile threshold and launch form when the context has
 // them for this size class
-LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb);
+LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb, int64_t entries);
 bem_status lu_autotune(bem_ctx* ctx, bem_prec prec, int n, int batch, int gemm_kind,
                        const int32_t* candidates, int32_t* best_nb, double* best_ms);
 

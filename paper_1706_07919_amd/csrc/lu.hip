@@ -2287,21 +2287,26 @@ struct Fac {
 
 }  // namespace
 
-int lu_default_nb(bem_prec prec, int n) {
-  (void)prec;
-  // wide blocks cut the trailing-update traffic of large matrices (measured:
-  // 512 beats 256 by 5 % at n = 5124 in a batch of 512)
+static int lu_default_nb(int n, int64_t entries) {
+  // few matrix entries in all: the chain through the launches of a block counts,
+  // and narrow blocks shorten it (64 against 256 columns: 8 matrices of n = 642 take
+  // 1.65 against 2.12 ms, 8 of 1284 in float64 6.0 against 6.9; 128 against 256: 32 of
+  // 1284 6.5 against 6.7 ms, 8 of 2562 13.1 against 13.6).  With more the trailing
+  // updates do, which wide blocks run deeper and with less traffic (512 of 1284: 57,
+  // 50 and 45 ms with 64, 128 and 256; 64 of 5124: 177 and 167 ms with 256 and 512).
+  if (n < 4096 && entries < 24 * 1024 * 1024) return kSwapRows / 4;
+  if (n < 4096 && entries < 80 * 1024 * 1024) return kSwapRows / 2;
   return n >= 4096 ? 2 * kSwapRows : kSwapRows;
 }
 
-int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n) {
+int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int64_t entries) {
   const auto it = ctx->tuned.find({(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512});
-  return it != ctx->tuned.end() ? it->second.nb : lu_default_nb(prec, n);
+  return it != ctx->tuned.end() ? it->second.nb : lu_default_nb(n, entries);
 }
 
-LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb) {
+LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb, int64_t entries) {
   LuPlan plan;
-  plan.nb = nb > 0 ? nb : lu_plan_nb(ctx, prec, gemm_kind, n);
+  plan.nb = nb > 0 ? nb : lu_plan_nb(ctx, prec, gemm_kind, n, entries);
   const auto it = ctx->tuned.find({(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512});
   if (it != ctx->tuned.end()) {
     plan.gemm_narrow_max = it->second.narrow_max;
