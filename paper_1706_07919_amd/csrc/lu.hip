@@ -386,10 +386,14 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_kernel(LuGroups G, int rowC, 
 //   Im C -= T3 - T1 - T2.
 // Each MFMA 32x32x2 covers two complex k of one product, so a complex k costs
 // 1.5 MFMA per 32x32 block instead of 2 (4M).  The operand sums are formed
-// once while staging the tiles in LDS.
+// once while staging the tiles in LDS.  ex (or NULL): only the matrices whose
+// operands cannot be split (split_wide).
+__device__ inline bool split_wide(const int32_t* counts, int K);
 __global__ __launch_bounds__(256) void gemm_c32_3m_kernel(LuGroups G, int rowC, int colC,
                                                           int colA, int rowB, int rowEnd,
-                                                          int colEnd, int K, int tiles_n) {
+                                                          int colEnd, int K, int tiles_n,
+                                                          const int32_t* __restrict__ ex, int64_t ss) {
+  if (ex && !split_wide(ex + blockIdx.y * ss + ss - 4, K)) return;
   __shared__ float As[2][3][G32_BK][G32_BM + 4];
   __shared__ float Bs[2][3][G32_BK][G32_BN + 4];
   GemmView<float2> gv;
@@ -1265,9 +1269,9 @@ constexpr int GP_BLK = 2 * 2 * GB_BM;   // 16-byte words per tile and 8-k block
 constexpr size_t kPackLimit = (size_t)4 << 30;
 
 // 16-byte words of one matrix's scale exponents (the f16 form): t_k [K],
-// ea [128 tiles_m], eb [128 tiles_n]
+// ea [128 tiles_m], eb [128 tiles_n], and in the last word its range counts
 inline int64_t scale_words(int tiles_m, int tiles_n, int K) {
-  return (4 * ((int64_t)K + GB_BM * tiles_m + GB_BN * tiles_n) + 15) / 16;
+  return (4 * ((int64_t)K + GB_BM * tiles_m + GB_BN * tiles_n) + 15) / 16 + 1;
 }
 // 16-byte words of the packed A and B of one matrix for an M x N update of depth K
 inline int64_t pack_words(int M, int N, int K) {
@@ -1372,12 +1376,14 @@ __global__ __launch_bounds__(256) void pack_b_kernel(LuGroups G, int rowB, int c
 // lo's sign), and x y ~ hi hi + hi lo + lo hi drops only lo lo (2^-22 of the
 // product at most).  MFMA f16 adds sixteen products per rounding of the float32
 // accumulator where MFMA f32 32x32x2 adds two, and there are no sums
-// (a + b)(c + d) - a c - b d to cancel, so the update is closer to the float64
-// product than the float32 3M one: relative error of a 256 x 256 update,
-// Gaussian data, K = 64 / 512 / 1024: 1.4 / 3.6 / 5.0e-7 against 2.1 / 5.8 /
-// 8.1e-7; backward error ||PA - LU|| / ||A|| of Gaussian matrices of n = 1284 and
-// 1600: 1.1e-5 and 1.6e-5 against 1.8e-5 and 2.8e-5.  (The 4M form's is 0.6e-5
-// and 0.8e-5, so it keeps its float32 products.)  24 flops on the 2.5 PFLOP/s unit
+// (a + b)(c + d) - a c - b d to cancel.  Measured against the float32 3M
+// products: boundary-integral systems (two hard spheres of n = 5124 in all, one
+// hard and one mixed of n = 2562), PA - LU against |L||U| entry by entry, rms: 8.06,
+// 7.94 and 8.20e-8 against 9.32, 8.66 and 9.22e-8; Gaussian data, relative error of a
+// 256 x 256 update of K = 64 / 512 / 1024: 1.4 / 3.6 / 5.0e-7 against 2.1 / 5.8 /
+// 8.1e-7, and ||PA - LU|| / ||A|| at n = 1284 and 1600: 1.1e-5 and 1.6e-5 against
+// 1.8e-5 and 2.8e-5.  (The 4M form's is 0.6e-5 and 0.8e-5 there, so it keeps its
+// float32 products.)  24 flops on the 2.5 PFLOP/s unit
 // replace 6 on the 0.157 one: the updates of 64 matrices of n = 5124 take 62 ms
 // and 11 ms of splitting instead of 127 ms.
 //
@@ -1385,10 +1391,21 @@ __global__ __launch_bounds__(256) void pack_b_kernel(LuGroups G, int rowB, int c
 // (exact).  Row k of U is divided by 2^t_k, t_k the exponent of its largest
 // entry, and column k of L multiplied by it; then each row i of L is scaled by
 // 2^(14 - ea_i) and each column j of U by 2^(14 - eb_j), their largest entries
-// in [2^14, 2^15).  Scaling rows or columns of the matrix by powers of two
-// therefore changes no bit of the products, and an entry keeps its full split
-// down to 2^-15 of the largest of its row or column (its error is at most 2^-39
-// of that entry below).  The epilogue takes 2^(ea_i + eb_j - 28) back.
+// in [2^14, 2^15).  The epilogue takes 2^(ea_i + eb_j - 28) back.  A scaled entry
+// of at least 1/2 keeps 22 bits or more; a smaller one has an absolute error of
+// up to 2^-25 (2^-39 of its row's or column's largest), which no scaling cures
+// where a row's large entries meet small ones of a column.  So the packing
+// counts, as maxima over the rows of L and the columns of U of a matrix, the
+// nonzero entries below 1/2 (s) and the entries below 64 (p).  Row i and column j
+// share at least K - p_L - p_U places where both are 64 or more, that is
+// sum_k |l_ik u_kj| >= 2^12 (K - p), and small entries cost at most 2^-9 s.  Where
+// 8 s > K - p that could exceed 2^-24 sum_k |l_ik u_kj|, and the matrix takes this
+// update as float32 products (split_wide; infinities too).  None of the
+// boundary-integral systems measured does (n = 1284 to 10242, hard, soft, mixed: s
+// is 0 to 4 of 128 to 512).  So
+//   |error| <= (3 2^-22 + 2^-24) sum_k |l_ik u_kj|
+// besides the float32 accumulation, the first term from lo's rounding and the
+// dropped lo lo (2^-23.5 rms).
 //
 // Bias: MFMA f16 cuts the products it adds off at the accumulator's last bit
 // towards minus infinity, a mean error of -0.05 of the rms one.  Random errors
@@ -1410,6 +1427,49 @@ __device__ inline int scale_exp(float m) {
 }
 __device__ inline float exp2i(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
 
+// Range counts of a matrix: s of L's rows, s of U's columns, p of each.
+// Whether the update's float32 products cannot be split (above)
+__device__ inline bool split_wide(const int32_t* counts, int K) {
+  const int s = counts[0] + counts[1];
+  return s > 0 && 8 * s > K - counts[2] - counts[3];
+}
+// s (high half) and p of 2 NP scaled values, NP complex entries
+template <int NP>
+__device__ inline int range_count(const float* x) {
+  int c = 0;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const float r = fmaxf(fabsf(x[2 * q]), fabsf(x[2 * q + 1]));
+    c += (r >= 64.f ? 0 : 1) + (r > 0.f && r < 0.5f ? 1 << 16 : 0);
+  }
+  return c;
+}
+// A workgroup's rows (or columns) into the matrix's counts: thread 32 part + r
+// holds part of row r's count, pad of it for depth past K; largest: row r's
+// largest entry before its scaling
+__device__ inline void store_counts(int c, int pad, bool valid, float largest, int (*red)[32],
+                                    int32_t* s_out, int32_t* p_out) {
+  const int r = threadIdx.x & 31, part = threadIdx.x >> 5;
+  red[part][r] = c;
+  __syncthreads();
+  if (part) return;
+  int sum = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) sum += red[q][r];
+  int s = sum >> 16, p = (sum & 0xffff) - pad;
+  if (largest > 3.4028234e38f) s = 1 << 20;   // an infinity
+  if (!valid) s = p = 0;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) {
+    s = max(s, __shfl_xor(s, o, 32));
+    p = max(p, __shfl_xor(p, o, 32));
+  }
+  if (r == 0) {
+    if (s) atomicMax(s_out, s);
+    if (p) atomicMax(p_out, p);
+  }
+}
+
 __device__ inline void split8h(const float* x, uint4& hi, uint4& lo) {
   unsigned hw[4], lw[4];
 #pragma unroll
@@ -1424,8 +1484,8 @@ __device__ inline void split8h(const float* x, uint4& hi, uint4& lo) {
   lo = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
-// t_k of row rowB + k of U over the columns [colC, min(colEnd, n)); one
-// workgroup per row
+// t_k of row rowB + k of U over the columns [colC, min(colEnd, n)), one
+// workgroup per row; clears the range counts
 __global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int colC, int colEnd,
                                                        int64_t ss, int32_t* __restrict__ ex) {
   __shared__ float red[4];
@@ -1447,6 +1507,7 @@ __global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
+  if (k == 0 && threadIdx.x < 4) ex[blockIdx.y * ss + ss - 4 + threadIdx.x] = 0;
   if (threadIdx.x == 0)
     ex[blockIdx.y * ss + k] = scale_exp(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
 }
@@ -1460,6 +1521,7 @@ __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, i
                                                          uint4* __restrict__ out,
                                                          int32_t* __restrict__ ex) {
   __shared__ float red[8][32];
+  __shared__ int cnt[8][32];
   LuGroup grp;
   int b = 0;
   if (!locate(G, blockIdx.y, grp, b)) return;
@@ -1513,11 +1575,13 @@ __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, i
   if (part == 0) ex[blockIdx.y * ss + K + gr] = e;
   const float sc = exp2i(14 - e);
   const int tile = gr / GB_BM, row = gr % GB_BM;
+  int count = 0;
   for (int s8 = part; s8 < S8; s8 += 8) {
     load(s8, x);
     const float sg = (s8 / (kFlipK / 8)) & 1 ? -sc : sc;
 #pragma unroll
     for (int q = 0; q < 16; ++q) x[q] *= sg;
+    count += range_count<8>(x);
     uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + s8) * GP_BLK;
 #pragma unroll
     for (int kg = 0; kg < 2; ++kg) {
@@ -1527,6 +1591,8 @@ __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, i
       o[kg * 2 * GB_BM + GB_BM + row] = lo;
     }
   }
+  int32_t* counts = ex + blockIdx.y * ss + ss - 4;
+  store_counts(count, 8 * S8 - K, gr < M, m, cnt, counts, counts + 2);
 }
 
 // U = rows [rowB, rowB + K) x cols [colC, min(colEnd, n)): 32 columns per
@@ -1537,6 +1603,7 @@ __global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, i
                                                          int64_t ss, uint4* __restrict__ out,
                                                          int32_t* __restrict__ ex) {
   __shared__ float red[8][32];
+  __shared__ int cnt[8][32];
   LuGroup grp;
   int b = 0;
   if (!locate(G, blockIdx.y, grp, b)) return;
@@ -1572,17 +1639,21 @@ __global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, i
   if (part == 0) ex[blockIdx.y * ss + K + GB_BM * tiles_m + gc] = e;
   const float sc = exp2i(14 - e);
   const int tile = gc / GB_BN, col = gc % GB_BN;
+  int count = 0;
 #pragma unroll 2
   for (int g = part; g < 2 * S8; g += 8) {
     load(g, x);
 #pragma unroll
     for (int q = 0; q < 8; ++q) x[q] *= sc;
+    count += range_count<4>(x);
     uint4 hi, lo;
     split8h(x, hi, lo);
     uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + g / 2) * GP_BLK + (g & 1) * 2 * GB_BN;
     o[col] = hi;
     o[GB_BN + col] = lo;
   }
+  int32_t* counts = ex + blockIdx.y * ss + ss - 4;
+  store_counts(count, 8 * S8 - K, gc < N, m, cnt, counts + 1, counts + 3);
 }
 
 // (a, -b) pairs of the real-part pattern -> (b, a) of the imaginary-part
@@ -1630,6 +1701,7 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
   const int tcol = (t % strip) / gsz;
   const int tm = first + (t % strip) % gsz, tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
   const int64_t mat = first_mat + b;
+  if (F16 && split_wide(ex + mat * ss + ss - 4, K)) return;   // (gemm_c32_lds_wide_kernel's)
   const int M = min(rowEnd, n) - rowC, N = min(colEnd, n) - colC;
   const int m0 = tm * GB_BM, n0 = tn * GB_BN;
   const int ld = (int)ld64;   // n * ld < 2^31 is checked on the host
@@ -1761,6 +1833,35 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
         if (row < M) C[row * ld + col] = make_float2(c[v].x - dr, c[v].y - di);
       }
     }
+}
+
+// The float32 products of the matrices whose operands cannot be split, of the
+// work list of gemm_c32_split_kernel: resident workgroups step through it, and
+// leave at once where there is no such matrix (every update of the
+// boundary-integral systems: 5 us for 64 of n = 5124).
+__global__ __launch_bounds__(256, 2) void gemm_c32_lds_wide_kernel(
+    LuGroups G, GemmList W, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd, int K,
+    const int32_t* __restrict__ ex, int64_t ss) {
+  __shared__ u32x4 As[2][GL_BM * GL_BK / 2], Bs[2][GL_BK * 128 / 2];
+  int mats = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxGroups; ++i)
+    if (i < G.ng) mats += G.g[i].count;
+  bool any = false;
+  for (int i = threadIdx.x; i < mats; i += 256) any |= split_wide(ex + i * ss + ss - 4, K);
+  if (!__syncthreads_or(any)) return;
+  const int64_t total = W.start[G.ng], per = (total + 7) >> 3;
+  const int64_t lo = (int64_t)(blockIdx.x & 7) * per, hi = min(total, lo + per);
+  for (int64_t item = lo + (blockIdx.x >> 3); item < hi; item += gridDim.x >> 3) {
+    int64_t mat = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxGroups; ++i)
+      if (i < G.ng && item >= W.start[i])
+        mat += item < W.start[i + 1] ? (item - W.start[i]) / (W.tm[i] * W.tn[i]) : G.g[i].count;
+    if (!split_wide(ex + mat * ss + ss - 4, K)) continue;   // uniform
+    gemm_lds_tile<true, 2>(G, W, item, rowC, colC, colA, rowB, rowEnd, colEnd, K, As, Bs);
+    __syncthreads();   // the tile's LDS reads are done
+  }
 }
 
 // ============================================================== GEMM f64
@@ -2007,21 +2108,26 @@ struct Fac {
     for (int i = G.ng + 1; i <= kMaxGroups; ++i) W.start[i] = W.start[G.ng];
     return W;
   }
-  // float32 3M / 4M update through gemm_c32_lds_kernel; false (nothing
-  // launched) when an operand is not 16-byte aligned (odd ld, column offset or
-  // depth)
-  bool gemm_lds(const LuGroups& G, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd,
-                int K, int N) {
+  // workgroups of the LDS kernels the chip holds (two per CU)
+  int64_t resident_wgs() const { return (int64_t)ctx->num_cus * 2 / 8 * 8; }
+  // operands 16-byte aligned: even ld, column offsets and depth
+  static bool lds_aligned(const LuGroups& G, int colC, int colA, int K) {
     if ((colA | colC | K) & 1) return false;
     for (int i = 0; i < G.ng; ++i)
       if (G.g[i].ld & 1) return false;
+    return true;
+  }
+  // float32 3M / 4M update through gemm_c32_lds_kernel; false (nothing
+  // launched) when an operand is not aligned for it
+  bool gemm_lds(const LuGroups& G, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd,
+                int K, int N) {
+    if (!lds_aligned(G, colC, colA, K)) return false;
     const bool narrow = N <= std::max(64, plan.gemm_narrow_max);
     const GemmList W = work_list(G, rowC, colC, rowEnd, colEnd, narrow ? 64 : 128);
     const int64_t total = W.start[G.ng];
     if (total <= 0) return true;
-    // persistent form: the resident workgroups (two per CU) when the launch
-    // has more tiles than that
-    const int64_t resident = (int64_t)ctx->num_cus * 2 / 8 * 8;
+    // persistent form when the launch has more tiles than that
+    const int64_t resident = resident_wgs();
     const bool persist = plan.gemm_persistent && ctx->gemm_queue && total > resident;
     const int64_t grid = persist ? resident : (total + 7) / 8 * 8;
     uint32_t* queue = persist ? (uint32_t*)ctx->gemm_queue : nullptr;
@@ -2108,7 +2214,8 @@ struct Fac {
       }
       else if (gkind == kGemm3M)
         hipLaunchKernelGGL(gemm_c32_3m_kernel, dim3(tm * tn, total), dim3(256), 0, ctx->stream, G,
-                           rowC, colC, colA, rowB, rowEnd, colEnd, K, tn);
+                           rowC, colC, colA, rowB, rowEnd, colEnd, K, tn, (const int32_t*)nullptr,
+                           (int64_t)0);
       else
         hipLaunchKernelGGL(gemm_c32_kernel, dim3(tm * tn, total), dim3(256), 0, ctx->stream, G,
                            rowC, colC, colA, rowB, rowEnd, colEnd, K, tn);
@@ -2209,10 +2316,16 @@ struct Fac {
       const char* kname = f16 ? "gemm_f16x3" : "gemm_b3_packed";
       pi = prof_begin(ctx, kname);
       const dim3 gd((unsigned)((W.start[Gs.ng] + 7) / 8 * 8)), bd(256);
-      if (f16)
+      if (f16) {
         hipLaunchKernelGGL(gemm_c32_split_kernel<true>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
                            rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
-      else
+        if (lds_aligned(Gs, colC, colA, K))
+          hipLaunchKernelGGL(gemm_c32_lds_wide_kernel, dim3((unsigned)std::min<int64_t>(gd.x, resident_wgs())),
+                             bd, 0, ctx->stream, Gs, W, rowC, colC, colA, rowB, rowEnd, colEnd, K, ex, ss);
+        else
+          hipLaunchKernelGGL(gemm_c32_3m_kernel, dim3(tiles_m * tiles_n, nbat), bd, 0, ctx->stream, Gs,
+                             rowC, colC, colA, rowB, rowEnd, colEnd, K, tiles_n, ex, ss);
+      } else
         hipLaunchKernelGGL(gemm_c32_split_kernel<false>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
                            rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
       prof_end(ctx, kname, pi, 8.0 * mn * K, 8.0 * (mk + kn + 2.0 * mn));

@@ -1,0 +1,61 @@
+"""Float32 3M factorisations whose large updates run as f16 split products, on
+operands a row and column scaling cannot bring into f16's range: the factors stay
+within the float32 error of the products |L||U| entry by entry, and matrices that
+can be split keep their split form beside them."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+native = pytest.importorskip("paper_1706_07919_amd.native")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    c = native.Context(0)
+    yield c
+    c.close()
+
+
+def matrix(rng, n, nb, form):
+    """[[L1], [L2]] [I, U] plus a dominant diagonal in the trailing block: the
+    first block column's factors are L1, L2 and U as given, its update C - L2 U."""
+    def c(*shape):
+        return rng.uniform(-0.5, 0.5, shape) + 1j * rng.uniform(-0.5, 0.5, shape)
+    L1, L2, U = np.tril(c(nb, nb), -1) * 0.1 + np.eye(nb), c(n - nb, nb), c(nb, n - nb)
+    if form == "graded column":        # one column of U sets every row's scale
+        U[:, -1] = 2.0 ** (60.0 - 40.0 * np.arange(nb) / nb)
+    elif form == "entry over zeros":   # a large entry of L that meets zeros
+        L2[:] *= 2.0 ** -32
+        L2[:, 0] = 0.5
+        U[0] = 0.0
+    A = np.zeros((n, n), np.complex128)
+    A[:nb, :nb], A[nb:, :nb], A[:nb, nb:] = L1, L2, L1 @ U
+    A[nb:, nb:] = L2 @ U + np.diag(np.full(n - nb, n, np.float64))
+    return A.astype(np.complex64)
+
+
+@pytest.mark.parametrize("n,nb,pad", [(1152, 128, 0), (1089, 64, 1), (1290, 100, 0)])
+@pytest.mark.parametrize("forms", [("graded column",), ("entry over zeros",),
+                                   ("plain", "graded column", "plain", "entry over zeros")])
+def test_operands_past_the_split_keep_float32(ctx, n, nb, pad, forms):
+    rng = np.random.default_rng(n)
+    M = np.stack([matrix(rng, n, nb, f) for f in forms])
+    batch, ld = len(forms), n + pad
+    A = torch.zeros((batch, n, ld), dtype=torch.complex64)
+    A[:, :, :n] = torch.as_tensor(M)
+    A = A.cuda()
+    piv = torch.zeros((batch, n), dtype=torch.int32, device="cuda")
+    info = torch.ones(batch, dtype=torch.int32, device="cuda")
+    native.bem_getrf_batched(ctx, native.BEM_C64, n, ld, n * ld, batch, A, piv, info, nb, native.BEM_GEMM_3M)
+    assert info.cpu().numpy().tolist() == [0] * batch
+    LU, p = A.cpu().numpy()[:, :, :n].astype(np.complex128), piv.cpu().numpy()
+    for b in range(batch):
+        L, U = np.tril(LU[b], -1) + np.eye(n), np.triu(LU[b])
+        PA = M[b].astype(np.complex128)
+        for i in range(n):
+            PA[[i, p[b, i]]] = PA[[p[b, i], i]]
+        # n roundings of 2^-24, four real products each
+        assert np.all(np.abs(L @ U - PA) <= 4 * n * 2.0 ** -24 * (np.abs(L) @ np.abs(U))), forms[b]
