@@ -424,7 +424,7 @@ __device__ __forceinline__ bool residual_terms(const ResArgs& p, const KChunk<KC
                    dz = p.x[3 * j + 2] - xi[m][2];
       const bool self = j == p.i0 + m;
       double rinv;
-      dist_and_inverse(self ? 1.0 : dx * dx + dy * dy + dz * dz, r[m], rinv);
+      dist_and_inverse64(self ? 1.0 : dx * dx + dy * dy + dz * dz, r[m], rinv);
       wr[m] = self ? 0.0 : wj * rinv;
       wq[m] = wj * ((dx * nx + dy * ny + dz * nz) * (rinv * rinv * rinv));   // (0 for itself)
       if (PH != kPhWide) wide |= !(kmax * r[m] < kPhaseNear);

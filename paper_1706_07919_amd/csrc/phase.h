@@ -45,6 +45,19 @@ __device__ inline void phase_sincos_near(double x, double* s, double* c) {
   *c = ((q + 1) & 2) ? -ca : ca;
 }
 
+// r and 1/r from r^2 > 0 without the library's square root and division: the
+// float64 reciprocal square root estimate (any float64 r^2, where the float32 one
+// ends at distances of 1e-19 and 1e19), two Newton steps, and a correction step for
+// r (it enters the phases, so it is kept to the rounding of a square root).
+__device__ inline void dist_and_inverse64(double r2, double& r, double& rinv) {
+  double y = __builtin_amdgcn_rsq(r2);
+  y *= fma(-0.5 * r2, y * y, 1.5);
+  y *= fma(-0.5 * r2, y * y, 1.5);
+  rinv = y;
+  const double r1 = r2 * y;
+  r = fma(fma(-r1, r1, r2), 0.5 * y, r1);
+}
+
 __device__ inline void phase_sincos(double x, double* s, double* c) {
   if (!(fabs(x) < kPhaseNear)) {
     sincos(x, s, c);
