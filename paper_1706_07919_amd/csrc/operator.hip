@@ -407,11 +407,15 @@ __device__ __forceinline__ bool residual_terms(const ResArgs& p, const KChunk<KC
                                                const int64_t (&base)[KC], double kmax,
                                                double (&acc)[kResRows][2][KC]) {
   bool wide = false;
+  // (a row past the last is the last one again, never stored)
   double xi[kResRows][3];
+  int row[kResRows];
 #pragma unroll
-  for (int m = 0; m < kResRows; ++m)
+  for (int m = 0; m < kResRows; ++m) {
+    row[m] = min(p.i0 + m, p.n - 1);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) xi[m][c] = p.x[3 * min(p.i0 + m, p.n - 1) + c];
+    for (int c = 0; c < 3; ++c) xi[m][c] = p.x[3 * row[m] + c];
+  }
   for (int j = threadIdx.x; j < p.n; j += kThreads) {
     const double nx = p.nrm[3 * j], ny = p.nrm[3 * j + 1], nz = p.nrm[3 * j + 2];
     const double wj = p.w[j];
@@ -422,7 +426,7 @@ __device__ __forceinline__ bool residual_terms(const ResArgs& p, const KChunk<KC
     for (int m = 0; m < kResRows; ++m) {
       const double dx = p.x[3 * j] - xi[m][0], dy = p.x[3 * j + 1] - xi[m][1],
                    dz = p.x[3 * j + 2] - xi[m][2];
-      const bool self = j == p.i0 + m;
+      const bool self = j == row[m];
       double rinv;
       dist_and_inverse64(self ? 1.0 : dx * dx + dy * dy + dz * dz, r[m], rinv);
       wr[m] = self ? 0.0 : wj * rinv;
