@@ -157,8 +157,8 @@ __global__ __launch_bounds__(256) void laswp_kernel(LuGroups G, SwapJobs J) {
 // ============================================================== small TRSM
 // X = L^{-1} B, L = unit lower triangle of rows/cols [r0, r0+m1) (m1 <= M),
 // B = rows [r0, r0+m1) x cols [col0, col1).  The chain of M unknowns bounds it:
-// four neighbouring lanes share a column (lane g holds rows 4k + g), so a step
-// hands one unknown round the quad and updates M/4 rows per lane at most, and
+// four neighbouring lanes share a column (lane g holds rows 4k + g), so four
+// unknowns go round the quad and update M/4 rows per lane at most, and
 // a workgroup of 64 columns spreads over the four SIMDs.  One lane per column and
 // 32 unknowns took 12 us at 162 columns where this takes 7 us, and 64 unknowns (16 us)
 // took two such launches and a product between them.  Wide block rows (64
@@ -175,24 +175,41 @@ __device__ __forceinline__ double quad_value(double v) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-// unknown 4 K0 + Q of every column, out of the rows below it
-template <typename C, int KR, int K0, int Q, typename LM>
-__device__ __forceinline__ void trsm_step(C (&x)[KR], const LM& L, int g) {
-  const C xj = cmk<C>(quad_value<Q>(x[K0].x), quad_value<Q>(x[K0].y));
-  const auto* l = L[4 * K0 + Q][g];
-  if (Q < 3) {   // the rest of its own four rows
-    const C s = cfms(x[K0], l[K0], xj);
-    x[K0].x = g > Q ? s.x : x[K0].x;
-    x[K0].y = g > Q ? s.y : x[K0].y;
-  }
+// Unknowns 4 K0 .. 4 K0 + 3 of every column, out of the rows below them.  Their four
+// products with an entry of L are summed before the sum is subtracted: one
+// rounding of the entry for four unknowns (fused into it, the two multiply-adds of a
+// product round it eight times: |PA - LU| of the hard sphere of n = 2562 is then
+// 9.4e-8 of |L||U|, now 6.1e-8).
+template <typename C, int KR, int K0, typename LM>
+__device__ __forceinline__ void trsm_quad(C (&x)[KR], const LM& L, int g) {
+  using R = decltype(C::x);
+  C xj[4], d = cmk<C>(R(0), R(0));
+  auto add = [](C s, C a, C b) {   // s + a b
+    return cmk<C>(fma(a.x, b.x, fma(-a.y, b.y, s.x)), fma(a.x, b.y, fma(a.y, b.x, s.y)));
+  };
+  auto own = [&](auto q) {   // unknown q, and its product into the later ones of the four
+    constexpr int Q = decltype(q)::value;
+    const C t = g == Q ? csub(x[K0], d) : x[K0];
+    xj[Q] = cmk<C>(quad_value<Q>(t.x), quad_value<Q>(t.y));
+    if (g == Q) x[K0] = t;
+    if (Q < 3) d = add(d, L[4 * K0 + Q][g][K0], xj[Q]);
+  };
+  own(std::integral_constant<int, 0>{});
+  own(std::integral_constant<int, 1>{});
+  own(std::integral_constant<int, 2>{});
+  own(std::integral_constant<int, 3>{});
 #pragma unroll
-  for (int k = K0 + 1; k < KR; ++k) x[k] = cfms(x[k], l[k], xj);
+  for (int k = K0 + 1; k < KR; ++k) {
+    C s = cmk<C>(R(0), R(0));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s = add(s, L[4 * K0 + q][g][k], xj[q]);
+    x[k] = csub(x[k], s);
+  }
 }
 template <typename C, int KR, typename LM, int... K>
-__device__ __forceinline__ void trsm_steps(C (&x)[KR], const LM& L, int g,
+__device__ __forceinline__ void trsm_quads(C (&x)[KR], const LM& L, int g,
                                            std::integer_sequence<int, K...>) {
-  ((trsm_step<C, KR, K, 0>(x, L, g), trsm_step<C, KR, K, 1>(x, L, g),
-    trsm_step<C, KR, K, 2>(x, L, g), trsm_step<C, KR, K, 3>(x, L, g)), ...);
+  (trsm_quad<C, KR, K>(x, L, g), ...);
 }
 
 template <typename C, int M>
@@ -224,7 +241,7 @@ __global__ __launch_bounds__(256) void trsm_kernel(LuGroups G, int r0, int m1_al
     if (j < i) L[j][i & 3][i >> 2] = i < m1 ? v : cmk<C>(0, 0);
   }
   __syncthreads();
-  trsm_steps<C, KR>(x, L, g, std::make_integer_sequence<int, KR>{});
+  trsm_quads<C, KR>(x, L, g, std::make_integer_sequence<int, KR>{});
   if (col >= cend) return;
 #pragma unroll
   for (int k = 0; k < KR; ++k)
