@@ -14,10 +14,13 @@
 namespace bem {
 
 bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* perm);
+// acc: float64 accumulators of the float32 solves, acc_vectors x n (or NULL, 0);
+// more vectors than that are solved in slices
 bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
                          int batch, const void* LU, const int32_t* perm, int n_rhs,
-                         const void* Bin, void* X, int64_t bstride, const int32_t* fac_index = nullptr,
-                         const int32_t* vidx = nullptr, int n_sel = 0);
+                         const void* Bin, void* X, int64_t bstride, double2* acc, int64_t acc_vectors,
+                         const int32_t* fac_index = nullptr, const int32_t* vidx = nullptr,
+                         int n_sel = 0);
 
 bem_status fail(bem_ctx* ctx, bem_status st, const char* fmt, ...) {
   if (ctx) {
@@ -197,6 +200,7 @@ bem_status check_k(bem_ctx* ctx, int n_k, const double* k) {
 }
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
+size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 struct Chunk {
   // device buffers of one chunk of kc wavenumbers (n nodes, nr right-hand sides)
@@ -530,12 +534,21 @@ extern "C" bem_status bem_getrs_batched(bem_ctx* ctx, bem_prec prec, int32_t n, 
       !B || !X || B == X || bstride < (int64_t)n * n_rhs || (prec != BEM_C64 && prec != BEM_C128))
     return fail(ctx, BEM_EINVAL, "bem_getrs_batched: bad argument");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
+  // the permutations, and for float32 the solve's accumulators (slices of at least 512
+  // vectors; none, and float32 sums, where they cannot be allocated)
+  const size_t perm = align256(sizeof(int32_t) * (size_t)n * batch);
+  int64_t vectors = prec == BEM_C64 ? std::min<int64_t>((int64_t)batch * n_rhs,
+                                                        std::max<int64_t>(512, (16 << 20) / n)) : 0;
   void* ws = nullptr;
-  bem_status st = workspace(ctx, sizeof(int32_t) * (size_t)n * batch, &ws);
+  bem_status st = workspace(ctx, perm + 16 * (size_t)(vectors * n), &ws);
+  if (st == BEM_ENOMEM && vectors > 0) {
+    vectors = 0;
+    st = workspace(ctx, perm, &ws);
+  }
   if (st != BEM_OK) return st;
   if ((st = lu_perm(ctx, n, batch, piv, (int32_t*)ws)) != BEM_OK) return st;
   return lu_solve_perm(ctx, prec, n, ld, stride, batch, LU, (const int32_t*)ws, n_rhs, B, X,
-                       bstride);
+                       bstride, (double2*)((char*)ws + perm), vectors);
 }
 
 // ============================================================ batched solve
@@ -573,7 +586,7 @@ bem_status chunk_finish_fp64(SolveRun& R, const Chunk& c, int k0, int kc, int64_
   if ((st = lu_perm(ctx, n, kc, c.piv, c.perm)) != BEM_OK) return st;
   double2* xo = R.xout + (size_t)k0 * nr * n;
   if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, (int64_t)n * ld, kc, c.A, c.perm, nr, c.b, xo,
-                          (int64_t)nr * n)) != BEM_OK)
+                          (int64_t)nr * n, nullptr, 0)) != BEM_OK)
     return st;
   std::vector<int32_t> hinfo(kc);
   if ((st = launch_residual(ctx, s, kc, R.pr->k + k0, nr, y, xo, c.diag, c.r)) != BEM_OK) return st;
@@ -670,7 +683,7 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
     if ((st = upload(h_act)) != BEM_OK) return st;
     if ((st = launch_ir_scale(ctx, nv, n, rsrc, c.r32, c.scale)) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, (int64_t)n * ld, kc, c.A, c.perm, nr, c.r32,
-                            c.d32, (int64_t)nr * n)) != BEM_OK)
+                            c.d32, (int64_t)nr * n, c.r, nv)) != BEM_OK)
       return st;
     if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, active, c.x, c.dn2, c.xn2, 0)) != BEM_OK)
       return st;
@@ -751,7 +764,6 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
   return BEM_OK;
 }
 
-size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 }  // namespace
 
@@ -965,7 +977,7 @@ extern "C" bem_status bem_refine_batched(bem_ctx* ctx, const bem_surface* s, int
       BEM_HIP_TRY(ctx, hipMemcpyAsync(active, h_act, nv, hipMemcpyHostToDevice, ctx->stream));
       if ((st = launch_ir_scale(ctx, nv, n, r, r32, scale)) != BEM_OK) return st;
       if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, stride, cur, LU, perm, n_rhs, r32, d32,
-                              (int64_t)n_rhs * n, fac_index + k0, sel, nsel)) != BEM_OK)
+                              (int64_t)n_rhs * n, r, nv, fac_index + k0, sel, nsel)) != BEM_OK)
         return st;
       if ((st = launch_ir_update(ctx, nv, n, d32, scale, active, xk, dn2, xn2)) != BEM_OK) return st;
       BEM_HIP_TRY(ctx, hipMemcpyAsync(h_dn, dn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
@@ -1268,7 +1280,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
         if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
         if ((st = lu_perm(ctx, n, cur, c.piv, c.perm)) != BEM_OK) return st;
         if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, stride, cur, c.LU, c.perm, nr, c.b, c.x,
-                                (int64_t)nr * n)) != BEM_OK)
+                                (int64_t)nr * n, nullptr, 0)) != BEM_OK)
           return st;
       } else {
         if ((st = launch_c128_to_c64(ctx, (int64_t)cur * stride, c.A64, c.LU)) != BEM_OK) return st;
@@ -1284,7 +1296,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
           BEM_HIP_TRY(ctx, hipMemcpyAsync(c.active, h_act, nv, hipMemcpyHostToDevice, ctx->stream));
           if ((st = launch_ir_scale(ctx, nv, n, c.r, c.r32, c.scale)) != BEM_OK) return st;
           if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, stride, cur, c.LU, c.perm, nr, c.r32,
-                                  c.d32, (int64_t)nr * n)) != BEM_OK)
+                                  c.d32, (int64_t)nr * n, c.r, nv)) != BEM_OK)
             return st;
           if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, c.active, c.x, c.dn2, c.xn2, 1)) != BEM_OK)
             return st;
@@ -1450,7 +1462,7 @@ extern "C" bem_status bem_solve_chief(bem_ctx* ctx, const bem_surface* s, int32_
     if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
     if ((st = lu_perm(ctx, n, cur, (const int32_t*)P[3], (int32_t*)P[4])) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, sm, cur, P[2], (const int32_t*)P[4], nr, P[7],
-                            P[8], (int64_t)nr * n)) != BEM_OK)
+                            P[8], (int64_t)nr * n, nullptr, 0)) != BEM_OK)
       return st;
     // the stacked system's residual and right-hand side per row
     if ((st = fill_zero(ctx, P[11], (size_t)nv * n * 16)) != BEM_OK) return st;

@@ -10,6 +10,10 @@
 // workgroup per vector doing both read its factors at 21 GB/s: 64 systems of
 // n = 5124 took 9.9 ms per solve, 8 of n = 10242 12 ms, 32 of n = 2562 with 8 sets
 // of factors 2.9 ms; now 5.1, about 2.5 and 1.0 ms.
+//
+// The blocks' contributions are taken off float64 copies of the float32 vectors (acc,
+// where the caller has room for them): rounding a vector once per block of 256
+// gave solves of n = 5124 a 1.2 times larger error than one sum per unknown.
 #include <algorithm>
 
 #include "common.h"
@@ -92,15 +96,16 @@ constexpr int TS_TILES = 5;          // tiles of the largest block
 constexpr int TS_NB = 4 * TS_B;      // block; a remainder of up to a tile joins the last one
 constexpr int TS_DLD = TS_B + 1;     // leading dimension of a staged diagonal tile
 
-// LDS of trsv_block: two diagonal tiles, the block's unknowns, the sums of the
-// row tile about to be solved
+// LDS of trsv_block: the block's right-hand side, two diagonal tiles, the block's
+// unknowns, the sums of the row tile about to be solved
 template <typename C>
 constexpr size_t trsv_lds() {
-  return sizeof(C) * (2 * TS_B * TS_DLD + TS_TILES * TS_B + 2 * TS_B);
+  return sizeof(double2) * TS_TILES * TS_B + sizeof(C) * (2 * TS_B * TS_DLD + TS_TILES * TS_B + 2 * TS_B);
 }
 
-// Solves rows [i0, i0 + rows) of L (FWD) or U in place: xs (LDS) holds the
-// block's right-hand side on entry and its solution on exit.  Tiles are taken
+// Solves rows [i0, i0 + rows) of L (FWD) or U: bs (LDS) holds the block's right-hand
+// side, in float64 so that an unknown is rounded once when the earlier tiles' sums
+// have been taken off, and xs and bs its solution on exit.  Tiles are taken
 // in solving order (logical tile t is physical t, or T - 1 - t backwards).  Wave
 // 2 (I - 1) + half owns row tile I and one half of the columns of each tile it
 // multiplies: a lane keeps its row's 32 entries in registers, loaded while the
@@ -112,7 +117,7 @@ constexpr size_t trsv_lds() {
 // 2.3e-7 to 3.4e-7 at n = 642).
 template <typename R, bool FWD>
 __device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__ Lb, int64_t ld, int i0,
-                                           int rows, bool vec, typename Cx<R>::T* D,
+                                           int rows, bool vec, double2* bs, typename Cx<R>::T* D,
                                            typename Cx<R>::T* xs, typename Cx<R>::T* sums) {
   using C = typename Cx<R>::T;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -172,11 +177,12 @@ __device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__
     if (wid == solver) {
       const C* d = D + (J & 1) * TS_B * TS_DLD + lane * TS_DLD;
       const int r0 = phys(J) * TS_B;
-      C v = xs[r0 + lane];   // (xs is padded with zeros to whole tiles)
+      double2 b = bs[r0 + lane];   // (padded with zeros to whole tiles)
       if (J > 0) {
-        v.x -= sums[lane].x + sums[TS_B + lane].x;
-        v.y -= sums[lane].y + sums[TS_B + lane].y;
+        b.x -= sums[lane].x + sums[TS_B + lane].x;
+        b.y -= sums[lane].y + sums[TS_B + lane].y;
       }
+      C v = cmk<C>((R)b.x, (R)b.y);
       if (FWD) {
 #pragma unroll
         for (int c = 0; c < TS_B; ++c) {
@@ -195,6 +201,7 @@ __device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__
         }
       }
       xs[r0 + lane] = v;
+      bs[r0 + lane] = make_double2(v.x, v.y);
     }
     if (J + 1 < T) stage_store(J + 1);
     __syncthreads();   // the unknowns of tile J are there
@@ -218,16 +225,17 @@ __device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__
 
 // One workgroup per vector.  WHOLE: the whole solve of systems of one block
 // (permuted right-hand side in, both triangles); else the block [i0, i0 + rows)
-// of L (FWD) or U of the vectors in X.
+// of L (FWD) or U of the vectors in acc [gridDim.x][n], or NULL: in X.
 template <typename R, bool WHOLE, bool FWD>
 __global__ __launch_bounds__(TS_T) void trsv_block_kernel(
     int n, int64_t ld, int64_t stride, const typename Cx<R>::T* __restrict__ LU,
     const int32_t* __restrict__ perm, int n_rhs, const typename Cx<R>::T* __restrict__ Bin,
     typename Cx<R>::T* __restrict__ X, int64_t bstride, const int32_t* __restrict__ fac_index,
-    const int32_t* __restrict__ vidx, int i0, int rows, bool vec) {
+    const int32_t* __restrict__ vidx, int i0, int rows, bool vec, double2* __restrict__ acc) {
   using C = typename Cx<R>::T;
   extern __shared__ unsigned char smem[];
-  C* D = reinterpret_cast<C*>(smem);
+  double2* bs = reinterpret_cast<double2*>(smem);
+  C* D = reinterpret_cast<C*>(bs + TS_TILES * TS_B);
   C* xs = D + 2 * TS_B * TS_DLD;
   C* sums = xs + TS_TILES * TS_B;
   // vector group: blockIdx / n_rhs, or the vidx entry when a subset is solved,
@@ -238,42 +246,58 @@ __global__ __launch_bounds__(TS_T) void trsv_block_kernel(
   const C* Lb = LU + (int64_t)fac * stride;
   if (threadIdx.x < TS_TILES * TS_B) {
     const int i = threadIdx.x;
-    C v = cmk<C>(R(0), R(0));
-    if (i < rows) v = WHOLE ? Bin[off + perm[(int64_t)fac * n + i]] : X[off + i0 + i];
-    xs[i] = v;
+    double2 b = make_double2(0.0, 0.0);
+    if (i < rows) {
+      if (!WHOLE && acc) {
+        b = acc[(int64_t)blockIdx.x * n + i0 + i];
+      } else {
+        const C v = WHOLE ? Bin[off + perm[(int64_t)fac * n + i]] : X[off + i0 + i];
+        b = make_double2(v.x, v.y);
+      }
+    }
+    bs[i] = b;
+    xs[i] = cmk<C>(R(0), R(0));
   }
   if (WHOLE) {
-    trsv_block<R, true>(Lb, ld, 0, rows, vec, D, xs, sums);
-    trsv_block<R, false>(Lb, ld, 0, rows, vec, D, xs, sums);
+    trsv_block<R, true>(Lb, ld, 0, rows, vec, bs, D, xs, sums);
+    trsv_block<R, false>(Lb, ld, 0, rows, vec, bs, D, xs, sums);
   } else {
-    trsv_block<R, FWD>(Lb, ld, i0, rows, vec, D, xs, sums);
+    trsv_block<R, FWD>(Lb, ld, i0, rows, vec, bs, D, xs, sums);
   }
-  if ((int)threadIdx.x < rows) X[off + i0 + threadIdx.x] = xs[threadIdx.x];
+  if ((int)threadIdx.x < rows) {
+    const C v = xs[threadIdx.x];
+    X[off + i0 + threadIdx.x] = v;
+    // (what the solve with U starts from)
+    if (!WHOLE && FWD && acc) acc[(int64_t)blockIdx.x * n + i0 + threadIdx.x] = make_double2(v.x, v.y);
+  }
 }
 
-// X = P B
+// acc = P B, or X = P B
 template <typename C>
 __global__ void trsv_permute_kernel(int n, const int32_t* __restrict__ perm, int n_rhs,
                                     const C* __restrict__ Bin, C* __restrict__ X, int64_t bstride,
                                     const int32_t* __restrict__ fac_index,
-                                    const int32_t* __restrict__ vidx) {
+                                    const int32_t* __restrict__ vidx, double2* __restrict__ acc) {
   const int i = blockIdx.y * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int mat = vidx ? vidx[blockIdx.x / n_rhs] : blockIdx.x / n_rhs;
   const int fac = fac_index ? fac_index[mat] : mat;
   const int64_t off = (int64_t)mat * bstride + (int64_t)(blockIdx.x % n_rhs) * n;
-  X[off + i] = Bin[off + perm[(int64_t)fac * n + i]];
+  const C v = Bin[off + perm[(int64_t)fac * n + i]];
+  if (acc) acc[(int64_t)blockIdx.x * n + i] = make_double2(v.x, v.y);
+  else X[off + i] = v;
 }
 
-// X[rows] -= LU[rows, c0 .. c0 + cols) X[c0 .. c0 + cols) for the rows [ra, rb),
-// NR right-hand sides at once.  A wave takes 16 / NR rows, its lanes the columns
+// V[rows] -= LU[rows, c0 .. c0 + cols) X[c0 .. c0 + cols) for the rows [ra, rb),
+// NR right-hand sides at once; V = acc, its matrices acc_stride apart, or X.  A wave takes 16 / NR rows, its lanes the columns
 // (16-byte words); the 32 sums of a wave are reduced by recursive halving (32
 // shuffles).
 template <typename R, int NR>
 __global__ __launch_bounds__(256) void trsv_update_kernel(
     int n, int64_t ld, int64_t stride, const typename Cx<R>::T* __restrict__ LU, int n_rhs,
     typename Cx<R>::T* __restrict__ X, int64_t bstride, const int32_t* __restrict__ fac_index,
-    const int32_t* __restrict__ vidx, int ra, int rb, int c0, int cols, bool vec) {
+    const int32_t* __restrict__ vidx, int ra, int rb, int c0, int cols, bool vec,
+    double2* __restrict__ acc, int64_t acc_stride) {
   using C = typename Cx<R>::T;
   constexpr int RPW = 16 / NR, PER = 16 / (int)sizeof(C), CW = 64 * PER;   // columns of a step
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -344,8 +368,13 @@ __global__ __launch_bounds__(256) void trsv_update_kernel(
   h[0] += __shfl_xor(h[0], 1, 64);
   const int e = lane >> 1, i = e / (2 * NR), r = (e / 2) % NR;
   if (!(lane & 1) && r0 + i < rb && r < nrh) {
-    R* dst = reinterpret_cast<R*>(x + (int64_t)r * n + r0 + i) + (e & 1);
-    *dst -= h[0];
+    if (acc) {
+      double2* a = acc + blockIdx.y * acc_stride + (int64_t)(rh0 + r) * n + r0 + i;
+      reinterpret_cast<double*>(a)[e & 1] -= h[0];
+    } else {
+      R* dst = reinterpret_cast<R*>(x + (int64_t)r * n + r0 + i) + (e & 1);
+      *dst -= h[0];
+    }
   }
 }
 
@@ -481,9 +510,9 @@ __global__ __launch_bounds__(SW_T) void trsv_sweep_kernel(int n, int64_t ld, int
 }
 
 template <typename R>
-bem_status solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
+void solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
                     const void* LU_, const int32_t* perm, int n_rhs, const void* B_, void* X_,
-                    int64_t bstride, const int32_t* fac_index, const int32_t* vidx) {
+                    int64_t bstride, const int32_t* fac_index, const int32_t* vidx, double2* acc) {
   using C = typename Cx<R>::T;
   const C* LU = (const C*)LU_;
   const C* B = (const C*)B_;
@@ -495,11 +524,11 @@ bem_status solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
   const dim3 bt(TS_T), vectors((unsigned)(groups * n_rhs));
   if (n <= TS_TILES * TS_B) {
     hipLaunchKernelGGL((trsv_block_kernel<R, true, true>), vectors, bt, lds, ctx->stream, n, ld,
-                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, 0, n, vec);
-    return BEM_OK;
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, 0, n, vec, acc);
+    return;
   }
   hipLaunchKernelGGL(trsv_permute_kernel<C>, dim3(vectors.x, (n + 255) / 256), dim3(256), 0,
-                     ctx->stream, n, perm, n_rhs, B, X, bstride, fac_index, vidx);
+                     ctx->stream, n, perm, n_rhs, B, X, bstride, fac_index, vidx, acc);
   // blocks of TS_NB unknowns, the last with up to TS_TILES tiles
   const int nb = std::max(1, (n - TS_B + TS_NB - 1) / TS_NB);
   auto start = [&](int q) { return q * TS_NB; };
@@ -513,7 +542,8 @@ bem_status solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
         hipLaunchKernelGGL((trsv_update_kernel<R, NR>),
                            dim3((rb - ra + 64 / NR - 1) / (64 / NR), groups, (nz + NR - 1) / NR),
                            dim3(256), 0, ctx->stream, n, ld, stride, LU, nz, X + (int64_t)z0 * n,
-                           bstride, fac_index, vidx, ra, rb, start(q), rows(q), vec);
+                           bstride, fac_index, vidx, ra, rb, start(q), rows(q), vec,
+                           acc ? acc + (int64_t)z0 * n : nullptr, (int64_t)n_rhs * n);
       }
     };
     if (n_rhs == 1) go(std::integral_constant<int, 1>{});
@@ -522,15 +552,14 @@ bem_status solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
   };
   for (int q = 0; q < nb; ++q) {
     hipLaunchKernelGGL((trsv_block_kernel<R, false, true>), vectors, bt, lds, ctx->stream, n, ld,
-                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec);
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec, acc);
     update(start(q) + rows(q), n, q);
   }
   for (int q = nb - 1; q >= 0; --q) {
     hipLaunchKernelGGL((trsv_block_kernel<R, false, false>), vectors, bt, lds, ctx->stream, n, ld,
-                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec);
+                       stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, start(q), rows(q), vec, acc);
     update(0, start(q), q);
   }
-  return BEM_OK;
 }
 
 }  // namespace
@@ -550,8 +579,8 @@ bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* 
 
 bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
                          int batch, const void* LU, const int32_t* perm, int n_rhs,
-                         const void* Bin, void* X, int64_t bstride, const int32_t* fac_index,
-                         const int32_t* vidx, int n_sel) {
+                         const void* Bin, void* X, int64_t bstride, double2* acc, int64_t acc_vectors,
+                         const int32_t* fac_index, const int32_t* vidx, int n_sel) {
   if (vidx) batch = n_sel;
   if (batch <= 0 || n_rhs <= 0) return BEM_OK;
   static bool attr_set = false;
@@ -572,7 +601,6 @@ bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t
   const size_t esz = prec == BEM_C128 ? 16 : 8;
   const int most = 65535;   // groups per launch (grid y)
   const int pi = prof_begin(ctx, "getrs");
-  bem_status st = BEM_OK;
   const double items = batch;
   const size_t lds = sweep_lds(esz, n);
   // (one block needs no updates; more right-hand sides share the factors' reads above)
@@ -588,19 +616,27 @@ bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t
                          bstride, fac_index, vidx);
     batch = 0;
   }
-  for (int g0 = 0; g0 < batch && st == BEM_OK; g0 += most) {
-    const int g = std::min(most, batch - g0);
+  // slices of matrices, and of right-hand sides where not one matrix's fit acc
+  if (prec == BEM_C128 || acc_vectors <= 0) acc = nullptr;
+  const int zs = acc ? (int)std::min<int64_t>(n_rhs, acc_vectors) : n_rhs;
+  const int gs = acc ? (int)std::min<int64_t>(most, acc_vectors / zs) : most;
+  for (int g0 = 0; g0 < batch; g0 += gs) {
+    const int g = std::min(gs, batch - g0);
     // without an index list the slice is taken by moving the pointers
     const size_t vo = vidx ? 0 : (size_t)g0 * bstride * esz;
     const char* lu = (const char*)LU + (vidx || fac_index ? 0 : (size_t)g0 * stride * esz);
     const int32_t* pm = perm + (vidx || fac_index ? 0 : (size_t)g0 * n);
     const int32_t* fi = fac_index && !vidx ? fac_index + g0 : fac_index;
     const int32_t* vi = vidx ? vidx + g0 : nullptr;
-    const char* b = (const char*)Bin + vo;
-    char* x = (char*)X + vo;
-    st = prec == BEM_C128
-             ? solve_go<double>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi)
-             : solve_go<float>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi);
+    for (int z0 = 0; z0 < n_rhs; z0 += zs) {
+      const int z = std::min(zs, n_rhs - z0);
+      const char* b = (const char*)Bin + vo + (size_t)z0 * n * esz;
+      char* x = (char*)X + vo + (size_t)z0 * n * esz;
+      if (prec == BEM_C128)
+        solve_go<double>(ctx, n, ld, stride, g, lu, pm, z, b, x, bstride, fi, vi, nullptr);
+      else
+        solve_go<float>(ctx, n, ld, stride, g, lu, pm, z, b, x, bstride, fi, vi, acc);
+    }
   }
   prof_end(ctx, "getrs", pi, 8.0 * (double)n * n * n_rhs * items,
            (double)esz * ((double)n * n + 3.0 * n * n_rhs) * items);
