@@ -133,17 +133,14 @@ __device__ inline R part_sum(R v) {
 // the recurrence form plus 180 of geometry and phases per (point, source), and
 // the LDS reads of 32 bytes of data per wavenumber.  On an even chunk (k_q =
 // k_0 + q dk to a few ulp) both phases advance by rotation, so a pair takes
-// four sincos instead of 2 FCH, and G carries w / r from the start.  Uneven
+// four sincos instead of 2 FCH, and G carries w / r from the start; the products
+// k r keep their rounding errors and every step the wavenumbers' own (EvenChunk), so
+// the phases are closer than a sincos of each rounded product.  Uneven
 // wavenumbers, and workgroups with a phase past the 2^20 rad for which the
 // reduction of phase.h holds, go one wavenumber at a time (any other form in
 // this kernel spills registers).  2304 points x 32 wavenumbers x 2562 nodes with
-// the nodes' own sums: 4.46 to 1.13 ms against a library sincos per value.
-__device__ __forceinline__ double2 unit_phase(double t) {
-  double s, c;
-  phase_sincos_near(t, &s, &c);
-  return make_double2(c, s);
-}
-
+// the nodes' own sums take 1.31 ms (4.46 with a library sincos per value; 1.13 with
+// uncorrected rotations).
 template <int FCH, int MODE, int NR>
 __global__ __launch_bounds__(kFT, 2) void field64_kernel(
     FieldSources src, int n, const double* __restrict__ x, const double* __restrict__ nrm,
@@ -171,17 +168,9 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
   const bool own = MODE == 0 || p >= m;
   const double px = own ? ax : xp[3 * p], py = own ? ay : xp[3 * p + 1],
                pz = own ? az : xp[3 * p + 2];
-  // the chunk's wavenumbers, continued evenly past a partial chunk's end (those
-  // sums are not stored)
-  double kk[FCH], kmax = 0.0;
-  const double dkk = nf > 1 ? (kv[m0 + nf - 1] - kv[m0]) / (nf - 1) : 0.0;
-  bool uni = true;
-#pragma unroll
-  for (int f = 0; f < FCH; ++f) {
-    kk[f] = f < nf ? kv[m0 + f] : kv[m0] + f * dkk;
-    kmax = fmax(kmax, fabs(kk[f]));
-    if (!(fabs(kk[f] - (kk[0] + f * dkk)) <= 4e-16 * fabs(kk[f]))) uni = false;
-  }
+  // (the sums of wavenumbers past a partial chunk's end are not stored)
+  EvenChunk<FCH> kc;
+  kc.load(kv + m0, nf);
   // geometry of source jj of the staged tile: r, n_a.(x_j - x_a), w / r,
   // (d.n_j) / r^2, n_a.n_j
   struct Pair {
@@ -190,14 +179,8 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
   auto geometry = [&](int jj) {
     Pair g;
     const double dx = sx[jj][0] - px, dy = sx[jj][1] - py, dz = sx[jj][2] - pz;
-    // 1/r from the reciprocal square root estimate and two Newton steps, r
-    // with a correction step of its own (it enters the phase)
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    double rinv = __builtin_amdgcn_rsq(r2);
-    rinv *= fma(-0.5 * r2, rinv * rinv, 1.5);
-    rinv *= fma(-0.5 * r2, rinv * rinv, 1.5);
-    const double r = r2 * rinv;
-    g.r = fma(fma(-r, r, r2), 0.5 * rinv, r);
+    double rinv;
+    dist_and_inverse64(dx * dx + dy * dy + dz * dz, g.r, rinv);
     g.c = (dx * sn[jj][0] + dy * sn[jj][1] + dz * sn[jj][2]) * (rinv * rinv);
     g.nn = anx * sn[jj][0] + any * sn[jj][1] + anz * sn[jj][2];
     g.sa = anx * (sx[jj][0] - ax) + any * (sx[jj][1] - ay) + anz * (sx[jj][2] - az);
@@ -273,7 +256,7 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
     }
   };
   bool wide = false;
-  if (uni) {
+  if (kc.even) {
     double2 A1[FCH][NR], A2[FCH], A3[FCH];   // A3 times k
 #pragma unroll
     for (int f = 0; f < FCH; ++f) {
@@ -288,17 +271,17 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
       for (int jj = part; jj < cnt; jj += kParts) {
         if (src.nodes && j0 + jj == a) continue;   // both brackets vanish there
         const Pair g = geometry(jj);
-        wide |= !(kmax * fmax(g.r, fabs(g.sa)) < kPhaseNear);
-        const double2 E = unit_phase(kk[0] * g.r), dE = unit_phase(dkk * g.r);
-        const double2 dF = unit_phase(dkk * g.sa);
-        double2 F = unit_phase(kk[0] * g.sa), G = make_double2(g.wr * E.x, g.wr * E.y);
+        wide |= !(kc.kmax * fmax(g.r, fabs(g.sa)) < kPhaseNear);
+        const double2 E = unit_phase(kc.k[0], g.r), dE = unit_phase(kc.dk, g.r);
+        const double2 dF = unit_phase(kc.dk, g.sa);
+        double2 F = unit_phase(kc.k[0], g.sa), G = make_double2(g.wr * E.x, g.wr * E.y);
 #pragma unroll
         for (int f = 0; f < FCH; ++f) {
           if (f > 0) {
-            G = make_double2(fma(G.x, dE.x, -G.y * dE.y), fma(G.x, dE.y, G.y * dE.x));
-            F = make_double2(fma(F.x, dF.x, -F.y * dF.y), fma(F.x, dF.y, F.y * dF.x));
+            G = turn(rotate(G, dE), kc.step[f] * g.r);
+            F = turn(rotate(F, dF), kc.step[f] * g.sa);
           }
-          term(jj, f, kk[f], g, G, F, A1[f], A2[f], A3[f]);
+          term(jj, f, kc.k[f], g, G, F, A1[f], A2[f], A3[f]);
         }
       }
     }
