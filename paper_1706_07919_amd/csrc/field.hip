@@ -139,8 +139,8 @@ __device__ inline R part_sum(R v) {
 // wavenumbers, and workgroups with a phase past the 2^20 rad for which the
 // reduction of phase.h holds, go one wavenumber at a time (any other form in
 // this kernel spills registers).  2304 points x 32 wavenumbers x 2562 nodes with
-// the nodes' own sums take 1.31 ms (4.46 with a library sincos per value; 1.13 with
-// uncorrected rotations).
+// the nodes' own sums take 1.29 ms (4.46 with a library sincos per value; 1.13 with
+// the roundings left out).
 template <int FCH, int MODE, int NR>
 __global__ __launch_bounds__(kFT, 2) void field64_kernel(
     FieldSources src, int n, const double* __restrict__ x, const double* __restrict__ nrm,
@@ -272,14 +272,16 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
         if (src.nodes && j0 + jj == a) continue;   // both brackets vanish there
         const Pair g = geometry(jj);
         wide |= !(kc.kmax * fmax(g.r, fabs(g.sa)) < kPhaseNear);
-        const double2 E = unit_phase(kc.k[0], g.r), dE = unit_phase(kc.dk, g.r);
-        const double2 dF = unit_phase(kc.dk, g.sa);
-        double2 F = unit_phase(kc.k[0], g.sa), G = make_double2(g.wr * E.x, g.wr * E.y);
+        const double2 E = unit_phase(kc.k[kc.kMid], g.r), dE = unit_phase(kc.dk, g.r);
+        const double2 F0 = unit_phase(kc.k[kc.kMid], g.sa), dF = unit_phase(kc.dk, g.sa);
+        const double2 G0 = make_double2(g.wr * E.x, g.wr * E.y);
+        double2 G = G0, F = F0;
 #pragma unroll
-        for (int f = 0; f < FCH; ++f) {
-          if (f > 0) {
-            G = turn(rotate(G, dE), kc.step[f] * g.r);
-            F = turn(rotate(F, dF), kc.step[f] * g.sa);
+        for (int i = 0; i < FCH; ++i) {
+          const int f = kc.order(i);
+          if (i > 0) {
+            G = kc.advance(i, i == kc.kUp ? G0 : G, dE, g.r);
+            F = kc.advance(i, i == kc.kUp ? F0 : F, dF, g.sa);
           }
           term(jj, f, kc.k[f], g, G, F, A1[f], A2[f], A3[f]);
         }

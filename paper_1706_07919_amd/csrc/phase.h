@@ -56,6 +56,9 @@ __device__ inline double2 unit_phase(double k, double t) {
 __device__ inline double2 rotate(double2 a, double2 b) {   // a b
   return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
+__device__ inline double2 rotate_back(double2 a, double2 b) {   // a conj(b)
+  return make_double2(fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -a.x * b.y));
+}
 __device__ inline double2 turn(double2 a, double e) {   // a e^{i e}, e tiny
   return make_double2(fma(-e, a.y, a.x), fma(e, a.x, a.y));
 }
@@ -69,6 +72,17 @@ template <int KC>
 struct EvenChunk {
   double k[KC], step[KC], dk, kmax;
   bool even;
+  // Phases start from the middle wavenumber: a rotation's rounding counts once per step
+  // taken, so the ends are up to KC / 2 steps off instead of KC - 1.  The i-th value
+  // is wavenumber order(i): up from the middle, then, from it again, down.
+  static constexpr int kMid = (KC - 1) / 2, kUp = KC - kMid;
+  static constexpr int order(int i) { return i < kUp ? kMid + i : KC - 1 - i; }
+  // phase of wavenumber order(i), i > 0, from that of the one before it (from the
+  // middle one's for i == kUp), d = e^{i dk t}
+  __device__ inline double2 advance(int i, double2 e, double2 d, double t) const {
+    const int q = order(i);
+    return i < kUp ? turn(rotate(e, d), step[q] * t) : turn(rotate_back(e, d), -step[q + 1] * t);
+  }
   // wavenumbers kv[0 .. n - 1], 1 <= n <= KC, continued evenly past n
   __device__ inline void load(const double* kv, int n) {
     const double k0 = kv[0];
@@ -94,14 +108,14 @@ struct EvenChunk {
 // r and 1/r from r^2 > 0 without the library's square root and division: the
 // float64 reciprocal square root estimate (any float64 r^2, where the float32 one
 // ends at distances of 1e-19 and 1e19), two Newton steps, and a correction step for
-// r (it enters the phases, so it is kept to the rounding of a square root).
+// each, which keep them to the rounding of a square root and a division.
 __device__ inline void dist_and_inverse64(double r2, double& r, double& rinv) {
   double y = __builtin_amdgcn_rsq(r2);
   y *= fma(-0.5 * r2, y * y, 1.5);
   y *= fma(-0.5 * r2, y * y, 1.5);
-  rinv = y;
   const double r1 = r2 * y;
   r = fma(fma(-r1, r1, r2), 0.5 * y, r1);
+  rinv = fma(y, fma(-r, y, 1.0), y);
 }
 
 __device__ inline void phase_sincos(double x, double* s, double* c) {

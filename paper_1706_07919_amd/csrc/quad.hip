@@ -30,7 +30,7 @@ namespace {
 constexpr int kQ = 7;          // points of the triangle rule
 constexpr int kMaxInc = 12;    // element incidences kept per node
 constexpr int kQT = 256;       // threads of the row kernels
-constexpr int kRhsChunk = 2;   // right-hand sides per assembly launch
+constexpr int kRhsChunk = 2;   // most right-hand sides per assembly launch
 constexpr int kKc = 8;         // wavenumbers per assembly workgroup
 constexpr double kFourPiQ = 12.566370614359172953850573533118;
 
@@ -170,8 +170,8 @@ __device__ inline double block_sum(double v, double* sh) {
 // e^{ikr} / r advanced by rotation along its wavenumbers (four multiply-adds), so
 // a value costs about 11 instructions and a twelfth of a sincos; a workgroup per
 // wavenumber with a library sincos, square root and division per value took
-// 10.1 ms for 63 wavenumbers on 1002 nodes, this form 2.0 ms.  A partial chunk is
-// continued evenly (nothing stored past its end); uneven wavenumbers, or a phase
+// 10.1 ms for 63 wavenumbers on 1002 nodes, this form 2.2 ms (2.0 without the
+// roundings that EvenChunk keeps).  A partial chunk is continued evenly (nothing stored past its end); uneven wavenumbers, or a phase
 // past the 2^20 rad of phase.h's reduction, go one wavenumber at a time.
 struct QuadRow {
   int n, npts, i, kq0, kc, n_rhs, r0, nr;
@@ -179,7 +179,6 @@ struct QuadRow {
   const uint8_t* bc;
   const int32_t* inc;
   const double2* y;
-  double k0, dk;
 };
 
 struct QuadPair {
@@ -191,39 +190,29 @@ __device__ __forceinline__ QuadPair quad_pair(const double* o, double x0, double
   g.dx = o[0] - x0;
   g.dy = o[1] - x1;
   g.dz = o[2] - x2;
-  const double r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
-  double ri = __builtin_amdgcn_rsq(r2);
-  ri *= fma(-0.5 * r2, ri * ri, 1.5);
-  ri *= fma(-0.5 * r2, ri * ri, 1.5);
-  const double r = r2 * ri;
-  g.r = fma(fma(-r, r, r2), 0.5 * ri, r);
-  g.c = (g.dx * o[3] + g.dy * o[4] + g.dz * o[5]) * (ri * ri);
-  g.wr = ri;
+  dist_and_inverse64(g.dx * g.dx + g.dy * g.dy + g.dz * g.dz, g.r, g.wr);
+  g.c = (g.dx * o[3] + g.dy * o[4] + g.dz * o[5]) * (g.wr * g.wr);
   return g;
 }
 template <bool NEAR>
-__device__ __forceinline__ double2 quad_phase(double t) {
+__device__ __forceinline__ double2 quad_phase(double k, double t) {
+  if (NEAR) return unit_phase(k, t);
   double s, c;
-  if (NEAR) phase_sincos_near(t, &s, &c);
-  else phase_sincos(t, &s, &c);
+  phase_sincos(k * t, &s, &c);
   return make_double2(c, s);
 }
-__device__ __forceinline__ double2 rot(double2 a, double2 b) {
-  return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
-}
 
-// The row for KC wavenumbers k0 + q dk (kq0 the first's index): A, b, diag64.
-// red: LDS of [kQT / 64][2 kRhsChunk + 4][8].  False (nothing stored) if a phase
-// is too wide for the NEAR form.
-template <int KC, bool NEAR, typename OUT>
-__device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, int64_t ld,
+// The row for the KC wavenumbers of kc (p.kq0 the first's index): A, b, diag64.
+// red: LDS of [kQT / 64][2 NR + 4][8] (NR: at least p.nr).  False (nothing stored) if
+// a phase is too wide for the NEAR form.
+template <int KC, bool NEAR, int NR, typename OUT>
+__device__ __forceinline__ bool quad_row(const QuadRow& p, const EvenChunk<KC>& kc, OUT* __restrict__ A, int64_t ld,
                                          int64_t a_stride, double2* __restrict__ b,
                                          double2* __restrict__ diag64,
-                                         double (*red)[2 * kRhsChunk + 4][8]) {
+                                         double (*red)[2 * NR + 4][8]) {
   const int i = p.i, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const double x0 = p.x[3 * i], x1 = p.x[3 * i + 1], x2 = p.x[3 * i + 2];
   const double n0 = p.nrm[3 * i], n1 = p.nrm[3 * i + 1], n2 = p.nrm[3 * i + 2];
-  const double kmax = fmax(fabs(p.k0), fabs(p.k0 + (KC - 1) * p.dk));
   bool wide = false;
   // workgroup sums of component c of the chunk into red[.][c][q]
   auto reduce = [&](int c, const double (&v)[KC]) {
@@ -251,20 +240,22 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
       const QuadPair g = quad_pair(o, x0, x1, x2);
       const double s0 = n0 * g.dx + n1 * g.dy + n2 * g.dz;
       const double nn = n0 * o[3] + n1 * o[4] + n2 * o[5], wr = o[6] * g.wr;
-      if (NEAR) wide |= !(kmax * fmax(g.r, fabs(s0)) < kPhaseNear);
-      const double2 E = quad_phase<NEAR>(p.k0 * g.r);
-      double2 F = quad_phase<NEAR>(p.k0 * s0), G = make_double2(wr * E.x, wr * E.y), dE, dF;
+      if (NEAR) wide |= !(kc.kmax * fmax(g.r, fabs(s0)) < kPhaseNear);
+      const double2 E = quad_phase<NEAR>(kc.k[kc.kMid], g.r), F0 = quad_phase<NEAR>(kc.k[kc.kMid], s0);
+      const double2 G0 = make_double2(wr * E.x, wr * E.y);
+      double2 F = F0, G = G0, dE, dF;
       if (KC > 1) {
-        dE = quad_phase<NEAR>(p.dk * g.r);
-        dF = quad_phase<NEAR>(p.dk * s0);
+        dE = quad_phase<NEAR>(kc.dk, g.r);
+        dF = quad_phase<NEAR>(kc.dk, s0);
       }
 #pragma unroll
-      for (int q = 0; q < KC; ++q) {
-        if (q > 0) {
-          G = rot(G, dE);
-          F = rot(F, dF);
+      for (int i = 0; i < KC; ++i) {
+        const int q = kc.order(i);
+        if (i > 0) {
+          G = kc.advance(i, i == kc.kUp ? G0 : G, dE, g.r);
+          F = kc.advance(i, i == kc.kUp ? F0 : F, dF, s0);
         }
-        const double k = p.k0 + q * p.dk, ckr = k * (g.c * g.r), kn = k * nn;
+        const double k = kc.k[q], ckr = k * (g.c * g.r), kn = k * nn;
         const double2 H = make_double2(fma(-g.c, G.x, -ckr * G.y), fma(ckr, G.x, -g.c * G.y));
         const double gp = -kn * F.y, fp = kn * F.x;
         d[0][q] += fma(gp, G.x, -F.x * H.x);
@@ -274,12 +265,12 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) reduce(2 * kRhsChunk + c, d[c]);
+    for (int c = 0; c < 4; ++c) reduce(2 * NR + c, d[c]);
   }
   if (__syncthreads_or(wide)) return false;
-  double bac[2 * kRhsChunk][KC];
+  double bac[2 * NR][KC];
 #pragma unroll
-  for (int c = 0; c < 2 * kRhsChunk; ++c)
+  for (int c = 0; c < 2 * NR; ++c)
 #pragma unroll
     for (int q = 0; q < KC; ++q) bac[c][q] = 0.0;
   for (int j = threadIdx.x; j < p.n; j += kQT) {
@@ -294,13 +285,15 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
         const double* o = p.qp + 8 * ((int64_t)e * kQ + t);
         const QuadPair g = quad_pair(o, x0, x1, x2);
         const double wr = o[6] * g.wr * kShape[t][a], cr = g.c * g.r;
-        const double2 E = quad_phase<NEAR>(p.k0 * g.r);
-        double2 G = make_double2(wr * E.x, wr * E.y), dE;
-        if (KC > 1) dE = quad_phase<NEAR>(p.dk * g.r);
+        const double2 E = quad_phase<NEAR>(kc.k[kc.kMid], g.r);
+        const double2 G0 = make_double2(wr * E.x, wr * E.y);
+        double2 G = G0, dE;
+        if (KC > 1) dE = quad_phase<NEAR>(kc.dk, g.r);
 #pragma unroll
-        for (int q = 0; q < KC; ++q) {
-          if (q > 0) G = rot(G, dE);
-          const double ckr = (p.k0 + q * p.dk) * cr;
+        for (int i = 0; i < KC; ++i) {
+          const int q = kc.order(i);
+          if (i > 0) G = kc.advance(i, i == kc.kUp ? G0 : G, dE, g.r);
+          const double ckr = kc.k[q] * cr;
           mp[q].x += G.x;
           mp[q].y += G.y;
           mh[q].x = fma(g.c, G.x, fma(ckr, G.y, mh[q].x));
@@ -314,11 +307,11 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
       if (q >= p.kc) break;   // uniform
       const int64_t kq = p.kq0 + q;
       if (j == i) {
-        const double ki = 1.0 / (p.k0 + q * p.dk);
-        mh[q].x += kFourPiQ - total(2 * kRhsChunk, q);
-        mh[q].y -= total(2 * kRhsChunk + 1, q);
-        mp[q].x -= total(2 * kRhsChunk + 2, q) * ki;
-        mp[q].y -= total(2 * kRhsChunk + 3, q) * ki;
+        const double ki = 1.0 / kc.k[q];
+        mh[q].x += kFourPiQ - total(2 * NR, q);
+        mh[q].y -= total(2 * NR + 1, q);
+        mp[q].x -= total(2 * NR + 2, q) * ki;
+        mp[q].y -= total(2 * NR + 3, q) * ki;
         if (p.r0 == 0 && diag64) {
           diag64[2 * (kq * p.n + i)] = mh[q];
           diag64[2 * (kq * p.n + i) + 1] = mp[q];
@@ -331,7 +324,7 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
         Ap->y = u.y;
       }
 #pragma unroll
-      for (int r = 0; r < kRhsChunk; ++r)
+      for (int r = 0; r < NR; ++r)
         if (r < p.nr) {
           const double2 yv = p.y[(kq * p.n_rhs + p.r0 + r) * p.n + j];
           bac[2 * r][q] -= v.x * yv.x - v.y * yv.y;
@@ -340,7 +333,7 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
     }
   }
 #pragma unroll
-  for (int c = 0; c < 2 * kRhsChunk; ++c)
+  for (int c = 0; c < 2 * NR; ++c)
     if (c < 2 * p.nr) reduce(c, bac[c]);
   __syncthreads();
   const int q = threadIdx.x & 7, r = threadIdx.x >> 3;
@@ -351,27 +344,25 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, OUT* __restrict__ A, 
   return true;
 }
 
-template <typename OUT>
+template <typename OUT, int NR>
 __global__ __launch_bounds__(kQT, 2) void quad_assemble_kernel(
     int n, const double* __restrict__ x, const double* __restrict__ nrm,
     const uint8_t* __restrict__ bc, int npts, const double* __restrict__ qp,
     const int32_t* __restrict__ inc, const double* __restrict__ kv, int n_k, int n_rhs, int r0,
     int nr, const double2* __restrict__ y, OUT* __restrict__ A, int64_t ld, int64_t a_stride,
     double2* __restrict__ b, double2* __restrict__ diag64) {
-  __shared__ double red[kQT / 64][2 * kRhsChunk + 4][8];
+  __shared__ double red[kQT / 64][2 * NR + 4][8];
   const int q0 = blockIdx.y * kKc, kc = min(kKc, n_k - q0);
-  QuadRow p{n, npts, (int)blockIdx.x, q0, kc, n_rhs, r0, nr, x, nrm, qp, bc, inc, y, kv[q0], 0.0};
-  p.dk = kc > 1 ? (kv[q0 + kc - 1] - kv[q0]) / (kc - 1) : 0.0;
-  bool uni = true;
-  for (int q = 1; q < kc; ++q)
-    if (!(fabs(kv[q0 + q] - (p.k0 + q * p.dk)) <= 4e-16 * fabs(kv[q0 + q]))) uni = false;
-  if (uni && quad_row<kKc, true>(p, A, ld, a_stride, b, diag64, red)) return;
+  QuadRow p{n, npts, (int)blockIdx.x, q0, kc, n_rhs, r0, nr, x, nrm, qp, bc, inc, y};
+  EvenChunk<kKc> chunk;
+  chunk.load(kv + q0, kc);
+  if (chunk.even && quad_row<kKc, true, NR>(p, chunk, A, ld, a_stride, b, diag64, red)) return;
   p.kc = 1;
-  p.dk = 0.0;
   for (int q = 0; q < kc; ++q) {
     p.kq0 = q0 + q;
-    p.k0 = kv[q0 + q];
-    (void)quad_row<1, false>(p, A, ld, a_stride, b, diag64, red);
+    EvenChunk<1> one;
+    one.load(kv + p.kq0, 1);
+    (void)quad_row<1, false, NR>(p, one, A, ld, a_stride, b, diag64, red);
   }
 }
 
@@ -463,16 +454,16 @@ bem_status launch_quad_assemble(bem_ctx* ctx, const bem_quad_surface* s, const d
   for (int r0 = 0; r0 < n_rhs; r0 += kRhsChunk) {
     const int nr = std::min(kRhsChunk, n_rhs - r0);
     dim3 grid(s->n, (n_k + kKc - 1) / kKc);
-    if (prec == BEM_C128)
-      hipLaunchKernelGGL(quad_assemble_kernel<double2>, grid, dim3(kQT), 0, ctx->stream, s->n,
-                         s->x, s->nrm, s->bc, npts, qp, inc, k, n_k, n_rhs, r0, nr,
-                         (const double2*)y, (double2*)A, ld, a_stride, (double2*)b,
-                         (double2*)diag64);
-    else
-      hipLaunchKernelGGL(quad_assemble_kernel<float2>, grid, dim3(kQT), 0, ctx->stream, s->n,
-                         s->x, s->nrm, s->bc, npts, qp, inc, k, n_k, n_rhs, r0, nr,
-                         (const double2*)y, (float2*)A, ld, a_stride, (double2*)b,
-                         (double2*)diag64);
+#define BEM_QUAD_ASSEMBLE(OUT, NR)                                                                \
+  hipLaunchKernelGGL((quad_assemble_kernel<OUT, NR>), grid, dim3(kQT), 0, ctx->stream, s->n, s->x, \
+                     s->nrm, s->bc, npts, qp, inc, k, n_k, n_rhs, r0, nr, (const double2*)y,      \
+                     (OUT*)A, ld, a_stride, (double2*)b, (double2*)diag64)
+    // (one right-hand side's accumulators leave the registers for the phases)
+    if (prec == BEM_C128 && nr == 1) BEM_QUAD_ASSEMBLE(double2, 1);
+    else if (prec == BEM_C128) BEM_QUAD_ASSEMBLE(double2, kRhsChunk);
+    else if (nr == 1) BEM_QUAD_ASSEMBLE(float2, 1);
+    else BEM_QUAD_ASSEMBLE(float2, kRhsChunk);
+#undef BEM_QUAD_ASSEMBLE
     BEM_CHECK_LAUNCH(ctx);
   }
   // node-pair work: every (row, quadrature point) kernel value once for the
