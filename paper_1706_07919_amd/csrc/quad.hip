@@ -31,6 +31,7 @@ constexpr int kQ = 7;          // points of the triangle rule
 constexpr int kMaxInc = 12;    // element incidences kept per node
 constexpr int kQT = 256;       // threads of the row kernels
 constexpr int kRhsChunk = 2;   // most right-hand sides per assembly launch
+constexpr int kRhsWide = 4;    // and of a row that goes one wavenumber at a time
 constexpr int kKc = 8;         // wavenumbers per assembly workgroup
 constexpr double kFourPiQ = 12.566370614359172953850573533118;
 
@@ -171,8 +172,11 @@ __device__ inline double block_sum(double v, double* sh) {
 // a value costs about 11 instructions and a twelfth of a sincos; a workgroup per
 // wavenumber with a library sincos, square root and division per value took
 // 10.1 ms for 63 wavenumbers on 1002 nodes, this form 2.2 ms (2.0 without the
-// roundings that EvenChunk keeps).  A partial chunk is continued evenly (nothing stored past its end); uneven wavenumbers, or a phase
-// past the 2^20 rad of phase.h's reduction, go one wavenumber at a time.
+// roundings that EvenChunk keeps).  A partial chunk is continued evenly (nothing
+// stored past its end).  Uneven wavenumbers, or a phase past the 2^20 rad of phase.h's
+// reduction, go one wavenumber at a time; their values cost the most, so a row then
+// takes up to kRhsWide right-hand sides, those of the next launch among them (24
+// uneven wavenumbers with four of them: 3.3 ms, with two a launch 6.5).
 struct QuadRow {
   int n, npts, i, kq0, kc, n_rhs, r0, nr;
   const double *x, *nrm, *qp;
@@ -203,13 +207,14 @@ __device__ __forceinline__ double2 quad_phase(double k, double t) {
 }
 
 // The row for the KC wavenumbers of kc (p.kq0 the first's index): A, b, diag64.
-// red: LDS of [kQT / 64][2 NR + 4][8] (NR: at least p.nr).  False (nothing stored) if
-// a phase is too wide for the NEAR form.
-template <int KC, bool NEAR, int NR, typename OUT>
+// red: LDS; NR: at least p.nr.  False (nothing stored) if a phase is too wide for the
+// NEAR form.
+template <int KC, bool NEAR, int NR, int COMPS, typename OUT>
 __device__ __forceinline__ bool quad_row(const QuadRow& p, const EvenChunk<KC>& kc, OUT* __restrict__ A, int64_t ld,
                                          int64_t a_stride, double2* __restrict__ b,
                                          double2* __restrict__ diag64,
-                                         double (*red)[2 * NR + 4][8]) {
+                                         double (&red)[kQT / 64][COMPS][8]) {
+  static_assert(COMPS >= 2 * NR + 4, "the row's sums");
   const int i = p.i, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const double x0 = p.x[3 * i], x1 = p.x[3 * i + 1], x2 = p.x[3 * i + 2];
   const double n0 = p.nrm[3 * i], n1 = p.nrm[3 * i + 1], n2 = p.nrm[3 * i + 2];
@@ -351,18 +356,22 @@ __global__ __launch_bounds__(kQT, 2) void quad_assemble_kernel(
     const int32_t* __restrict__ inc, const double* __restrict__ kv, int n_k, int n_rhs, int r0,
     int nr, const double2* __restrict__ y, OUT* __restrict__ A, int64_t ld, int64_t a_stride,
     double2* __restrict__ b, double2* __restrict__ diag64) {
-  __shared__ double red[kQT / 64][2 * NR + 4][8];
+  constexpr int NW = NR == 1 ? 1 : kRhsWide;
+  static_assert(kRhsWide % kRhsChunk == 0, "whole launches per wide row");
+  __shared__ double red[kQT / 64][2 * NW + 4][8];
   const int q0 = blockIdx.y * kKc, kc = min(kKc, n_k - q0);
   QuadRow p{n, npts, (int)blockIdx.x, q0, kc, n_rhs, r0, nr, x, nrm, qp, bc, inc, y};
   EvenChunk<kKc> chunk;
   chunk.load(kv + q0, kc);
   if (chunk.even && quad_row<kKc, true, NR>(p, chunk, A, ld, a_stride, b, diag64, red)) return;
+  if (r0 % kRhsWide) return;   // (uniform) its right-hand sides are an earlier launch's
   p.kc = 1;
+  p.nr = min(NW, n_rhs - r0);
   for (int q = 0; q < kc; ++q) {
     p.kq0 = q0 + q;
     EvenChunk<1> one;
     one.load(kv + p.kq0, 1);
-    (void)quad_row<1, false, NR>(p, one, A, ld, a_stride, b, diag64, red);
+    (void)quad_row<1, false, NW>(p, one, A, ld, a_stride, b, diag64, red);
   }
 }
 
