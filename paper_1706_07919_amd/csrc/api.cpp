@@ -14,11 +14,12 @@
 namespace bem {
 
 bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* perm);
-// acc: float64 accumulators of the float32 solves, acc_vectors x n (or NULL, 0);
-// more vectors than that are solved in slices
+// acc: float64 accumulators of float32 solves, batch x n_rhs x n (or NULL, where
+// lu_solve_acc_bytes is 0 or they cannot be had)
+size_t lu_solve_acc_bytes(const bem_ctx* ctx, bem_prec prec, int n, int batch, int n_rhs);
 bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
                          int batch, const void* LU, const int32_t* perm, int n_rhs,
-                         const void* Bin, void* X, int64_t bstride, double2* acc, int64_t acc_vectors,
+                         const void* Bin, void* X, int64_t bstride, double2* acc,
                          const int32_t* fac_index = nullptr, const int32_t* vidx = nullptr,
                          int n_sel = 0);
 
@@ -534,21 +535,19 @@ extern "C" bem_status bem_getrs_batched(bem_ctx* ctx, bem_prec prec, int32_t n, 
       !B || !X || B == X || bstride < (int64_t)n * n_rhs || (prec != BEM_C64 && prec != BEM_C128))
     return fail(ctx, BEM_EINVAL, "bem_getrs_batched: bad argument");
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, BEM_EHIP, "hipSetDevice");
-  // the permutations, and for float32 the solve's accumulators (slices of at least 512
-  // vectors; none, and float32 sums, where they cannot be allocated)
+  // the permutations and the solve's accumulators (float32 sums where there is no room)
   const size_t perm = align256(sizeof(int32_t) * (size_t)n * batch);
-  int64_t vectors = prec == BEM_C64 ? std::min<int64_t>((int64_t)batch * n_rhs,
-                                                        std::max<int64_t>(512, (16 << 20) / n)) : 0;
+  size_t acc = lu_solve_acc_bytes(ctx, prec, n, batch, n_rhs);
   void* ws = nullptr;
-  bem_status st = workspace(ctx, perm + 16 * (size_t)(vectors * n), &ws);
-  if (st == BEM_ENOMEM && vectors > 0) {
-    vectors = 0;
+  bem_status st = workspace(ctx, perm + acc, &ws);
+  if (st == BEM_ENOMEM && acc > 0) {
+    acc = 0;
     st = workspace(ctx, perm, &ws);
   }
   if (st != BEM_OK) return st;
   if ((st = lu_perm(ctx, n, batch, piv, (int32_t*)ws)) != BEM_OK) return st;
   return lu_solve_perm(ctx, prec, n, ld, stride, batch, LU, (const int32_t*)ws, n_rhs, B, X,
-                       bstride, (double2*)((char*)ws + perm), vectors);
+                       bstride, acc ? (double2*)((char*)ws + perm) : nullptr);
 }
 
 // ============================================================ batched solve
@@ -586,7 +585,7 @@ bem_status chunk_finish_fp64(SolveRun& R, const Chunk& c, int k0, int kc, int64_
   if ((st = lu_perm(ctx, n, kc, c.piv, c.perm)) != BEM_OK) return st;
   double2* xo = R.xout + (size_t)k0 * nr * n;
   if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, (int64_t)n * ld, kc, c.A, c.perm, nr, c.b, xo,
-                          (int64_t)nr * n, nullptr, 0)) != BEM_OK)
+                          (int64_t)nr * n, nullptr)) != BEM_OK)
     return st;
   std::vector<int32_t> hinfo(kc);
   if ((st = launch_residual(ctx, s, kc, R.pr->k + k0, nr, y, xo, c.diag, c.r)) != BEM_OK) return st;
@@ -683,7 +682,7 @@ bem_status chunk_finish_ir(SolveRun& R, const Chunk& c, int k0, int kc, int64_t 
     if ((st = upload(h_act)) != BEM_OK) return st;
     if ((st = launch_ir_scale(ctx, nv, n, rsrc, c.r32, c.scale)) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, (int64_t)n * ld, kc, c.A, c.perm, nr, c.r32,
-                            c.d32, (int64_t)nr * n, c.r, nv)) != BEM_OK)
+                            c.d32, (int64_t)nr * n, c.r)) != BEM_OK)
       return st;
     if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, active, c.x, c.dn2, c.xn2, 0)) != BEM_OK)
       return st;
@@ -977,7 +976,7 @@ extern "C" bem_status bem_refine_batched(bem_ctx* ctx, const bem_surface* s, int
       BEM_HIP_TRY(ctx, hipMemcpyAsync(active, h_act, nv, hipMemcpyHostToDevice, ctx->stream));
       if ((st = launch_ir_scale(ctx, nv, n, r, r32, scale)) != BEM_OK) return st;
       if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, stride, cur, LU, perm, n_rhs, r32, d32,
-                              (int64_t)n_rhs * n, r, nv, fac_index + k0, sel, nsel)) != BEM_OK)
+                              (int64_t)n_rhs * n, r, fac_index + k0, sel, nsel)) != BEM_OK)
         return st;
       if ((st = launch_ir_update(ctx, nv, n, d32, scale, active, xk, dn2, xn2)) != BEM_OK) return st;
       BEM_HIP_TRY(ctx, hipMemcpyAsync(h_dn, dn2, 8 * nv, hipMemcpyDeviceToHost, ctx->stream));
@@ -1280,7 +1279,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
         if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
         if ((st = lu_perm(ctx, n, cur, c.piv, c.perm)) != BEM_OK) return st;
         if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, stride, cur, c.LU, c.perm, nr, c.b, c.x,
-                                (int64_t)nr * n, nullptr, 0)) != BEM_OK)
+                                (int64_t)nr * n, nullptr)) != BEM_OK)
           return st;
       } else {
         if ((st = launch_c128_to_c64(ctx, (int64_t)cur * stride, c.A64, c.LU)) != BEM_OK) return st;
@@ -1296,7 +1295,7 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
           BEM_HIP_TRY(ctx, hipMemcpyAsync(c.active, h_act, nv, hipMemcpyHostToDevice, ctx->stream));
           if ((st = launch_ir_scale(ctx, nv, n, c.r, c.r32, c.scale)) != BEM_OK) return st;
           if ((st = lu_solve_perm(ctx, BEM_C64, n, ld, stride, cur, c.LU, c.perm, nr, c.r32,
-                                  c.d32, (int64_t)nr * n, c.r, nv)) != BEM_OK)
+                                  c.d32, (int64_t)nr * n, c.r)) != BEM_OK)
             return st;
           if ((st = launch_ir_update(ctx, nv, n, c.d32, c.scale, c.active, c.x, c.dn2, c.xn2, 1)) != BEM_OK)
             return st;
@@ -1462,7 +1461,7 @@ extern "C" bem_status bem_solve_chief(bem_ctx* ctx, const bem_surface* s, int32_
     if ((st = lu_factor_groups(ctx, BEM_C128, sets, plan, 0)) != BEM_OK) return st;
     if ((st = lu_perm(ctx, n, cur, (const int32_t*)P[3], (int32_t*)P[4])) != BEM_OK) return st;
     if ((st = lu_solve_perm(ctx, BEM_C128, n, ld, sm, cur, P[2], (const int32_t*)P[4], nr, P[7],
-                            P[8], (int64_t)nr * n, nullptr, 0)) != BEM_OK)
+                            P[8], (int64_t)nr * n, nullptr)) != BEM_OK)
       return st;
     // the stacked system's residual and right-hand side per row
     if ((st = fill_zero(ctx, P[11], (size_t)nv * n * 16)) != BEM_OK) return st;

@@ -382,11 +382,7 @@ __global__ __launch_bounds__(256) void trsv_update_kernel(
 // processed in blocks of 64 rows.  For each block, the 64 x 64 diagonal block
 // is staged in LDS while the waves form the off-diagonal dot products (row-major
 // rows against the solved part of x, coalesced), then one wave substitutes
-// through the diagonal block from LDS.  x lives in LDS.  With one right-hand side
-// and a quarter more matrices than compute units this reads the factors faster than
-// the launches above, whose chip empties between blocks: 384 matrices of n = 1284 take
-// 1.44 ms against 1.66, 512 of 2562 4.9 against 7.2, 384 of 5124 13.7 against 20.1;
-// with 256 of 1284 it is 1.31 against 1.18, of 2562 3.7 against 3.8.
+// through the diagonal block from LDS.  x lives in LDS.
 constexpr int SW_B = 64;
 constexpr int SW_T = 512;
 template <typename C> __device__ inline C minus(C a, C b) { return cmk<C>(a.x - b.x, a.y - b.y); }
@@ -509,6 +505,29 @@ __global__ __launch_bounds__(SW_T) void trsv_sweep_kernel(int n, int64_t ld, int
   for (int i = tid; i < n; i += SW_T) xg[i] = x[i];
 }
 
+// Whether the sweep takes a solve.  It puts a workgroup on every vector, so it wins
+// once the vectors fill the chip, whose compute units the launches by blocks leave
+// between them; before that its one chain per vector costs more than their launches.
+// ms by blocks against the sweep, float32, on 256 compute units:
+//   n = 162    512 vectors 0.077 / 0.102    960  0.135 / 0.119   32000 3.58 / 2.83
+//   n = 642    256         0.39 / 0.49      320  0.52 / 0.43     1024  0.93 / 0.51
+//   n = 1284   256         0.83 / 0.92      320  1.52 / 1.20     1024  2.81 / 2.20
+//   n = 5124   48          3.7 / 9.5        256  10.7 / 9.0      1024  40 / 18
+// The float64 block kernels hold one workgroup per compute unit (their tiles fill the
+// LDS), and win only where a vector's sweep is long:
+//   n = 162    64 vectors  0.140 / 0.091                         4096  2.01 / 0.76
+//   n = 642    64          0.60 / 0.57      320  1.17 / 0.63     1024  2.30 / 1.15
+//   n = 1000   64          0.94 / 1.07      256  0.87 / 0.80
+//   n = 1284   64          1.30 / 1.62      320  2.57 / 2.95     1024  5.05 / 5.53
+// and with one right-hand side 256 matrices of 1284 take 2.2 / 1.8.
+bool sweeps(const bem_ctx* ctx, bem_prec prec, int n, int batch, int n_rhs) {
+  const int64_t vectors = (int64_t)batch * n_rhs, cus = ctx->num_cus;
+  if (sweep_lds(prec == BEM_C128 ? 16 : 8, n) > 150 * 1024) return false;
+  if (prec == BEM_C128) return n < 960 || (vectors >= cus && (n_rhs == 1 || n < 1200));
+  if (n <= TS_TILES * TS_B) return vectors > (n > 2 * TS_B ? 3 * cus : cus);
+  return n < 1536 ? 4 * vectors >= 5 * cus : vectors >= cus;
+}
+
 template <typename R>
 void solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
                     const void* LU_, const int32_t* perm, int n_rhs, const void* B_, void* X_,
@@ -522,7 +541,7 @@ void solve_go(bem_ctx* ctx, int n, int64_t ld, int64_t stride, int groups,
                                    : ((ld | stride) & 1) == 0 && ((uintptr_t)LU & 15) == 0;
   const size_t lds = trsv_lds<C>();
   const dim3 bt(TS_T), vectors((unsigned)(groups * n_rhs));
-  if (n <= TS_TILES * TS_B) {
+  if constexpr (sizeof(R) == 4) if (n <= TS_TILES * TS_B) {   // (float64: sweeps)
     hipLaunchKernelGGL((trsv_block_kernel<R, true, true>), vectors, bt, lds, ctx->stream, n, ld,
                        stride, LU, perm, n_rhs, B, X, bstride, fac_index, vidx, 0, n, vec, acc);
     return;
@@ -577,9 +596,14 @@ bem_status lu_perm(bem_ctx* ctx, int n, int batch, const int32_t* piv, int32_t* 
   return BEM_OK;
 }
 
+size_t lu_solve_acc_bytes(const bem_ctx* ctx, bem_prec prec, int n, int batch, int n_rhs) {
+  return prec == BEM_C64 && n > TS_TILES * TS_B && !sweeps(ctx, prec, n, batch, n_rhs)
+             ? sizeof(double2) * (size_t)batch * n_rhs * n : 0;
+}
+
 bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t stride,
                          int batch, const void* LU, const int32_t* perm, int n_rhs,
-                         const void* Bin, void* X, int64_t bstride, double2* acc, int64_t acc_vectors,
+                         const void* Bin, void* X, int64_t bstride, double2* acc,
                          const int32_t* fac_index, const int32_t* vidx, int n_sel) {
   if (vidx) batch = n_sel;
   if (batch <= 0 || n_rhs <= 0) return BEM_OK;
@@ -593,7 +617,6 @@ bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t
     big((const void*)trsv_block_kernel<float, true, true>);
     big((const void*)trsv_block_kernel<float, false, true>);
     big((const void*)trsv_block_kernel<float, false, false>);
-    big((const void*)trsv_block_kernel<double, true, true>);
     big((const void*)trsv_block_kernel<double, false, true>);
     big((const void*)trsv_block_kernel<double, false, false>);
     attr_set = true;
@@ -603,40 +626,33 @@ bem_status lu_solve_perm(bem_ctx* ctx, bem_prec prec, int n, int64_t ld, int64_t
   const int pi = prof_begin(ctx, "getrs");
   const double items = batch;
   const size_t lds = sweep_lds(esz, n);
-  // (one block needs no updates; more right-hand sides share the factors' reads above)
-  if (n_rhs == 1 && 4 * (int64_t)batch >= 5 * (int64_t)ctx->num_cus && n > TS_TILES * TS_B &&
-      lds <= 150 * 1024) {
+  if (sweeps(ctx, prec, n, batch, n_rhs)) {
+    const dim3 vectors((unsigned)(batch * n_rhs));
     if (prec == BEM_C128)
-      hipLaunchKernelGGL((trsv_sweep_kernel<double>), dim3(batch), dim3(SW_T), lds, ctx->stream, n, ld,
+      hipLaunchKernelGGL((trsv_sweep_kernel<double>), vectors, dim3(SW_T), lds, ctx->stream, n, ld,
                          stride, (const double2*)LU, perm, n_rhs, (const double2*)Bin, (double2*)X,
                          bstride, fac_index, vidx);
     else
-      hipLaunchKernelGGL((trsv_sweep_kernel<float>), dim3(batch), dim3(SW_T), lds, ctx->stream, n, ld,
+      hipLaunchKernelGGL((trsv_sweep_kernel<float>), vectors, dim3(SW_T), lds, ctx->stream, n, ld,
                          stride, (const float2*)LU, perm, n_rhs, (const float2*)Bin, (float2*)X,
                          bstride, fac_index, vidx);
     batch = 0;
   }
-  // slices of matrices, and of right-hand sides where not one matrix's fit acc
-  if (prec == BEM_C128 || acc_vectors <= 0) acc = nullptr;
-  const int zs = acc ? (int)std::min<int64_t>(n_rhs, acc_vectors) : n_rhs;
-  const int gs = acc ? (int)std::min<int64_t>(most, acc_vectors / zs) : most;
-  for (int g0 = 0; g0 < batch; g0 += gs) {
-    const int g = std::min(gs, batch - g0);
+  for (int g0 = 0; g0 < batch; g0 += most) {
+    const int g = std::min(most, batch - g0);
     // without an index list the slice is taken by moving the pointers
     const size_t vo = vidx ? 0 : (size_t)g0 * bstride * esz;
     const char* lu = (const char*)LU + (vidx || fac_index ? 0 : (size_t)g0 * stride * esz);
     const int32_t* pm = perm + (vidx || fac_index ? 0 : (size_t)g0 * n);
     const int32_t* fi = fac_index && !vidx ? fac_index + g0 : fac_index;
     const int32_t* vi = vidx ? vidx + g0 : nullptr;
-    for (int z0 = 0; z0 < n_rhs; z0 += zs) {
-      const int z = std::min(zs, n_rhs - z0);
-      const char* b = (const char*)Bin + vo + (size_t)z0 * n * esz;
-      char* x = (char*)X + vo + (size_t)z0 * n * esz;
-      if (prec == BEM_C128)
-        solve_go<double>(ctx, n, ld, stride, g, lu, pm, z, b, x, bstride, fi, vi, nullptr);
-      else
-        solve_go<float>(ctx, n, ld, stride, g, lu, pm, z, b, x, bstride, fi, vi, acc);
-    }
+    const char* b = (const char*)Bin + vo;
+    char* x = (char*)X + vo;
+    if (prec == BEM_C128)
+      solve_go<double>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi, nullptr);
+    else
+      solve_go<float>(ctx, n, ld, stride, g, lu, pm, n_rhs, b, x, bstride, fi, vi,
+                      acc ? acc + (size_t)g0 * n_rhs * n : nullptr);
   }
   prof_end(ctx, "getrs", pi, 8.0 * (double)n * n * n_rhs * items,
            (double)esz * ((double)n * n + 3.0 * n * n_rhs) * items);
