@@ -31,12 +31,12 @@ constexpr int kGemmK = 32;   // depth held in registers
 
 template <bool TA, bool TB, int EPI, int T, bool VA, bool VB>
 __global__ __launch_bounds__(T == 1 ? 1024 : 256, T == 1 ? 1 : 2) void gemm_r32_kernel(
-    int M, int N, int K, int kpart, const float* __restrict__ A, int lda,
+    int M, int N, int K, int kpart, int parts, const float* __restrict__ A, int lda,
     const float* __restrict__ B, int ldb, const float* __restrict__ bias, float* __restrict__ C,
     int ldc, float* __restrict__ Y) {
-  extern __shared__ float part[];   // [waves][T * T * 16][64]
+  extern __shared__ float part[];   // [parts][T * T * 16][64]
   const int m0 = blockIdx.y * 32 * T, n0 = blockIdx.x * 32 * T;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int h = lane >> 5, l32 = lane & 31;
   constexpr int G = kGemmK / 8;
   struct Ops {
@@ -116,6 +116,7 @@ __global__ __launch_bounds__(T == 1 ? 1024 : 256, T == 1 ? 1 : 2) void gemm_r32_
       mma(o);
     }
   }
+  if (wid < parts)
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -130,8 +131,68 @@ __global__ __launch_bounds__(T == 1 ? 1024 : 256, T == 1 ? 1 : 2) void gemm_r32_
     const int col = n0 + 32 * (ij % T) + (l & 31);
     if (row >= M || col >= N) continue;
     float z = 0.f;
-    for (int w = 0; w < nw; ++w) z += part[w * T * T * 1024 + e];
+    for (int w = 0; w < parts; ++w) z += part[w * T * T * 1024 + e];
     if (EPI != 0 && bias) z += bias[col];
+    C[(int64_t)row * ldc + col] = z;
+    if (EPI == 1) Y[(int64_t)row * ldc + col] = z / (1.f + __expf(-z));
+  }
+}
+
+// The same product where it is shallow and its tiles fill the chip: the outputs are the
+// work, so a wave keeps one 32 x 32 block in registers and stores it from there (64 x
+// 64 tile per workgroup, operands through LDS), and many waves are in flight.  The
+// kernel above has two waves per SIMD, and its tile goes through LDS once more.  ms
+// of x W + b with SiLU here and there: 4096 x 10248 outputs of depth 10 0.100 / 0.258
+// (3.4 TB/s), 128 0.239 / 0.294, 192 0.306 / 0.381, 256 0.387 / 0.412, 384 0.542 /
+// 0.517; 256 x 10248 of depth 10 0.022 / 0.036, 96 0.035 / 0.040, 192 0.051 / 0.047.
+constexpr int MB = 64, NB = 64, KB = 16;
+
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void gemm_r32_shallow_kernel(
+    int M, int N, int K, const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
+    const float* __restrict__ bias, float* __restrict__ C, int ldc, float* __restrict__ Y) {
+  __shared__ float As[KB][MB + 4];
+  __shared__ float Bs[KB][NB + 4];
+  const int m0 = blockIdx.y * MB, n0 = blockIdx.x * NB;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int wm = wid >> 1, wn = wid & 1;
+  const int h = lane >> 5, l32 = lane & 31;
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  for (int k0 = 0; k0 < K; k0 += KB) {
+    // stage op(A) tile [KB][MB] and op(B) tile [KB][NB]: 1024 elements each
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = tid + 256 * q;
+      int mm, kk;
+      if (TA) { kk = e >> 6; mm = e & 63; } else { mm = e >> 4; kk = e & 15; }
+      const int gm = m0 + mm, gk = k0 + kk;
+      float va = 0.f;
+      if (gm < M && gk < K) va = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
+      As[kk][mm] = va;
+      int nn, kb;
+      if (TB) { nn = e >> 4; kb = e & 15; } else { kb = e >> 6; nn = e & 63; }
+      const int gn = n0 + nn, gkb = k0 + kb;
+      float vb = 0.f;
+      if (gn < N && gkb < K) vb = TB ? B[(int64_t)gn * ldb + gkb] : B[(int64_t)gkb * ldb + gn];
+      Bs[kb][nn] = vb;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < KB; k += 2)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[k + h][wm * 32 + l32], Bs[k + h][wn * 32 + l32],
+                                                 acc, 0, 0, 0);
+    __syncthreads();
+  }
+  const int col = n0 + wn * 32 + l32;
+  if (col >= N) return;
+  const float bv = (EPI != 0 && bias) ? bias[col] : 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = m0 + wm * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+    if (row >= M) continue;
+    const float z = acc[v] + bv;
     C[(int64_t)row * ldc + col] = z;
     if (EPI == 1) Y[(int64_t)row * ldc + col] = z / (1.f + __expf(-z));
   }
@@ -251,7 +312,8 @@ template <bool TA, bool TB, int EPI, int T>
 void gemm_go_t(bem_ctx* ctx, int M, int N, int K, const float* A, int lda, const float* B, int ldb,
                const float* bias, float* C, int ldc, float* Y) {
   const dim3 grid((N + 32 * T - 1) / (32 * T), (M + 32 * T - 1) / (32 * T));
-  // waves per workgroup: up to 16 (T = 1) or 4, each with at least 32 of depth
+  // parts of the depth: up to 16 (T = 1) or 4, each at least 32 deep, a wave each.
+  // (Four waves at least share the outputs.)
   int nw = T == 1 ? 16 : 4;
   while (nw > 1 && K < kGemmK * nw) nw /= 2;
   const int kpart = (K + kGemmK * nw - 1) / (kGemmK * nw) * kGemmK;
@@ -259,8 +321,8 @@ void gemm_go_t(bem_ctx* ctx, int M, int N, int K, const float* A, int lda, const
   const bool vb = TB && ldb % 4 == 0 && ((uintptr_t)B & 15) == 0;
   const size_t lds = (size_t)nw * T * T * 4096;
 #define BEM_MLP_GEMM(VA, VB)                                                                      \
-  hipLaunchKernelGGL((gemm_r32_kernel<TA, TB, EPI, T, VA, VB>), grid, dim3(64 * nw), lds,         \
-                     ctx->stream, M, N, K, kpart, A, lda, B, ldb, bias, C, ldc, Y)
+  hipLaunchKernelGGL((gemm_r32_kernel<TA, TB, EPI, T, VA, VB>), grid, dim3(64 * std::max(nw, 4)), lds,         \
+                     ctx->stream, M, N, K, kpart, nw, A, lda, B, ldb, bias, C, ldc, Y)
   if (va && vb) BEM_MLP_GEMM(!TA, TB);
   else if (va) BEM_MLP_GEMM(!TA, false);
   else if (vb) BEM_MLP_GEMM(false, TB);
@@ -273,7 +335,14 @@ void gemm_go_t(bem_ctx* ctx, int M, int N, int K, const float* A, int lda, const
 template <bool TA, bool TB, int EPI>
 void gemm_go(bem_ctx* ctx, int M, int N, int K, const float* A, int lda, const float* B, int ldb,
              const float* bias, float* C, int ldc, float* Y) {
-  if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) >= ctx->num_cus)
+  const dim3 tiles((N + NB - 1) / NB, (M + MB - 1) / MB);
+  const bool fills = (int64_t)tiles.x * tiles.y >= ctx->num_cus;
+  // shallow: a depth of 128, or 256 with x and W as they lie and four tiles a CU
+  const int shallow = !TA && !TB && (int64_t)tiles.x * tiles.y >= 4 * (int64_t)ctx->num_cus ? 256 : 128;
+  if (fills && K <= shallow)
+    hipLaunchKernelGGL((gemm_r32_shallow_kernel<TA, TB, EPI>), tiles, dim3(256), 0, ctx->stream, M, N, K, A,
+                       lda, B, ldb, bias, C, ldc, Y);
+  else if (fills)
     gemm_go_t<TA, TB, EPI, 2>(ctx, M, N, K, A, lda, B, ldb, bias, C, ldc, Y);
   else
     gemm_go_t<TA, TB, EPI, 1>(ctx, M, N, K, A, lda, B, ldb, bias, C, ldc, Y);
