@@ -207,23 +207,23 @@ __global__ void silu_bwd_kernel(int64_t count, const float* __restrict__ z,
   dz[t] = dy[t] * s * (1.f + zz * (1.f - s));
 }
 
-// db[n] = sum_b dz[b][n]: 64 columns per workgroup, 16 threads per column (one
+// db[n] = sum_b dz[b][n]: 64 columns per workgroup, up to 16 threads per column (one
 // thread per column: 256 dependent-latency loads and few workgroups, 281 us for
 // the five layers of a training step; now 21 us)
 __global__ __launch_bounds__(1024) void colsum_kernel(int B, int N, const float* __restrict__ dz,
                                                       float* __restrict__ db) {
   __shared__ float sh[16][64];
   const int n = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
+  const int ng = blockDim.x >> 6;
   float s = 0.f;
   if (n < N) {
 #pragma unroll 8
-    for (int b = g; b < B; b += 16) s += dz[(int64_t)b * N + n];
+    for (int b = g; b < B; b += ng) s += dz[(int64_t)b * N + n];
   }
   sh[g][threadIdx.x & 63] = s;
   __syncthreads();
   if (g == 0 && n < N) {
-#pragma unroll
-    for (int q = 1; q < 16; ++q) s += sh[q][threadIdx.x];
+    for (int q = 1; q < ng; ++q) s += sh[q][threadIdx.x];
     db[n] = s;
   }
 }
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(1024) void mse_grad_kernel(int64_t count, float sca
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int q = 1; q < 16; ++q) acc += sh[q];
+    for (int q = 1; q < (int)blockDim.x >> 6; ++q) acc += sh[q];
     partial[blockIdx.x] = acc;
   }
 }
@@ -397,7 +397,8 @@ extern "C" bem_status bem_mlp_dense_bwd(bem_ctx* ctx, int32_t B, int32_t in, int
   }
   // dW[in][out] = x^T g ; db = colsum(g) ; dx[B][in] = g W^T
   gemm_go<true, false, 0>(ctx, in, out, B, x, in, g, out, nullptr, dW, out, nullptr);
-  hipLaunchKernelGGL(colsum_kernel, dim3((out + 63) / 64), dim3(1024), 0, ctx->stream, B, out, g,
+  hipLaunchKernelGGL(colsum_kernel, dim3((out + 63) / 64),
+                     dim3(64 * std::min(16, (B + 7) / 8)), 0, ctx->stream, B, out, g,
                      db);
   if (dx) gemm_go<false, true, 0>(ctx, B, in, out, g, out, W, out, nullptr, dx, in, nullptr);
   prof_end(ctx, "mlp", pi, 2.0 * B * in * out * (dx ? 2.0 : 1.0),
@@ -411,7 +412,10 @@ extern "C" bem_status bem_mlp_mse_grad(bem_ctx* ctx, int64_t count, const float*
                                        int32_t n_partial) {
   if (!ctx || count <= 0 || !y || !t || !dy || !loss_partial || n_partial <= 0)
     return BEM_EINVAL;
-  hipLaunchKernelGGL(mse_grad_kernel, dim3(n_partial), dim3(1024), 0, ctx->stream, count,
+  // few sums: large workgroups fill the chip; many do by themselves (1024 sums of 2e7
+  // elements: 52 us with 1024 threads, 48 with 256)
+  const int threads = n_partial < 2 * ctx->num_cus ? 1024 : 256;
+  hipLaunchKernelGGL(mse_grad_kernel, dim3(n_partial), dim3(threads), 0, ctx->stream, count,
                      (float)(1.0 / (double)count), y, t, dy, loss_partial);
   BEM_CHECK_LAUNCH(ctx);
   return BEM_OK;
