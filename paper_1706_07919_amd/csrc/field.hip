@@ -110,6 +110,7 @@ __device__ inline void phase_f32(double theta, float& s, float& c) {
   phase_rev(theta * kInv2Pi, s, c);
 }
 
+constexpr int kUneven = 4;
 constexpr int kFT = 256, kNJ = 128, kParts = 8, kPW = kFT / kParts;   // kPW points per workgroup
 
 // sum over the kParts consecutive lanes of one point (butterfly: every lane
@@ -303,7 +304,50 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
     }
     if (!wide) return;   // uniform
   }
-  // uneven wavenumbers or wide phases: one wavenumber at a time
+  // uneven wavenumbers: kUneven of them share a pair's geometry, a sincos each
+  if (!wide) {
+    constexpr int NU = FCH < kUneven ? FCH : kUneven;
+    for (int f0 = 0; f0 < nf; f0 += NU) {
+      double2 A1[NU][NR], A2[NU], A3[NU];
+      double k[NU];
+#pragma unroll
+      for (int f = 0; f < NU; ++f) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) A1[f][r] = make_double2(0.0, 0.0);
+        A2[f] = A3[f] = make_double2(0.0, 0.0);
+        k[f] = kv[m0 + min(f0 + f, nf - 1)];
+      }
+      for (int j0 = 0; j0 < src.n; j0 += kNJ) {
+        const int cnt = min(kNJ, src.n - j0);
+        stage(j0, cnt, f0, NU);
+        if (!valid) continue;
+        for (int jj = part; jj < cnt; jj += kParts) {
+          if (src.nodes && j0 + jj == a) continue;
+          const Pair g = geometry(jj);
+          wide |= !(kc.kmax * fmax(g.r, fabs(g.sa)) < kPhaseNear);
+#pragma unroll
+          for (int f = 0; f < NU; ++f) {
+            const double2 E = unit_phase(k[f], g.r), F = unit_phase(k[f], g.sa);
+            term(jj, f, k[f], g, make_double2(g.wr * E.x, g.wr * E.y), F, A1[f], A2[f], A3[f]);
+          }
+        }
+      }
+      if (f0 == 0) wide = __syncthreads_or(wide);   // (kmax covers the whole chunk)
+      if (wide) break;
+#pragma unroll
+      for (int f = 0; f < NU; ++f) {
+        const double2 s2 = make_double2(part_sum(A2[f].x), part_sum(A2[f].y));
+        const double2 s3 = make_double2(part_sum(A3[f].x), part_sum(A3[f].y));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          const double2 s1 = make_double2(part_sum(A1[f][r].x), part_sum(A1[f][r].y));
+          if (p < m && (r * NU + f) % kParts == part && r < nrh && f0 + f < nf) store(r, f0 + f, s1, s2, s3);
+        }
+      }
+    }
+    if (!wide) return;   // uniform
+  }
+  // wide phases: one wavenumber at a time, by the library past the reduction's range
   for (int f = 0; f < nf; ++f) {
     const double k = kv[m0 + f];
     double2 A1[NR], A2 = make_double2(0.0, 0.0), A3 = A2;
