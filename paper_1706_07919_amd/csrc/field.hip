@@ -381,10 +381,19 @@ __global__ __launch_bounds__(kFT, 2) void field64_kernel(
 __global__ void used_nodes_kernel(int m, const int32_t* __restrict__ i0,
                                   const uint8_t* __restrict__ inside, int32_t* __restrict__ flag,
                                   int32_t* __restrict__ count, int32_t* __restrict__ list) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= m || inside[p]) return;
-  const int a = i0[p];
-  if (flag[a] == 0 && atomicExch(&flag[a], 1) == 0) list[atomicAdd(count, 1)] = a;
+  const int p = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63;
+  const bool valid = p < m && !inside[p];
+  const int a = valid ? i0[p] : -1;
+  // neighbouring points share their node: one lane of a wave asks for each (one lane a
+  // point put 20000 atomics on 12 nodes: 173 us, now 4)
+  unsigned long long todo = __ballot(valid);
+  while (todo) {
+    const int l = __ffsll(todo) - 1;
+    const int node = __builtin_amdgcn_readlane(a, l);
+    todo &= ~__ballot(a == node);
+    if (lane == l && flag[node] == 0 && atomicExch(&flag[node], 1) == 0)
+      list[atomicAdd(count, 1)] = node;
+  }
 }
 
 // ---------------------------------------------------------------- grouped field
