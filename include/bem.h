@@ -300,7 +300,10 @@ bem_status bem_solve_chief(bem_ctx* ctx, const bem_surface* s, int32_t n_k, cons
  *   int32: row i was interchanged with row piv[i] (absolute, 0-based).
  *   info[batch] [dev] int32: 0, or 1 + index of the first exactly-zero pivot.
  *   nb = block width (0 = the width measured by bem_autotune_lu for this size
- *   class, else 512 for n >= 4096 and 256 below; at most 1024 is used), gemm_kind
+ *   class and amount of work, else 512 for n >= 4096 and below that 64, 128 or 256 for
+ *   fewer than 24 Mi, fewer than 80 Mi or more matrix entries (n^2 batch); at most
+ *   1024 is used).  With nb = 0 the factors of a matrix can therefore differ in their
+ *   last bits between batches.  gemm_kind
  *   (bem_gemm_kind) the complex GEMM form of the trailing updates for c64
  *   (ignored for c128).  n * ld must stay below 2^31.
  * bem_getrs_batched: X = A^{-1} B for n_rhs vectors per matrix:
@@ -316,14 +319,15 @@ bem_status bem_getrs_batched(bem_ctx* ctx, bem_prec prec, int32_t n, int32_t ld,
 /* Plan of the factorisation measured on this device: factors `batch`
  * pseudo-random n x n matrices (diagonally dominant, deterministic) of the
  * given precision and GEMM form once per candidate block width (a
- * 0-terminated list [host], or NULL for 256, 384, 512, 768, 1024) and, for
+ * 0-terminated list [host], or NULL for 64, 128, 256, 384, 512, 768, 1024) and, for
  * the float32 MFMA forms (BEM_GEMM_4M, BEM_GEMM_3M), per GEMM shape: 128 x 64
  * tiles for updates of up to 64 or up to 128 columns (128 x 128 above), and
  * one workgroup per tile or persistent workgroups drawing tiles from per-XCD
  * counters; best of two runs each.  The fastest plan is kept in the context
  * for every later factorisation of that precision, GEMM form and size class
- * (n rounded up to 512) whose caller passes nb = 0 (the GEMM shape applies
- * whatever nb the caller passes).  best_nb, best_ms [host] may be NULL.
+ * (n rounded up to 512): its width where the caller passes nb = 0 and the matrix
+ * entries lie between the same two borders of the default widths (above), its GEMM
+ * shape for all.  best_nb, best_ms [host] may be NULL.
  * Allocates batch * n * ld elements for the duration of the call (BEM_ENOMEM
  * if they do not fit); synchronises the stream. */
 bem_status bem_autotune_lu(bem_ctx* ctx, bem_prec prec, int32_t n, int32_t batch,
@@ -337,12 +341,12 @@ bem_status bem_autotune_lu(bem_ctx* ctx, bem_prec prec, int32_t n, int32_t batch
 int32_t bem_autotune_lu_results(bem_ctx* ctx, int32_t max, int32_t* nb, int32_t* narrow_max,
                                 int32_t* persistent, double* ms);
 /* Sets the plan of a size class by hand (as bem_autotune_lu would keep it):
- * block width nb > 0, 128 x 64 GEMM tiles up to narrow_max columns (64 ..
+ * block width nb > 0 for every amount of work, 128 x 64 GEMM tiles up to narrow_max columns (64 ..
  * 1024), persistent GEMM launches 0/1.  Drops the context's captured
  * factorisations. */
 bem_status bem_lu_set_plan(bem_ctx* ctx, bem_prec prec, int32_t n, int32_t gemm_kind, int32_t nb,
                            int32_t narrow_max, int32_t persistent);
-/* The plan bem_autotune_lu (or bem_lu_set_plan) kept for (prec, gemm_kind,
+/* The plan bem_autotune_lu (or bem_lu_set_plan) kept last for (prec, gemm_kind,
  * size class of n); EINVAL if none.  Outputs [host] may be NULL. */
 bem_status bem_lu_tuned_plan(bem_ctx* ctx, bem_prec prec, int32_t n, int32_t gemm_kind,
                              int32_t* nb, int32_t* narrow_max, int32_t* persistent);

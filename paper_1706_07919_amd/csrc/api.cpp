@@ -509,8 +509,9 @@ extern "C" bem_status bem_lu_set_plan(bem_ctx* ctx, bem_prec prec, int32_t n, in
       (persistent != 0 && persistent != 1))
     return fail(ctx, BEM_EINVAL, "bem_lu_set_plan: bad argument");
   drop_graphs(ctx);
-  ctx->tuned[{(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512}] =
-      bem_ctx::TunedPlan{nb, narrow_max, persistent};
+  bem_ctx::TunedSize& t = ctx->tuned[{(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512}];
+  t.last = bem_ctx::TunedPlan{nb, narrow_max, persistent};
+  std::fill(t.nb, t.nb + 3, nb);
   return BEM_OK;
 }
 
@@ -520,9 +521,10 @@ extern "C" bem_status bem_lu_tuned_plan(bem_ctx* ctx, bem_prec prec, int32_t n, 
   const auto it = ctx->tuned.find({(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512});
   if (it == ctx->tuned.end())
     return fail(ctx, BEM_EINVAL, "bem_lu_tuned_plan: no measured plan for this size class");
-  if (nb) *nb = it->second.nb;
-  if (narrow_max) *narrow_max = it->second.narrow_max;
-  if (persistent) *persistent = it->second.persistent;
+  const bem_ctx::TunedPlan& plan = it->second.last;
+  if (nb) *nb = plan.nb;
+  if (narrow_max) *narrow_max = plan.narrow_max;
+  if (persistent) *persistent = plan.persistent;
   return BEM_OK;
 }
 

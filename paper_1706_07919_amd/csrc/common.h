@@ -38,7 +38,13 @@ struct bem_ctx {
   struct TunedPlan {
     int nb, narrow_max, persistent;
   };
-  std::map<std::pair<int, int>, TunedPlan> tuned;
+  // by precision and GEMM form, and size class; the width by the work class
+  // (lu_work_class) it was measured at, the GEMM shape for all
+  struct TunedSize {
+    TunedPlan last;
+    int nb[3] = {0, 0, 0};   // 0: the default
+  };
+  std::map<std::pair<int, int>, TunedSize> tuned;
   // every candidate of the last bem_autotune_lu call and its time (ms)
   std::vector<std::pair<TunedPlan, double>> tune_log;
   int num_cus = 256;
@@ -161,6 +167,8 @@ bem_status lu_solve(bem_ctx*, bem_prec, int n, int64_t ld, int64_t stride, int b
 // bem_autotune_lu has run for the size class, else the default for the largest n
 // and the entries (n^2, summed) of the matrices factored together
 int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int64_t entries);
+// the classes of work at which the default width differs (0, 1 or 2)
+int lu_work_class(int n, int64_t entries);
 // a factorisation's plan: block width nb (> 0) or the measured / default one,
 // and the measured GEMM tile threshold and launch form when the context has
 // them for this size class

@@ -2417,21 +2417,26 @@ struct Fac {
 
 }  // namespace
 
-static int lu_default_nb(int n, int64_t entries) {
+int lu_work_class(int n, int64_t entries) {
   // few matrix entries in all: the chain through the launches of a block counts,
   // and narrow blocks shorten it (64 against 256 columns: 8 matrices of n = 642 take
   // 1.65 against 2.12 ms, 8 of 1284 in float64 6.0 against 6.9; 128 against 256: 32 of
   // 1284 6.5 against 6.7 ms, 8 of 2562 13.1 against 13.6).  With more the trailing
   // updates do, which wide blocks run deeper and with less traffic (512 of 1284: 57,
   // 50 and 45 ms with 64, 128 and 256; 64 of 5124: 177 and 167 ms with 256 and 512).
-  if (n < 4096 && entries < 24 * 1024 * 1024) return kSwapRows / 4;
-  if (n < 4096 && entries < 80 * 1024 * 1024) return kSwapRows / 2;
-  return n >= 4096 ? 2 * kSwapRows : kSwapRows;
+  if (n < 4096 && entries < 24 * 1024 * 1024) return 0;
+  if (n < 4096 && entries < 80 * 1024 * 1024) return 1;
+  return 2;
+}
+static int lu_default_nb(int n, int64_t entries) {
+  const int c = lu_work_class(n, entries);
+  return c == 0 ? kSwapRows / 4 : c == 1 ? kSwapRows / 2 : n >= 4096 ? 2 * kSwapRows : kSwapRows;
 }
 
 int lu_plan_nb(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int64_t entries) {
   const auto it = ctx->tuned.find({(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512});
-  return it != ctx->tuned.end() ? it->second.nb : lu_default_nb(n, entries);
+  const int nb = it != ctx->tuned.end() ? it->second.nb[lu_work_class(n, entries)] : 0;
+  return nb > 0 ? nb : lu_default_nb(n, entries);
 }
 
 LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb, int64_t entries) {
@@ -2439,8 +2444,8 @@ LuPlan lu_plan_for(bem_ctx* ctx, bem_prec prec, int gemm_kind, int n, int nb, in
   plan.nb = nb > 0 ? nb : lu_plan_nb(ctx, prec, gemm_kind, n, entries);
   const auto it = ctx->tuned.find({(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512});
   if (it != ctx->tuned.end()) {
-    plan.gemm_narrow_max = it->second.narrow_max;
-    plan.gemm_persistent = it->second.persistent;
+    plan.gemm_narrow_max = it->second.last.narrow_max;
+    plan.gemm_persistent = it->second.last.persistent;
   }
   return plan;
 }
@@ -2557,7 +2562,7 @@ __global__ void tune_fill_kernel(int n, int64_t ld, int64_t stride, int batch, C
 
 bem_status lu_autotune(bem_ctx* ctx, bem_prec prec, int n, int batch, int gemm_kind,
                        const int32_t* candidates, int32_t* best_nb, double* best_ms) {
-  static const int32_t kDefault[] = {256, 384, 512, 768, 1024, 0};
+  static const int32_t kDefault[] = {64, 128, 256, 384, 512, 768, 1024, 0};   // (the default widths among them)
   const int32_t* cand = candidates ? candidates : kDefault;
   const int64_t ld = (n + 15) / 16 * 16, stride = (int64_t)n * ld;
   const size_t esz = prec == BEM_C128 ? 16 : 8;
@@ -2622,8 +2627,9 @@ bem_status lu_autotune(bem_ctx* ctx, bem_prec prec, int n, int batch, int gemm_k
   (void)hipFree(A);
   if (st != BEM_OK) return st;
   if (best == 0) return fail(ctx, BEM_EINVAL, "autotune: no candidate block width");
-  ctx->tuned[{(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512}] =
-      bem_ctx::TunedPlan{best, best_narrow, best_persist};
+  bem_ctx::TunedSize& t = ctx->tuned[{(int)prec * 16 + gemm_kind, (n + 511) / 512 * 512}];
+  t.last = bem_ctx::TunedPlan{best, best_narrow, best_persist};
+  t.nb[lu_work_class(n, (int64_t)n * n * batch)] = best;
   if (best_nb) *best_nb = best;
   if (best_ms) *best_ms = bms;
   return BEM_OK;
