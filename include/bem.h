@@ -56,8 +56,11 @@ void bem_ctx_destroy(bem_ctx* ctx);
 /* Message of the last failed call on this context ("" if none). */
 const char* bem_last_error(const bem_ctx* ctx);
 /* Upper bound (bytes) of device workspace bem_solve_batched may hold; 0 = 75%
- * of the free device memory at the time of the call.  A nonzero limit also caps
- * the packing buffer of BEM_GEMM_3M and BEM_GEMM_BF16X3 factorisations at a quarter of it. */
+ * of the free device memory at the time of the call.  The packing buffer of
+ * BEM_GEMM_3M factorisations (split operands, bem_gemm_kind) counts as workspace and
+ * takes at most a quarter of a nonzero limit; where the workspace leaves it no room,
+ * those factorisations run without it.  The buffer of BEM_GEMM_BF16X3 comes on top, at
+ * most a quarter of the limit. */
 bem_status bem_ctx_set_workspace_limit(bem_ctx* ctx, uint64_t bytes);
 
 /* Per-kernel accounting for roofline reports.  With profiling on, each launch

@@ -203,6 +203,26 @@ bem_status check_k(bem_ctx* ctx, int n_k, const double* k) {
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Most bytes of workspace a solve may take: the set limit, or three quarters of the
+// memory that is free or the context's (its packing buffer counted as taken); asked for
+// only where `need` does not fit what the context holds anyway.
+bem_status workspace_limit(bem_ctx* ctx, size_t need, size_t* limit) {
+  *limit = ctx->ws_limit ? ctx->ws_limit : (size_t)(0.75 * (double)ctx->ws_size);
+  if (ctx->ws_limit || need <= *limit) return BEM_OK;
+  size_t free_b = 0, total_b = 0;
+  BEM_HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
+  const size_t share = (size_t)(0.75 * (double)(free_b + ctx->ws_size + ctx->pack_size));
+  *limit = share - std::min(share, ctx->pack_size);
+  return BEM_OK;
+}
+// Gives the packing buffer back where it would hold more than a set limit together with
+// a workspace of `bytes` (bfloat16 words may come on top).
+void make_room(bem_ctx* ctx, size_t bytes, int mode) {
+  if (ctx->ws_limit && mode != BEM_FP32_IR_B3 && ctx->pack_size > 0 &&
+      std::max(bytes, ctx->ws_size) + ctx->pack_size > ctx->ws_limit)
+    release_pack(ctx);
+}
+
 struct Chunk {
   // device buffers of one chunk of kc wavenumbers (n nodes, nr right-hand sides)
   void* A;         // [kc][n][ld] c64 or c128
@@ -819,14 +839,11 @@ extern "C" bem_status bem_solve_batched(bem_ctx* ctx, const bem_problem* probs, 
     return s;
   };
   // (the free memory is asked for only where the limit it gives could bind)
-  size_t limit = ctx->ws_limit ? ctx->ws_limit : (size_t)(0.75 * (double)ctx->ws_size);
-  if (!ctx->ws_limit && round_bytes(1) > limit) {
-    size_t free_b = 0, total_b = 0;
-    BEM_HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
-    limit = (size_t)(0.75 * (double)(free_b + ctx->ws_size));
-  }
+  size_t limit = 0;
+  if ((st = workspace_limit(ctx, round_bytes(1), &limit)) != BEM_OK) return st;
   int rounds = 1;
   while (rounds < max_nk && round_bytes(rounds) > limit) rounds = std::min(max_nk, rounds * 2);
+  make_room(ctx, std::max(round_bytes(rounds), fallback_bytes), o.mode);
   void* ws = nullptr;
   if ((st = workspace(ctx, std::max(round_bytes(rounds), fallback_bytes), &ws)) != BEM_OK) return st;
   LuPlan plan;
@@ -1236,12 +1253,12 @@ extern "C" bem_status bem_solve_quadratic(bem_ctx* ctx, const bem_quad_surface* 
     (void)quad_carve(nullptr, n, ld, nr, kc, c128f, &used);
     return used + setup + 256;
   };
-  size_t free_b = 0, total_b = 0;
-  BEM_HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
-  const size_t limit = ctx->ws_limit ? ctx->ws_limit : (size_t)(0.75 * (double)(free_b + ctx->ws_size));
+  size_t limit = 0;
+  if ((st = workspace_limit(ctx, SIZE_MAX, &limit)) != BEM_OK) return st;
   int kc = n_k;
   // the residual grid holds a chunk's kc * n_rhs vectors in its y dimension
   while (kc > 1 && (bytes(kc, true) > limit || (int64_t)kc * n_rhs > 65535)) kc = (kc + 1) / 2;
+  make_room(ctx, bytes(kc, true), o.mode);
   void* ws = nullptr;
   if ((st = workspace(ctx, bytes(kc, true), &ws)) != BEM_OK) return st;
   double* qp = nullptr;

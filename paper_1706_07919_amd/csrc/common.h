@@ -160,6 +160,7 @@ bem_status lu_factor_groups(bem_ctx*, bem_prec, const std::vector<LuMatrixSet>& 
 bem_status lu_factor_groups_graph(bem_ctx*, bem_prec, const std::vector<LuMatrixSet>& sets,
                                   const LuPlan& plan, int gemm_kind);
 void drop_graphs(bem_ctx* ctx);
+void release_pack(bem_ctx* ctx);
 // Solve A_b X = B_b in place for B_b = B + b*bstride (n_rhs vectors of length n, stride n).
 bem_status lu_solve(bem_ctx*, bem_prec, int n, int64_t ld, int64_t stride, int batch,
                     const void* LU, const int32_t* piv, int n_rhs, void* B, int64_t bstride);

@@ -2486,26 +2486,53 @@ static bem_status build_fac(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
   return BEM_OK;
 }
 
-// Grow the context's packing buffer towards what the factorisation would use
-// (at most pack_cap); on allocation failure the buffer stays empty and the
-// trailing updates take the unpacked kernel.
-static size_t pack_cap(const bem_ctx* ctx) {
-  return ctx->ws_limit ? std::min<size_t>(kPackLimit, ctx->ws_limit / 4) : kPackLimit;
+// Most bytes of packing buffer a factorisation may use.  The split words of the 3M form
+// share a set limit with the workspace; those of bfloat16 come on top of it.
+static size_t pack_cap(const bem_ctx* ctx, int gkind) {
+  if (!ctx->ws_limit) return kPackLimit;
+  const size_t cap = std::min<size_t>(kPackLimit, ctx->ws_limit / 4);
+  return gkind == kGemmBf16x3 ? cap : std::min(cap, ctx->ws_limit - std::min<size_t>(ctx->ws_limit, ctx->ws_size));
 }
-static void reserve_pack(bem_ctx* ctx, const Fac& f, int nb) {
-  const size_t want = std::min(f.pack_need(nb), pack_cap(ctx));
-  if (want <= ctx->pack_size) return;
+// Waits for the stream and gives the buffer back (captured factorisations point
+// into it).
+void release_pack(bem_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
-  drop_graphs(ctx);   // captured factorisations point into the old buffer
+  drop_graphs(ctx);
   if (ctx->pack) (void)hipFree(ctx->pack);
   ctx->pack = nullptr;
   ctx->pack_size = 0;
-  if (hipMalloc(&ctx->pack, want) != hipSuccess) {
+}
+// Grow the context's packing buffer towards what the factorisation would use (at most
+// pack_cap, and without a limit what three quarters of the memory leave beside the
+// workspace).  A buffer that cannot grow stays as it is, and larger batches are
+// packed in slices; without one the updates take the unpacked kernels.
+static void reserve_pack(bem_ctx* ctx, const Fac& f, int nb) {
+  size_t want = std::min(f.pack_need(nb), pack_cap(ctx, f.gkind));
+  if (want <= ctx->pack_size) return;
+  if (!ctx->ws_limit) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    const size_t share = (size_t)(0.75 * (double)(free_b + ctx->ws_size + ctx->pack_size));
+    const size_t room = share - std::min(share, ctx->ws_size);
+    // (no regrowth by small steps where memory is short)
+    if (room < want && room < 2 * ctx->pack_size) return;
+    want = std::min(want, room);
+    if (want == 0) return;
+  }
+  const size_t had = ctx->pack_size;
+  release_pack(ctx);
+  for (const size_t bytes : {want, had}) {
+    if (bytes == 0) break;
+    if (hipMalloc(&ctx->pack, bytes) == hipSuccess) {
+      ctx->pack_size = bytes;
+      return;
+    }
     (void)hipGetLastError();
     ctx->pack = nullptr;
-    return;
   }
-  ctx->pack_size = want;
 }
 
 static bool capturing(hipStream_t s) {
@@ -2531,7 +2558,7 @@ bem_status lu_factor_groups(bem_ctx* ctx, bem_prec prec, const std::vector<LuMat
     if (!cap) reserve_pack(ctx, f, nb);
     if (!cap || ctx->stream == ctx->capture_stream || f.gkind == kGemmBf16x3) {
       f.pack = ctx->pack;
-      f.pack_bytes = std::min(ctx->pack_size, pack_cap(ctx));
+      f.pack_bytes = std::min(ctx->pack_size, pack_cap(ctx, f.gkind));
     }
   }
   f.blocked(nb);

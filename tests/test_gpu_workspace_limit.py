@@ -1,0 +1,70 @@
+"""A set limit bounds what the default solve holds, its packing buffer included: in
+one call, and after a factorisation that had the whole limit to itself."""
+import numpy as np
+import pytest
+
+from workloads import Body, HARD
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+native = pytest.importorskip("paper_1706_07919_amd.native")
+from paper_1706_07919_amd import DeviceSurface  # noqa: E402
+
+MIB = 1 << 20
+GRAIN = 8 * MIB   # what the device's allocations are rounded up to, a few of them
+
+
+@pytest.fixture(scope="module")
+def problem():
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    ds = DeviceSurface.from_bodies([Body((0.0, 0.0, z), 1.0, 1.0, 3, HARD) for z in (0.0, 3.0)])
+    k = torch.as_tensor(np.linspace(0.3, 4.0, 40)).cuda()
+    y = torch.empty((40, 1, ds.n), dtype=torch.complex128, device="cuda")
+    ctx = native.Context(0)
+    native.bem_incident(ctx, ds.struct, 40, k, (0.0, 0.0, 1.0), y)
+    solve(ctx, (ds, k, y), native.BEM_FP32_IR_3M)   # (loads every kernel)
+    ctx.close()
+    return ds, k, y
+
+
+def solve(ctx, problem, mode):
+    ds, k, y = problem
+    opts = native.bem_solve_opts_default()
+    opts.mode = mode
+    x = torch.zeros_like(y)
+    native.bem_solve_batched(ctx, [(ds.struct, len(k), k, 1, y)], opts, [x])
+    torch.cuda.synchronize()
+    return x
+
+
+def free_bytes():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("factor_first", [False, True])
+@pytest.mark.parametrize("spare", [0, 40 * MIB])
+def test_limit_holds_workspace_and_packing(problem, factor_first, spare):
+    ref = solve(native.Context(0), problem, native.BEM_FP32_IR_4M)
+    n = problem[0].n
+    A = torch.eye(n, dtype=torch.complex64, device="cuda").repeat(8, 1, 1).contiguous()
+    piv = torch.zeros((8, n), dtype=torch.int32, device="cuda")
+    info = torch.ones(8, dtype=torch.int32, device="cuda")
+    plain, ctx = native.Context(0), native.Context(0)
+    f0 = free_bytes()
+    solve(plain, problem, native.BEM_FP32_IR_4M)   # one round's workspace, no packing
+    limit = f0 - free_bytes() + spare
+    plain.close()
+    f0 = free_bytes()
+    ctx.set_workspace_limit(limit)
+    if factor_first:
+        native.bem_getrf_batched(ctx, native.BEM_C64, n, n, n * n, 8, A, piv, info, 0, native.BEM_GEMM_3M)
+    held, x = [], []
+    for _ in range(2):
+        x.append(solve(ctx, problem, native.BEM_FP32_IR_3M))
+        held.append(f0 - free_bytes())
+    ctx.close()
+    # (compared when everything is measured: torch loads the code of its own kernels)
+    assert max(held) <= limit + GRAIN
+    assert all((v - ref).norm() <= 1e-9 * ref.norm() for v in x)
