@@ -2681,19 +2681,23 @@ bem_status lu_factor_groups_graph(bem_ctx* ctx, bem_prec prec, const std::vector
     key.push_back(m.n);
     key.push_back(m.count);
   }
-  for (auto& g : ctx->lu_graphs)
-    if (g.key == key) {
-      BEM_HIP_TRY(ctx, hipGraphLaunch(g.exec, ctx->stream));
-      return BEM_OK;
-    }
   {
-    // the packing buffer must exist before capture (no allocation while capturing)
+    // The packing buffer must exist before capture (no allocation while capturing), and
+    // what a factorisation may use of it decides its launches: 3M updates are other
+    // arithmetic without it, so a graph is replayed only where an eager call would
+    // use the same.
     Fac f;
     int nb = 0;
     const bem_status st = build_fac(ctx, prec, sets, plan, gemm_kind, f, nb);
     if (st != BEM_OK) return st;
     if (!f.groups.empty() && f.use_pack) reserve_pack(ctx, f, nb);
+    key.push_back(f.use_pack ? (int64_t)std::min(ctx->pack_size, pack_cap(ctx, f.gkind)) : 0);
   }
+  for (auto& g : ctx->lu_graphs)
+    if (g.key == key) {
+      BEM_HIP_TRY(ctx, hipGraphLaunch(g.exec, ctx->stream));
+      return BEM_OK;
+    }
   if (!ctx->capture_stream)
     BEM_HIP_TRY(ctx, hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
   // record the launch sequence on the side stream (nothing executes), then

@@ -1,0 +1,43 @@
+"""Captured factorisations with f16 split updates: every replay is the eager solve bit
+for bit, with eager work between the replays, and also after the workspace limit took
+the packing buffer away and gave it back."""
+import numpy as np
+import pytest
+
+from workloads import Body, HARD
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+native = pytest.importorskip("paper_1706_07919_amd.native")
+from paper_1706_07919_amd import DeviceSurface  # noqa: E402
+
+
+@pytest.mark.parametrize("mode", [native.BEM_FP32_IR_3M, native.BEM_FP32_IR_B3])
+def test_replays_follow_the_limit(mode):
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    ctx = native.Context(0)
+    ds = DeviceSurface.from_bodies([Body((0.0, 0.0, z), 1.0, 1.0, 3, HARD) for z in (0.0, 3.0)])
+    k = torch.tensor([1.7], dtype=torch.float64).cuda()   # (one wavenumber: one round at any limit)
+    y = torch.empty((1, 1, ds.n), dtype=torch.complex128, device="cuda")
+    native.bem_incident(ctx, ds.struct, 1, k, (0.0, 0.0, 1.0), y)
+
+    def factors(use_graph):
+        opts = native.bem_solve_opts_default()
+        # (a loose tolerance keeps the first sweep's solution, which shows the factors' bits)
+        opts.mode, opts.use_graph, opts.tol_step = mode, use_graph, 1e-2
+        x = torch.zeros_like(y)
+        native.bem_solve_batched(ctx, [(ds.struct, 1, k, 1, y)], opts, [x])
+        return torch.view_as_real(x).cpu().numpy()
+
+    seen = []
+    for limit in (0, 1 << 20, 0, 1 << 20):
+        ctx.set_workspace_limit(limit)
+        replays = [factors(1) for _ in range(3)]
+        seen.append(factors(0))
+        replays.append(factors(1))
+        assert all(np.array_equal(r, seen[-1]) for r in replays), limit
+    ctx.close()
+    assert np.array_equal(seen[0], seen[2]) and np.array_equal(seen[1], seen[3])
+    # float32 3M products without the buffer; the bfloat16 forms agree bit for bit
+    assert np.array_equal(seen[0], seen[1]) == (mode == native.BEM_FP32_IR_B3)
