@@ -35,7 +35,7 @@ PEAK_HBM = 8.0e12
 # dominant kernel of the factorisation per GEMM form: (stats name, kernel,
 # issued MFMA flops per 4M-equivalent flop, MFMA peak)
 DOMINANT = {
-    "3m": ("gemm_f16x3", "gemm_c32_split_kernel<f16> (LU updates of at least 1024 x 1024, float32 "
+    "3m": ("gemm_f16x3", "gemm_c32_split_kernel<f16> (large LU updates, float32 "
                          "products as three f16 MFMA products of split, scaled operands)", 3.0,
            PEAK_BF16_MFMA),
     "4m": ("gemm_c32", "gemm_c32_lds_kernel<4M, 128x128> (LU trailing updates, complex 4M on "

@@ -70,8 +70,8 @@ bem_status bem_ctx_set_workspace_limit(bem_ctx* ctx, uint64_t bytes);
  * was last switched (set_profiling resets them).  Kernel names: "gemm_c32" and
  * "gemm_3m" (float32 4M / 3M updates of at least 65 columns), "gemm_c32_narrow" and
  * "gemm_3m_narrow" (17 to 64 columns), "gemm_c32_unaligned" and "gemm_3m_unaligned"
- * (operands not 16-byte aligned), "gemm_f16x3" (3M updates
- * of at least 1024 x 1024 on split operands), "gemm_b3", "gemm_b3_narrow", "gemm_b3_packed",
+ * (operands not 16-byte aligned), "gemm_f16x3" (large 3M
+ * updates, on split operands), "gemm_b3", "gemm_b3_narrow", "gemm_b3_packed",
  * "gemm_small", "pack", "gemm_c64", "panel", "laswp", "trsm", "assemble", "residual",
  * "getrs", "field", "synth".
  * For "assemble"/"residual" the flop slot counts node pairs and for "field"
@@ -182,8 +182,8 @@ bem_status bem_residual_check(bem_ctx* ctx, const bem_surface* s, int32_t n_k, c
  *   BEM_FP32_IR_4M  : c64 LU (complex GEMM as 4 real products, float32
  *                     accumulation) + iterative refinement with the
  *                     float64 matrix-free residual, until ||dx||/||x|| <= tol_step
- *   BEM_FP32_IR_3M  : as 4M with the 3-product complex GEMM and, for updates of
- *                     at least 1024 x 1024, f16x3 split products (bem_gemm_kind)
+ *   BEM_FP32_IR_3M  : as 4M with the 3-product complex GEMM and, for large
+ *                     updates, f16x3 split products (bem_gemm_kind)
  *   BEM_FP32_IR_B3  : as 4M with every real product of the GEMM taken as three
  *                     bfloat16 MFMA products of the split operands
  *                     (x = hi + lo; hi hi + hi lo + lo hi, float32 accumulation)
@@ -200,9 +200,9 @@ typedef enum {
 
 /* complex GEMM form of a c64 factorisation (last argument of bem_getrf_batched).
  * BEM_GEMM_4M and BEM_GEMM_3M: four or three float32 MFMA products per complex
- * one.  BEM_GEMM_3M runs its updates of at least 1024 x 1024 on MFMA f16, every
- * real product as three products of operands split into f16 pairs and scaled by
- * powers of two.  An update's error is at most (3 2^-22 + 2^-24) |L||U|, entry by
+ * one.  BEM_GEMM_3M runs its large updates (at least 1024 x 1024 of a depth of
+ * 256, at least 1536 x 1536 of a depth of 128) on MFMA f16, every real product as
+ * three products of operands split into f16 pairs and scaled by powers of two.  An update's error is at most (3 2^-22 + 2^-24) |L||U|, entry by
  * entry, besides its float32 accumulation (typically 2^-23.5; on Gaussian and
  * boundary-integral matrices below that of the float32 3M products); a matrix whose
  * entries span too wide a range for that takes the update in float32 MFMA products.

@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(256) void pack_b_kernel(LuGroups G, int rowB, int c
 }
 
 // ============================================================== float32 products on f16 MFMA
-// The 3M form takes its updates of at least 1024 x 1024 as three f16 MFMA products
+// The 3M form takes its large updates (Fac::pack_min) as three f16 MFMA products
 // per real product (four of those per complex one): x = hi + lo with
 // hi = f16(x) and lo = f16(x - hi) keeps 22 to 24 significant bits (11 + 11 and
 // lo's sign), and x y ~ hi hi + hi lo + lo hi drops only lo lo (2^-22 of the
@@ -2260,11 +2260,16 @@ struct Fac {
     }
     return S;
   }
-  // Smallest update (rows and columns) whose operands are packed.  bfloat16
-  // words: four tiles must read each operand.  f16 words, whose scales take two
-  // more passes: eight (21 matrices of n = 1284: 12.90 ms per 3M solve either
-  // way at 1024, 13.00 from 512 on; 8 of n = 2562: 44.6 against 45.1 ms).
-  int pack_min() const { return (gkind == kGemmBf16x3 ? 4 : 8) * GB_BM; }
+  // Smallest update (rows and columns) of depth K whose operands are packed.  bfloat16
+  // words: four tiles must read each operand.  f16 words, whose scales take two more
+  // passes: eight tiles from a depth of 256 on (64 matrices of n = 1284 in 7.48 ms with
+  // and 7.60 without, 16 of 2562 in 14.9 and 16.1), twelve from 128 (8 of 2562: 11.9 and
+  // 12.2; from 1024 on 16 of 1284 took 4.63 against 4.54), none below (one of 2000 at
+  // depth 64: 5.98 against 5.69).
+  int pack_min(int K) const {
+    if (gkind == kGemmBf16x3) return 4 * GB_BM;
+    return K >= 256 ? 8 * GB_BM : K >= 128 ? 12 * GB_BM : INT_MAX;
+  }
   // packing buffer bytes that would let every trailing update run in one slice
   size_t pack_need(int nb) const {
     size_t need = 0;
@@ -2272,7 +2277,7 @@ struct Fac {
       const int e = block_end(c, nb);
       int total, maxn;
       active(e, &total, &maxn);
-      if (total == 0 || maxn - e < pack_min()) continue;
+      if (total == 0 || maxn - e < pack_min(e - c)) continue;
       need = std::max(need, (size_t)pack_words(maxn - e, maxn - e, e - c) * 16 * total);
     }
     return need;
@@ -2289,7 +2294,7 @@ struct Fac {
     if (M <= 0 || N <= 0) return true;
     // each packed operand must be read by enough tiles to repay its pass
     const bool f16 = gkind != kGemmBf16x3;
-    if (std::min(M, N) < pack_min()) return false;
+    if (std::min(M, N) < pack_min(K)) return false;
     const int tiles_m = (M + GB_BM - 1) / GB_BM, tiles_n = (N + GB_BN - 1) / GB_BN;
     const size_t per = (size_t)pack_words(M, N, K) * 16;
     const int fit = (int)std::min<size_t>((size_t)total, pack ? pack_bytes / per : 0);

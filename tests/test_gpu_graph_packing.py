@@ -25,7 +25,7 @@ def test_replays_follow_the_limit(mode):
     def factors(use_graph):
         opts = native.bem_solve_opts_default()
         # (a loose tolerance keeps the first sweep's solution, which shows the factors' bits)
-        opts.mode, opts.use_graph, opts.tol_step = mode, use_graph, 1e-2
+        opts.mode, opts.use_graph, opts.tol_step, opts.nb = mode, use_graph, 1e-2, 256
         x = torch.zeros_like(y)
         native.bem_solve_batched(ctx, [(ds.struct, 1, k, 1, y)], opts, [x])
         return torch.view_as_real(x).cpu().numpy()

@@ -59,7 +59,7 @@ def test_two_sizes_in_slices(spare):
 
 def test_callers_capture_holds_no_packing():
     assert torch.cuda.is_available(), "GPU tests need a ROCm device"
-    n, nb = 1152, 128
+    n, nb = 1290, 256
     rng = np.random.default_rng(3)
     M = torch.as_tensor(seeded_complex(rng, (2, n, n)) + n ** 0.5 * np.eye(n)).to(torch.complex64).cuda()
     A = torch.empty_like(M)

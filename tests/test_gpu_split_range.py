@@ -37,7 +37,7 @@ def matrix(rng, n, nb, form):
     return A.astype(np.complex64)
 
 
-@pytest.mark.parametrize("n,nb,pad", [(1152, 128, 0), (1089, 64, 1), (1290, 100, 0)])
+@pytest.mark.parametrize("n,nb,pad", [(1280, 256, 0), (1345, 321, 1), (1290, 264, 0), (1700, 130, 0)])
 @pytest.mark.parametrize("forms", [("graded column",), ("entry over zeros",),
                                    ("plain", "graded column", "plain", "entry over zeros")])
 def test_operands_past_the_split_keep_float32(ctx, n, nb, pad, forms):

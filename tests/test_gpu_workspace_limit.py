@@ -31,7 +31,7 @@ def problem():
 def solve(ctx, problem, mode):
     ds, k, y = problem
     opts = native.bem_solve_opts_default()
-    opts.mode = mode
+    opts.mode, opts.nb = mode, 256
     x = torch.zeros_like(y)
     native.bem_solve_batched(ctx, [(ds.struct, len(k), k, 1, y)], opts, [x])
     torch.cuda.synchronize()
@@ -59,7 +59,7 @@ def test_limit_holds_workspace_and_packing(problem, factor_first, spare):
     f0 = free_bytes()
     ctx.set_workspace_limit(limit)
     if factor_first:
-        native.bem_getrf_batched(ctx, native.BEM_C64, n, n, n * n, 8, A, piv, info, 0, native.BEM_GEMM_3M)
+        native.bem_getrf_batched(ctx, native.BEM_C64, n, n, n * n, 8, A, piv, info, 256, native.BEM_GEMM_3M)
     held, x = [], []
     for _ in range(2):
         x.append(solve(ctx, problem, native.BEM_FP32_IR_3M))
