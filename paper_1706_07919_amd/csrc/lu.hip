@@ -184,15 +184,12 @@ template <typename C, int KR, int K0, typename LM>
 __device__ __forceinline__ void trsm_quad(C (&x)[KR], const LM& L, int g) {
   using R = decltype(C::x);
   C xj[4], d = cmk<C>(R(0), R(0));
-  auto add = [](C s, C a, C b) {   // s + a b
-    return cmk<C>(fma(a.x, b.x, fma(-a.y, b.y, s.x)), fma(a.x, b.y, fma(a.y, b.x, s.y)));
-  };
   auto own = [&](auto q) {   // unknown q, and its product into the later ones of the four
     constexpr int Q = decltype(q)::value;
     const C t = g == Q ? csub(x[K0], d) : x[K0];
     xj[Q] = cmk<C>(quad_value<Q>(t.x), quad_value<Q>(t.y));
     if (g == Q) x[K0] = t;
-    if (Q < 3) d = add(d, L[4 * K0 + Q][g][K0], xj[Q]);
+    if (Q < 3) d = cfma(d, L[4 * K0 + Q][g][K0], xj[Q]);
   };
   own(std::integral_constant<int, 0>{});
   own(std::integral_constant<int, 1>{});
@@ -202,7 +199,7 @@ __device__ __forceinline__ void trsm_quad(C (&x)[KR], const LM& L, int g) {
   for (int k = K0 + 1; k < KR; ++k) {
     C s = cmk<C>(R(0), R(0));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s = add(s, L[4 * K0 + q][g][k], xj[q]);
+    for (int q = 0; q < 4; ++q) s = cfma(s, L[4 * K0 + q][g][k], xj[q]);
     x[k] = csub(x[k], s);
   }
 }

@@ -34,10 +34,9 @@ template <typename C> __device__ inline C cmul(C a, C b) {
   return cmk<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 template <typename C> __device__ inline C csub(C a, C b) { return cmk<C>(a.x - b.x, a.y - b.y); }
-// s - a b as four fused multiply-adds (one rounding per real product-sum
-// instead of a rounded product then a subtraction)
-template <typename C> __device__ inline C cfms(C s, C a, C b) {
-  return cmk<C>(fma(-a.x, b.x, fma(a.y, b.y, s.x)), fma(-a.x, b.y, fma(-a.y, b.x, s.y)));
+// s + a b as four fused multiply-adds
+template <typename C> __device__ inline C cfma(C s, C a, C b) {
+  return cmk<C>(fma(a.x, b.x, fma(-a.y, b.y, s.x)), fma(a.x, b.y, fma(a.y, b.x, s.y)));
 }
 template <typename C> __device__ inline C crecip(C a) {
   // 1/a with scaling to avoid overflow (Smith's method)

@@ -35,63 +35,53 @@ constexpr int kRhsWide = 4;    // and of a row that goes one wavenumber at a tim
 constexpr int kKc = 8;         // wavenumbers per assembly workgroup
 constexpr double kFourPiQ = 12.566370614359172953850573533118;
 
-// The rule's points and weights (weights summing to the reference area 1/2)
-// and the six shape functions with their derivatives at the points.
+// Barycentric coordinates (L0, L1, L2) of the rule's points and the six shape
+// functions there.
+struct Shapes {
+  double L[kQ][3], N[kQ][6];
+};
+constexpr double kS15 = 3.872983346207417;   // sqrt(15)
+constexpr Shapes make_shapes() {
+  Shapes S{};
+  const double as[2] = {(6.0 - kS15) / 21.0, (6.0 + kS15) / 21.0};
+  for (int q = 0; q < kQ; ++q) {
+    for (int c = 0; c < 3; ++c) {
+      const double a = q ? as[(q - 1) / 3] : 1.0 / 3.0;
+      S.L[q][c] = q && (q - 1) % 3 == c ? 1.0 - 2.0 * a : a;
+    }
+    const double L0 = S.L[q][0], L1 = S.L[q][1], L2 = S.L[q][2];
+    const double N[6] = {L0 * (2 * L0 - 1), L1 * (2 * L1 - 1), L2 * (2 * L2 - 1), 4 * L0 * L1, 4 * L1 * L2, 4 * L2 * L0};
+    for (int a = 0; a < 6; ++a) S.N[q][a] = N[a];
+  }
+  return S;
+}
+// for the kernels that index them per thread
+__device__ __constant__ Shapes kShapes = make_shapes();
+
+// The rule's weights (summing to the reference area 1/2) and the shape functions with
+// their derivatives at the points.
 struct QuadRule {
   double N[kQ][6], dxi[kQ][6], deta[kQ][6], w[kQ];
 };
 
 QuadRule make_rule() {
+  constexpr Shapes S = make_shapes();
   QuadRule R;
-  const double s15 = std::sqrt(15.0);
-  double bx[kQ], by[kQ], bz[kQ];
-  bx[0] = by[0] = bz[0] = 1.0 / 3.0;
-  R.w[0] = 0.5 * (9.0 / 40.0);
-  const double as[2] = {(6.0 - s15) / 21.0, (6.0 + s15) / 21.0};
-  const double ws[2] = {(155.0 - s15) / 1200.0, (155.0 + s15) / 1200.0};
-  for (int g = 0; g < 2; ++g) {
-    const double a = as[g], c = 1.0 - 2.0 * a;
-    const double pts[3][3] = {{c, a, a}, {a, c, a}, {a, a, c}};
-    for (int t = 0; t < 3; ++t) {
-      const int q = 1 + 3 * g + t;
-      bx[q] = pts[t][0];
-      by[q] = pts[t][1];
-      bz[q] = pts[t][2];
-      R.w[q] = 0.5 * ws[g];
-    }
-  }
   for (int q = 0; q < kQ; ++q) {
-    // barycentric (L0, L1, L2) with L1 = xi, L2 = eta
-    const double L0 = bx[q], L1 = by[q], L2 = bz[q];
-    const double N[6] = {L0 * (2 * L0 - 1), L1 * (2 * L1 - 1), L2 * (2 * L2 - 1),
-                         4 * L0 * L1, 4 * L1 * L2, 4 * L2 * L0};
+    R.w[q] = 0.5 * (q == 0 ? 9.0 / 40.0 : (q < 4 ? 155.0 - kS15 : 155.0 + kS15) / 1200.0);
+    // barycentric L1 = xi, L2 = eta
+    const double L0 = S.L[q][0], L1 = S.L[q][1], L2 = S.L[q][2];
     // d/dxi: dL0 = -1, dL1 = +1; d/deta: dL0 = -1, dL2 = +1
     const double dx[6] = {-(4 * L0 - 1), 4 * L1 - 1, 0.0, 4 * (L0 - L1), 4 * L2, -4 * L2};
     const double de[6] = {-(4 * L0 - 1), 0.0, 4 * L2 - 1, -4 * L1, 4 * L1, 4 * (L0 - L2)};
     for (int a = 0; a < 6; ++a) {
-      R.N[q][a] = N[a];
+      R.N[q][a] = S.N[q][a];
       R.dxi[q][a] = dx[a];
       R.deta[q][a] = de[a];
     }
   }
   return R;
 }
-
-// N[q][a] of make_rule for the kernels that index it per thread
-__device__ __constant__ double kShape[kQ][6] = {
-#define BEM_S(L0, L1, L2) {(L0) * (2 * (L0) - 1), (L1) * (2 * (L1) - 1), (L2) * (2 * (L2) - 1), \
-                           4 * (L0) * (L1), 4 * (L1) * (L2), 4 * (L2) * (L0)}
-#define BEM_A1 (( 6.0 - 3.872983346207417) / 21.0)
-#define BEM_A2 (( 6.0 + 3.872983346207417) / 21.0)
-    BEM_S(1.0 / 3.0, 1.0 / 3.0, 1.0 / 3.0),
-    BEM_S(1.0 - 2.0 * BEM_A1, BEM_A1, BEM_A1), BEM_S(BEM_A1, 1.0 - 2.0 * BEM_A1, BEM_A1),
-    BEM_S(BEM_A1, BEM_A1, 1.0 - 2.0 * BEM_A1),
-    BEM_S(1.0 - 2.0 * BEM_A2, BEM_A2, BEM_A2), BEM_S(BEM_A2, 1.0 - 2.0 * BEM_A2, BEM_A2),
-    BEM_S(BEM_A2, BEM_A2, 1.0 - 2.0 * BEM_A2),
-#undef BEM_A1
-#undef BEM_A2
-#undef BEM_S
-};
 
 // quadrature points of every element: [F*7][8] = x, y, z, nx, ny, nz (unit
 // normal of the element surface), wJ (weight times area Jacobian), 0
@@ -289,7 +279,7 @@ __device__ __forceinline__ bool quad_row(const QuadRow& p, const EvenChunk<KC>& 
       for (int t = 0; t < kQ; ++t) {
         const double* o = p.qp + 8 * ((int64_t)e * kQ + t);
         const QuadPair g = quad_pair(o, x0, x1, x2);
-        const double wr = o[6] * g.wr * kShape[t][a], cr = g.c * g.r;
+        const double wr = o[6] * g.wr * kShapes.N[t][a], cr = g.c * g.r;
         const double2 E = quad_phase<NEAR>(kc.k[kc.kMid], g.r);
         const double2 G0 = make_double2(wr * E.x, wr * E.y);
         double2 G = G0, dE;

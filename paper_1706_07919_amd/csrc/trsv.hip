@@ -16,35 +16,15 @@
 // gave solves of n = 5124 a 1.2 times larger error than one sum per unknown.
 #include <algorithm>
 
-#include "common.h"
+#include "lu_types.h"
 
 namespace bem {
+using namespace lud;
 namespace {
 
-template <typename R> struct Cx;
-template <> struct Cx<float> { using T = float2; };
-template <> struct Cx<double> { using T = double2; };
-
-template <typename C> __device__ inline C cmk(decltype(C::x) a, decltype(C::x) b) {
-  C c; c.x = a; c.y = b; return c;
-}
-template <typename C> __device__ inline C cmul(C a, C b) {
+// a b, fused the same way in every loop
+template <typename C> __device__ inline C product(C a, C b) {
   return cmk<C>(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
-}
-// s + a b as four fused multiply-adds
-template <typename C> __device__ inline C cfma(C s, C a, C b) {
-  return cmk<C>(fma(a.x, b.x, fma(-a.y, b.y, s.x)), fma(a.x, b.y, fma(a.y, b.x, s.y)));
-}
-template <typename C> __device__ inline C crecip(C a) {
-  // 1/a with scaling to avoid overflow (Smith's method)
-  using R = decltype(C::x);
-  if (fabs(a.x) >= fabs(a.y)) {
-    R t = a.y / a.x, d = a.x + a.y * t;
-    return cmk<C>(R(1) / d, -t / d);
-  } else {
-    R t = a.x / a.y, d = a.y + a.x * t;
-    return cmk<C>(t / d, R(-1) / d);
-  }
 }
 // value of lane l (wave-uniform) in every lane
 __device__ inline float lane_value(float v, int l) {
@@ -187,16 +167,16 @@ __device__ __forceinline__ void trsv_block(const typename Cx<R>::T* __restrict__
 #pragma unroll
         for (int c = 0; c < TS_B; ++c) {
           const C x = cmk<C>(lane_value(v.x, c), lane_value(v.y, c));
-          const C p = cmul(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
+          const C p = product(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
           v = lane > c ? s : v;
         }
       } else {
         const C dinv = r0 + lane < rows ? crecip(d[lane]) : cmk<C>(R(1), R(0));
 #pragma unroll
         for (int c = TS_B - 1; c >= 0; --c) {
-          const C t = cmul(v, dinv);
+          const C t = product(v, dinv);
           const C x = cmk<C>(lane_value(t.x, c), lane_value(t.y, c));
-          const C p = cmul(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
+          const C p = product(d[c], x), s = cmk<C>(v.x - p.x, v.y - p.y);
           v = lane == c ? t : (lane < c ? s : v);
         }
       }
@@ -385,7 +365,6 @@ __global__ __launch_bounds__(256) void trsv_update_kernel(
 // through the diagonal block from LDS.  x lives in LDS.
 constexpr int SW_B = 64;
 constexpr int SW_T = 512;
-template <typename C> __device__ inline C minus(C a, C b) { return cmk<C>(a.x - b.x, a.y - b.y); }
 size_t sweep_lds(size_t esz, int n) { return esz * (size_t)(SW_B * (SW_B + 1) + SW_B + n); }
 
 template <typename R>
@@ -487,14 +466,14 @@ __global__ __launch_bounds__(SW_T) void trsv_sweep_kernel(int n, int64_t ld, int
         if (fwd) {
           for (int c = 0; c < rows; ++c) {
             const R xr = __shfl(v.x, c, 64), xi = __shfl(v.y, c, 64);
-            if (lane > c && lane < rows) v = minus(v, cmul(D[lane * (SW_B + 1) + c], cmk<C>(xr, xi)));
+            if (lane > c && lane < rows) v = csub(v, product(D[lane * (SW_B + 1) + c], cmk<C>(xr, xi)));
           }
         } else {
           const C dinv = lane < rows ? crecip(D[lane * (SW_B + 1) + lane]) : cmk<C>(R(1), R(0));
           for (int c = rows - 1; c >= 0; --c) {
-            if (lane == c) v = cmul(v, dinv);
+            if (lane == c) v = product(v, dinv);
             const R xr = __shfl(v.x, c, 64), xi = __shfl(v.y, c, 64);
-            if (lane < c) v = minus(v, cmul(D[lane * (SW_B + 1) + c], cmk<C>(xr, xi)));
+            if (lane < c) v = csub(v, product(D[lane * (SW_B + 1) + c], cmk<C>(xr, xi)));
           }
         }
         if (lane < rows) x[i0 + lane] = v;
