@@ -186,7 +186,7 @@ __device__ __forceinline__ void trsm_quad(C (&x)[KR], const LM& L, int g) {
   C xj[4], d = cmk<C>(R(0), R(0));
   auto own = [&](auto q) {   // unknown q, and its product into the later ones of the four
     constexpr int Q = decltype(q)::value;
-    const C t = g == Q ? csub(x[K0], d) : x[K0];
+    const C t = csub(x[K0], d);   // (lane Q's is the unknown)
     xj[Q] = cmk<C>(quad_value<Q>(t.x), quad_value<Q>(t.y));
     if (g == Q) x[K0] = t;
     if (Q < 3) d = cfma(d, L[4 * K0 + Q][g][K0], xj[Q]);

@@ -99,12 +99,12 @@ __device__ __forceinline__ void put(C& d, const C& v) {
 }
 // 1/a: float32 through float64 (no overflow, one rounding; shorter than two
 // float32 divisions), float64 by Smith's method; with one infinite part 0, as
-// Smith's method has it (d is infinite for no finite float2)
+// Smith's method has it
 __device__ inline float2 recip(float2 a) {
   const double x = a.x, y = a.y, d = fma(x, x, y * y);
   double r = __builtin_amdgcn_rcp(d);
   r = fma(r, fma(-d, r, 1.0), r);
-  const bool inf = d == __builtin_inf() && !(__builtin_isinf(x) && __builtin_isinf(y));
+  const bool inf = __builtin_isinf(a.x) != __builtin_isinf(a.y);
   return make_float2(inf ? 0.f : (float)(x * r), inf ? 0.f : (float)(-y * r));
 }
 __device__ inline double2 recip(double2 a) { return crecip(a); }
