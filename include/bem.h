@@ -202,10 +202,11 @@ typedef enum {
  * BEM_GEMM_4M and BEM_GEMM_3M: four or three float32 MFMA products per complex
  * one.  BEM_GEMM_3M runs its large updates (at least 1024 x 1024 of a depth of
  * 256, at least 1536 x 1536 of a depth of 128) on MFMA f16, every real product as
- * three products of operands split into f16 pairs and scaled by powers of two.  An update's error is at most (3 2^-22 + 2^-24) |L||U|, entry by
+ * three products of operands split into f16 pairs and scaled by powers of two.
+ * An update's error is at most (3 2^-22 + K 2^-27) |L||U| for a depth K, entry by
  * entry, besides its float32 accumulation (typically 2^-23.5; on Gaussian and
- * boundary-integral matrices below that of the float32 3M products); a matrix whose
- * entries span too wide a range for that takes the update in float32 MFMA products.
+ * boundary-integral matrices below that of the float32 3M products); tiles with
+ * entries whose operands span too wide a range for that take float32 MFMA products.
  * The split operands use the packing buffer described below, and where it
  * cannot be allocated, or in a caller's stream capture, those updates take the
  * float32 MFMA products too.

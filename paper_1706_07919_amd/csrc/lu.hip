@@ -400,14 +400,15 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_kernel(LuGroups G, int rowC, 
 //   Im C -= T3 - T1 - T2.
 // Each MFMA 32x32x2 covers two complex k of one product, so a complex k costs
 // 1.5 MFMA per 32x32 block instead of 2 (4M).  The operand sums are formed
-// once while staging the tiles in LDS.  ex (or NULL): only the matrices whose
-// operands cannot be split (split_wide).
-__device__ inline bool split_wide(const int32_t* counts, int K);
+// once while staging the tiles in LDS.  ex (or NULL): only the tiles that
+// gemm_c32_split_kernel left to float32 products.
+__device__ inline bool wide_tile(const int32_t* last, int flag_words, int tile);
 __global__ __launch_bounds__(256) void gemm_c32_3m_kernel(LuGroups G, int rowC, int colC,
                                                           int colA, int rowB, int rowEnd,
                                                           int colEnd, int K, int tiles_n,
-                                                          const int32_t* __restrict__ ex, int64_t ss) {
-  if (ex && !split_wide(ex + blockIdx.y * ss + ss - 4, K)) return;
+                                                          const int32_t* __restrict__ ex, int64_t ss,
+                                                          int flag_words) {
+  if (ex && !wide_tile(ex + blockIdx.y * ss + ss - 4, flag_words, blockIdx.x)) return;
   __shared__ float As[2][3][G32_BK][G32_BM + 4];
   __shared__ float Bs[2][3][G32_BK][G32_BN + 4];
   GemmView<float2> gv;
@@ -554,6 +555,17 @@ __global__ __launch_bounds__(256) void gemm_c32_3m_kernel(LuGroups G, int rowC, 
 //   tile); the last workgroup of a range to find it empty resets the range's
 //   counters for the next launch.
 constexpr int GL_BM = 128, GL_BK = 16, GL_GM = 4;
+
+// tile t of a matrix's walk: odd strips walk the columns backwards, so a strip starts
+// on the B columns the previous one ended on (still in L2)
+__device__ inline void strip_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int strip = GL_GM * tiles_n;
+  const int first = (t / strip) * GL_GM;
+  const int gsz = min(tiles_m - first, GL_GM);
+  const int tcol = (t % strip) / gsz;
+  tm = first + (t % strip) % gsz;
+  tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
+}
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Work list of one launch: group g owns items [start[g], start[g + 1]), each
@@ -603,13 +615,8 @@ __device__ __forceinline__ void gemm_lds_tile(const LuGroups& G, const GemmList&
   const int tiles = tiles_m * tiles_n;
   const int64_t b = local / tiles;
   const int t = (int)(local - b * tiles);
-  const int strip = GL_GM * tiles_n;
-  const int first = (t / strip) * GL_GM;
-  const int gsz = min(tiles_m - first, GL_GM);
-  // odd strips walk the columns backwards, so a strip starts on the B
-  // columns the previous one ended on (still in L2)
-  const int tcol = (t % strip) / gsz;
-  const int tm = first + (t % strip) % gsz, tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
+  int tm, tn;
+  strip_tile(t, tiles_m, tiles_n, tm, tn);
   const int M = min(rowEnd, n) - rowC, N = min(colEnd, n) - colC;
   const int m0 = tm * GL_BM, n0 = tn * BN;
   const GLOBAL float2* Mat = (const GLOBAL float2*)Abase + b * stride;
@@ -1282,10 +1289,16 @@ constexpr int GP_BLK = 2 * 2 * GB_BM;   // 16-byte words per tile and 8-k block
 // largest packing buffer a context holds; bigger batches are packed in slices
 constexpr size_t kPackLimit = (size_t)4 << 30;
 
-// 16-byte words of one matrix's scale exponents (the f16 form): t_k [K],
-// ea [128 tiles_m], eb [128 tiles_n], and in the last word its range counts
+// 32-bit words, in whole 16-byte words, of a flag per tile
+__host__ __device__ inline int tile_flag_words(int tiles_m, int tiles_n) {
+  return (tiles_m * tiles_n + 127) / 128 * 4;
+}
+// 16-byte words of one matrix's scales (the f16 form): t_k [K], ea [128 tiles_m],
+// eb [128 tiles_n], the sums of L's rows [128 tiles_m] and of U's columns [128 tiles_n],
+// the tiles' flags, and in the last word whether any entry is small and any flag set
 inline int64_t scale_words(int tiles_m, int tiles_n, int K) {
-  return (4 * ((int64_t)K + GB_BM * tiles_m + GB_BN * tiles_n) + 15) / 16 + 1;
+  return (4 * ((int64_t)K + 2 * (GB_BM * tiles_m + GB_BN * tiles_n)) + 15) / 16 +
+         tile_flag_words(tiles_m, tiles_n) / 4 + 1;
 }
 // 16-byte words of the packed A and B of one matrix for an M x N update of depth K
 inline int64_t pack_words(int M, int N, int K) {
@@ -1408,18 +1421,23 @@ __global__ __launch_bounds__(256) void pack_b_kernel(LuGroups G, int rowB, int c
 // in [2^14, 2^15).  The epilogue takes 2^(ea_i + eb_j - 28) back.  A scaled entry
 // of at least 1/2 keeps 22 bits or more; a smaller one has an absolute error of
 // up to 2^-25 (2^-39 of its row's or column's largest), which no scaling cures
-// where a row's large entries meet small ones of a column.  So the packing
-// counts, as maxima over the rows of L and the columns of U of a matrix, the
-// nonzero entries below 1/2 (s) and the entries below 64 (p).  Row i and column j
-// share at least K - p_L - p_U places where both are 64 or more, that is
-// sum_k |l_ik u_kj| >= 2^12 (K - p), and small entries cost at most 2^-9 s.  Where
-// 8 s > K - p that could exceed 2^-24 sum_k |l_ik u_kj|, and the matrix takes this
-// update as float32 products (split_wide; infinities too).  None of the
-// boundary-integral systems measured does (n = 1284 to 10242, hard, soft, mixed: s
-// is 0 to 4 of 128 to 512).  So
-//   |error| <= (3 2^-22 + 2^-24) sum_k |l_ik u_kj|
+// where a row's large entries meet small ones of a column.  A row i of L with such
+// entries costs c_ij at most 2^-24.5 sum_k |u_kj|, a column j of U
+// 2^-24.5 sum_k |l_ik| (|.| of a complex entry: |Re| + |Im|).  So the packing
+// keeps these two sums, negative where the row or column has entries below 1/2,
+// and a tile is written only if in all its entries what the range can cost is at
+// most K 2^-27 of the computed |l u|_ij, a quarter of the K 2^-25 sum_k |l_ik u_kj|
+// that the rounding of the float32 products (two a rounding) may reach.  Tiles
+// past that, and with infinities, are left to float32 products
+// (gemm_c32_lds_wide_kernel).  Boundary-integral systems: hard bodies have no such
+// entries, or hardly any; soft ones at long waves, whose |l u| decays over the matrix,
+// have them in most rows, and 0 to 5 % of their tiles take float32 products
+// (n = 5124 and 10242, k from 0.01 to 20).  Their factors are the better for the rest:
+// PA - LU against |L||U| at n = 10242, k = 0.31, soft: 3.5e-7 rms and 2.7e-6 at
+// most, with float32 products throughout 8.1e-7 and 4.9e-6.  So
+//   |error| <= (3 2^-22 + K 2^-27) sum_k |l_ik u_kj|
 // besides the float32 accumulation, the first term from lo's rounding and the
-// dropped lo lo (2^-23.5 rms).
+// dropped lo lo (2^-23.5 rms), the second zero without small entries.
 //
 // Bias: MFMA f16 cuts the products it adds off at the accumulator's last bit
 // towards minus infinity, a mean error of -0.05 of the rms one.  Random errors
@@ -1441,47 +1459,41 @@ __device__ inline int scale_exp(float m) {
 }
 __device__ inline float exp2i(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
 
-// Range counts of a matrix: s of L's rows, s of U's columns, p of each.
-// Whether the update's float32 products cannot be split (above)
-__device__ inline bool split_wide(const int32_t* counts, int K) {
-  const int s = counts[0] + counts[1];
-  return s > 0 && 8 * s > K - counts[2] - counts[3];
+// Whether tile tm * tiles_n + tn of the matrix whose last scale word this is was
+// left to float32 products
+__device__ inline bool wide_tile(const int32_t* last, int flag_words, int tile) {
+  return last[1] && ((last - flag_words)[tile >> 5] >> (tile & 31) & 1);
 }
-// s (high half) and p of 2 NP scaled values, NP complex entries
+// NP complex entries, scaled: adds to their sum |Re| + |Im|; whether one is small
 template <int NP>
-__device__ inline int range_count(const float* x) {
-  int c = 0;
+__device__ inline bool range_sum(const float* x, float& sum) {
+  bool small = false;
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     const float r = fmaxf(fabsf(x[2 * q]), fabsf(x[2 * q + 1]));
-    c += (r >= 64.f ? 0 : 1) + (r > 0.f && r < 0.5f ? 1 << 16 : 0);
+    small |= r > 0.f && r < 0.5f;
+    sum += fabsf(x[2 * q]) + fabsf(x[2 * q + 1]);
   }
-  return c;
+  return small;
 }
-// A workgroup's rows (or columns) into the matrix's counts: thread 32 part + r
-// holds part of row r's count, pad of it for depth past K; largest: row r's
-// largest entry before its scaling
-__device__ inline void store_counts(int c, int pad, bool valid, float largest, int (*red)[32],
-                                    int32_t* s_out, int32_t* p_out) {
+// The sums of a workgroup's rows (or columns), negative with small entries: thread
+// 32 part + r holds part of row r's (sums[r]); last: the matrix's last scale word
+__device__ inline void store_sums(float sum, bool small, float (*red)[32], float* sums,
+                                  int32_t* last) {
   const int r = threadIdx.x & 31, part = threadIdx.x >> 5;
-  red[part][r] = c;
+  __syncthreads();   // the maxima have been read
+  red[part][r] = small ? -sum : sum;
   __syncthreads();
   if (part) return;
-  int sum = 0;
+  float all = 0.f;
+  bool any = false;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) sum += red[q][r];
-  int s = sum >> 16, p = (sum & 0xffff) - pad;
-  if (largest > 3.4028234e38f) s = 1 << 20;   // an infinity
-  if (!valid) s = p = 0;
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) {
-    s = max(s, __shfl_xor(s, o, 32));
-    p = max(p, __shfl_xor(p, o, 32));
+  for (int q = 0; q < 8; ++q) {
+    all += fabsf(red[q][r]);
+    any |= red[q][r] < 0.f;
   }
-  if (r == 0) {
-    if (s) atomicMax(s_out, s);
-    if (p) atomicMax(p_out, p);
-  }
+  sums[r] = any ? -all : all;
+  if (any || all > 3.4028234e38f) atomicOr(last, 1);
 }
 
 __device__ inline void split8h(const float* x, uint4& hi, uint4& lo) {
@@ -1499,9 +1511,10 @@ __device__ inline void split8h(const float* x, uint4& hi, uint4& lo) {
 }
 
 // t_k of row rowB + k of U over the columns [colC, min(colEnd, n)), one
-// workgroup per row; clears the range counts
+// workgroup per row; clears the tiles' flags and the last word
 __global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int colC, int colEnd,
-                                                       int64_t ss, int32_t* __restrict__ ex) {
+                                                       int64_t ss, int flag_words,
+                                                       int32_t* __restrict__ ex) {
   __shared__ float red[4];
   LuGroup grp;
   int b = 0;
@@ -1521,7 +1534,9 @@ __global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (k == 0 && threadIdx.x < 4) ex[blockIdx.y * ss + ss - 4 + threadIdx.x] = 0;
+  if (k == 0)
+    for (int i = threadIdx.x; i < flag_words + 4; i += 256)
+      ex[blockIdx.y * ss + ss - 4 - flag_words + i] = 0;
   if (threadIdx.x == 0)
     ex[blockIdx.y * ss + k] = scale_exp(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
 }
@@ -1531,11 +1546,10 @@ __global__ __launch_bounds__(256) void urow_exp_kernel(LuGroups G, int rowB, int
 // the rows are read twice (their largest entries first, from cache after), and
 // written as pack_a_kernel's words.
 __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, int colA, int rowEnd,
-                                                         int K, int tiles_m, int64_t ms, int64_t ss,
-                                                         uint4* __restrict__ out,
+                                                         int K, int tiles_m, int tiles_n, int64_t ms,
+                                                         int64_t ss, uint4* __restrict__ out,
                                                          int32_t* __restrict__ ex) {
   __shared__ float red[8][32];
-  __shared__ int cnt[8][32];
   LuGroup grp;
   int b = 0;
   if (!locate(G, blockIdx.y, grp, b)) return;
@@ -1589,13 +1603,14 @@ __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, i
   if (part == 0) ex[blockIdx.y * ss + K + gr] = e;
   const float sc = exp2i(14 - e);
   const int tile = gr / GB_BM, row = gr % GB_BM;
-  int count = 0;
+  float sum = 0.f;
+  bool small = false;
   for (int s8 = part; s8 < S8; s8 += 8) {
     load(s8, x);
     const float sg = (s8 / (kFlipK / 8)) & 1 ? -sc : sc;
 #pragma unroll
     for (int q = 0; q < 16; ++q) x[q] *= sg;
-    count += range_count<8>(x);
+    small |= range_sum<8>(x, sum);
     uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + s8) * GP_BLK;
 #pragma unroll
     for (int kg = 0; kg < 2; ++kg) {
@@ -1605,8 +1620,9 @@ __global__ __launch_bounds__(256) void pack_a_f16_kernel(LuGroups G, int rowC, i
       o[kg * 2 * GB_BM + GB_BM + row] = lo;
     }
   }
-  int32_t* counts = ex + blockIdx.y * ss + ss - 4;
-  store_counts(count, 8 * S8 - K, gr < M, m, cnt, counts, counts + 2);
+  int32_t* mine = ex + blockIdx.y * ss;
+  store_sums(sum, small, red, (float*)(mine + K + GB_BM * tiles_m + GB_BN * tiles_n) + 32 * blockIdx.x,
+             mine + ss - 4);
 }
 
 // U = rows [rowB, rowB + K) x cols [colC, min(colEnd, n)): 32 columns per
@@ -1617,7 +1633,6 @@ __global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, i
                                                          int64_t ss, uint4* __restrict__ out,
                                                          int32_t* __restrict__ ex) {
   __shared__ float red[8][32];
-  __shared__ int cnt[8][32];
   LuGroup grp;
   int b = 0;
   if (!locate(G, blockIdx.y, grp, b)) return;
@@ -1653,21 +1668,23 @@ __global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, i
   if (part == 0) ex[blockIdx.y * ss + K + GB_BM * tiles_m + gc] = e;
   const float sc = exp2i(14 - e);
   const int tile = gc / GB_BN, col = gc % GB_BN;
-  int count = 0;
+  float sum = 0.f;
+  bool small = false;
 #pragma unroll 2
   for (int g = part; g < 2 * S8; g += 8) {
     load(g, x);
 #pragma unroll
     for (int q = 0; q < 8; ++q) x[q] *= sc;
-    count += range_count<4>(x);
+    small |= range_sum<4>(x, sum);
     uint4 hi, lo;
     split8h(x, hi, lo);
     uint4* o = out + blockIdx.y * ms + ((int64_t)tile * S8 + g / 2) * GP_BLK + (g & 1) * 2 * GB_BN;
     o[col] = hi;
     o[GB_BN + col] = lo;
   }
-  int32_t* counts = ex + blockIdx.y * ss + ss - 4;
-  store_counts(count, 8 * S8 - K, gc < N, m, cnt, counts + 1, counts + 3);
+  int32_t* mine = ex + blockIdx.y * ss;
+  store_sums(sum, small, red,
+             (float*)(mine + K + 2 * GB_BM * tiles_m + GB_BN * tiles_n) + 32 * blockIdx.x, mine + ss - 4);
 }
 
 // (a, -b) pairs of the real-part pattern -> (b, a) of the imaginary-part
@@ -1680,7 +1697,7 @@ template <bool F16>
 __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
     LuGroups G, GemmList W, int rowC, int colC, int rowEnd, int colEnd, int K,
     const uint4* __restrict__ Ap, int64_t a_ms, const uint4* __restrict__ Bp, int64_t b_ms,
-    const int32_t* __restrict__ ex, int64_t ss, int tiles_m_all) {
+    int32_t* __restrict__ ex, int64_t ss, int tiles_m_all, int tiles_n_all) {
   __shared__ u32x4 As[2][2 * GP_BLK], Bs[2][2 * GP_BLK];
   const int64_t total = W.start[G.ng];
   const int64_t item = (int64_t)(blockIdx.x & 7) * ((total + 7) >> 3) + (blockIdx.x >> 3);
@@ -1709,13 +1726,9 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
   const int tiles = tiles_m * tiles_n;
   const int64_t b = local / tiles;
   const int t = (int)(local - b * tiles);
-  const int strip = GL_GM * tiles_n;
-  const int first = (t / strip) * GL_GM;
-  const int gsz = min(tiles_m - first, GL_GM);
-  const int tcol = (t % strip) / gsz;
-  const int tm = first + (t % strip) % gsz, tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
+  int tm, tn;
+  strip_tile(t, tiles_m, tiles_n, tm, tn);
   const int64_t mat = first_mat + b;
-  if (F16 && split_wide(ex + mat * ss + ss - 4, K)) return;   // (gemm_c32_lds_wide_kernel's)
   const int M = min(rowEnd, n) - rowC, N = min(colEnd, n) - colC;
   const int m0 = tm * GB_BM, n0 = tn * GB_BN;
   const int ld = (int)ld64;   // n * ld < 2^31 is checked on the host
@@ -1821,6 +1834,36 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
     kloop(std::false_type{});
   const int32_t* ea = F16 ? ex + mat * ss + K : nullptr;
   const int32_t* eb = F16 ? ea + GB_BM * tiles_m_all : nullptr;
+  if constexpr (F16) {
+    int32_t* last = ex + mat * ss + ss - 4;
+    if (last[0]) {   // small entries: whether the range costs an entry of this tile too much
+      const float* rs = (const float*)(eb + GB_BN * tiles_n_all);
+      const float* cs = rs + GB_BM * tiles_m_all;
+      const float per = 6.f / (float)K;   // 2^-24.5 / (K 2^-27), rounded up
+      bool bad = false;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float c = cs[n0 + wn * 64 + j * 32 + l32];   // (both cover whole tiles)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const float r = rs[m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3)];
+            const float cost = (r < 0.f ? fabsf(c) : 0.f) + (c < 0.f ? fabsf(r) : 0.f);
+            const float lu = fmaxf(fabsf(acc_re[i][j][v]), fabsf(acc_im[i][j][v]));
+            bad |= lu < per * cost || fmaxf(fabsf(r), fabsf(c)) > 3.4028234e38f;
+          }
+        }
+      if (__syncthreads_or(bad)) {
+        if (tid == 0) {
+          const int tile = tm * tiles_n_all + tn;
+          atomicOr(last - tile_flag_words(tiles_m_all, tiles_n_all) + (tile >> 5), 1 << (tile & 31));
+          atomicOr(last + 1, 1);
+        }
+        return;
+      }
+    }
+  }
   const float sgn = ((K - 1) / kFlipK) & 1 ? -1.f : 1.f;   // of the accumulators after the last range
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -1849,30 +1892,38 @@ __global__ __launch_bounds__(256, 2) void gemm_c32_split_kernel(
     }
 }
 
-// The float32 products of the matrices whose operands cannot be split, of the
-// work list of gemm_c32_split_kernel: resident workgroups step through it, and
-// leave at once where there is no such matrix (every update of the
-// boundary-integral systems: 5 us for 64 of n = 5124).
+// The float32 products of the tiles that gemm_c32_split_kernel left, of the same work
+// list: resident workgroups step through it, and leave at once where there is no such
+// tile (most updates of boundary-integral systems: 5 us for 64 of n = 5124).
 __global__ __launch_bounds__(256, 2) void gemm_c32_lds_wide_kernel(
     LuGroups G, GemmList W, int rowC, int colC, int colA, int rowB, int rowEnd, int colEnd, int K,
-    const int32_t* __restrict__ ex, int64_t ss) {
+    const int32_t* __restrict__ ex, int64_t ss, int tiles_n_all, int flag_words) {
   __shared__ u32x4 As[2][GL_BM * GL_BK / 2], Bs[2][GL_BK * 128 / 2];
   int mats = 0;
 #pragma unroll
   for (int i = 0; i < kMaxGroups; ++i)
     if (i < G.ng) mats += G.g[i].count;
   bool any = false;
-  for (int i = threadIdx.x; i < mats; i += 256) any |= split_wide(ex + i * ss + ss - 4, K);
+  for (int i = threadIdx.x; i < mats; i += 256) any |= ex[i * ss + ss - 3] != 0;
   if (!__syncthreads_or(any)) return;
   const int64_t total = W.start[G.ng], per = (total + 7) >> 3;
   const int64_t lo = (int64_t)(blockIdx.x & 7) * per, hi = min(total, lo + per);
   for (int64_t item = lo + (blockIdx.x >> 3); item < hi; item += gridDim.x >> 3) {
     int64_t mat = 0;
+    int tm = 0, tn = 0;
 #pragma unroll
     for (int i = 0; i < kMaxGroups; ++i)
-      if (i < G.ng && item >= W.start[i])
-        mat += item < W.start[i + 1] ? (item - W.start[i]) / (W.tm[i] * W.tn[i]) : G.g[i].count;
-    if (!split_wide(ex + mat * ss + ss - 4, K)) continue;   // uniform
+      if (i < G.ng && item >= W.start[i]) {
+        if (item < W.start[i + 1]) {
+          const int tiles = W.tm[i] * W.tn[i];
+          const int64_t local = item - W.start[i];
+          mat += local / tiles;
+          strip_tile((int)(local % tiles), W.tm[i], W.tn[i], tm, tn);
+        } else {
+          mat += G.g[i].count;
+        }
+      }
+    if (!wide_tile(ex + mat * ss + ss - 4, flag_words, tm * tiles_n_all + tn)) continue;   // uniform
     gemm_lds_tile<true, 2>(G, W, item, rowC, colC, colA, rowB, rowEnd, colEnd, K, As, Bs);
     __syncthreads();   // the tile's LDS reads are done
   }
@@ -2229,7 +2280,7 @@ struct Fac {
       else if (gkind == kGemm3M)
         hipLaunchKernelGGL(gemm_c32_3m_kernel, dim3(tm * tn, total), dim3(256), 0, ctx->stream, G,
                            rowC, colC, colA, rowB, rowEnd, colEnd, K, tn, (const int32_t*)nullptr,
-                           (int64_t)0);
+                           (int64_t)0, 0);
       else
         hipLaunchKernelGGL(gemm_c32_kernel, dim3(tm * tn, total), dim3(256), 0, ctx->stream, G,
                            rowC, colC, colA, rowB, rowEnd, colEnd, K, tn);
@@ -2299,6 +2350,7 @@ struct Fac {
     const int S8 = (K + 7) / 8;
     const int64_t a_ms = (int64_t)tiles_m * S8 * GP_BLK, b_ms = (int64_t)tiles_n * S8 * GP_BLK;
     const int64_t ss = 4 * scale_words(tiles_m, tiles_n, K);
+    const int flags = tile_flag_words(tiles_m, tiles_n);
     uint4* Ap = (uint4*)pack;
     uint4* Bp = Ap + a_ms * fit;
     int32_t* ex = (int32_t*)(Bp + b_ms * fit);
@@ -2318,9 +2370,9 @@ struct Fac {
       int pi = prof_begin(ctx, "pack");
       if (f16) {
         hipLaunchKernelGGL(urow_exp_kernel, dim3(K, nbat), dim3(256), 0, ctx->stream, Gs, rowB,
-                           colC, colEnd, ss, ex);
+                           colC, colEnd, ss, flags, ex);
         hipLaunchKernelGGL(pack_a_f16_kernel, dim3(tiles_m * (GB_BM / 32), nbat), dim3(256), 0,
-                           ctx->stream, Gs, rowC, colA, rowEnd, K, tiles_m, a_ms, ss, Ap, ex);
+                           ctx->stream, Gs, rowC, colA, rowEnd, K, tiles_m, tiles_n, a_ms, ss, Ap, ex);
         hipLaunchKernelGGL(pack_b_f16_kernel, dim3(tiles_n * (GB_BN / 32), nbat), dim3(256), 0,
                            ctx->stream, Gs, rowB, colC, colEnd, K, tiles_m, tiles_n, b_ms, ss, Bp,
                            ex);
@@ -2337,16 +2389,17 @@ struct Fac {
       const dim3 gd((unsigned)((W.start[Gs.ng] + 7) / 8 * 8)), bd(256);
       if (f16) {
         hipLaunchKernelGGL(gemm_c32_split_kernel<true>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
-                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
+                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m, tiles_n);
         if (lds_aligned(Gs, colC, colA, K))
           hipLaunchKernelGGL(gemm_c32_lds_wide_kernel, dim3((unsigned)std::min<int64_t>(gd.x, resident_wgs())),
-                             bd, 0, ctx->stream, Gs, W, rowC, colC, colA, rowB, rowEnd, colEnd, K, ex, ss);
+                             bd, 0, ctx->stream, Gs, W, rowC, colC, colA, rowB, rowEnd, colEnd, K, ex, ss,
+                             tiles_n, flags);
         else
           hipLaunchKernelGGL(gemm_c32_3m_kernel, dim3(tiles_m * tiles_n, nbat), bd, 0, ctx->stream, Gs,
-                             rowC, colC, colA, rowB, rowEnd, colEnd, K, tiles_n, ex, ss);
+                             rowC, colC, colA, rowB, rowEnd, colEnd, K, tiles_n, ex, ss, flags);
       } else
         hipLaunchKernelGGL(gemm_c32_split_kernel<false>, gd, bd, 0, ctx->stream, Gs, W, rowC, colC,
-                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m);
+                           rowEnd, colEnd, K, Ap, a_ms, Bp, b_ms, ex, ss, tiles_m, tiles_n);
       prof_end(ctx, kname, pi, 8.0 * mn * K, 8.0 * (mk + kn + 2.0 * mn));
     }
     return true;
