@@ -971,6 +971,7 @@ KERNEL_SECTIONS = {
     "gemm_3m": ("GEMM f32, operands streamed into LDS", "GEMM f32 via bf16 split\n"),
     "gemm_c32": ("GEMM f32, operands streamed into LDS", "GEMM f32 via bf16 split\n"),
     "gemm_b3_packed": ("GEMM f32 via bf16 split, packed operands", "GEMM f64"),
+    "gemm_f16x3": ("float32 products on f16 MFMA", "GEMM f64"),
 }
 
 

@@ -555,17 +555,6 @@ __global__ __launch_bounds__(256) void gemm_c32_3m_kernel(LuGroups G, int rowC, 
 //   tile); the last workgroup of a range to find it empty resets the range's
 //   counters for the next launch.
 constexpr int GL_BM = 128, GL_BK = 16, GL_GM = 4;
-
-// tile t of a matrix's walk: odd strips walk the columns backwards, so a strip starts
-// on the B columns the previous one ended on (still in L2)
-__device__ inline void strip_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int strip = GL_GM * tiles_n;
-  const int first = (t / strip) * GL_GM;
-  const int gsz = min(tiles_m - first, GL_GM);
-  const int tcol = (t % strip) / gsz;
-  tm = first + (t % strip) % gsz;
-  tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
-}
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Work list of one launch: group g owns items [start[g], start[g + 1]), each
@@ -615,8 +604,13 @@ __device__ __forceinline__ void gemm_lds_tile(const LuGroups& G, const GemmList&
   const int tiles = tiles_m * tiles_n;
   const int64_t b = local / tiles;
   const int t = (int)(local - b * tiles);
-  int tm, tn;
-  strip_tile(t, tiles_m, tiles_n, tm, tn);
+  const int strip = GL_GM * tiles_n;
+  const int first = (t / strip) * GL_GM;
+  const int gsz = min(tiles_m - first, GL_GM);
+  // odd strips walk the columns backwards, so a strip starts on the B
+  // columns the previous one ended on (still in L2)
+  const int tcol = (t % strip) / gsz;
+  const int tm = first + (t % strip) % gsz, tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
   const int M = min(rowEnd, n) - rowC, N = min(colEnd, n) - colC;
   const int m0 = tm * GL_BM, n0 = tn * BN;
   const GLOBAL float2* Mat = (const GLOBAL float2*)Abase + b * stride;
@@ -1690,6 +1684,16 @@ __global__ __launch_bounds__(256) void pack_b_f16_kernel(LuGroups G, int rowB, i
 // (a, -b) pairs of the real-part pattern -> (b, a) of the imaginary-part
 // pattern (both 16-bit formats keep the sign in the top bit)
 __device__ inline u32x4 re_to_im4(u32x4 r) { return ((r >> 16) | (r << 16)) ^ 0x8000u; }
+
+// tile t of gemm_lds_tile's walk over a matrix
+__device__ inline void strip_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int strip = GL_GM * tiles_n;
+  const int first = (t / strip) * GL_GM;
+  const int gsz = min(tiles_m - first, GL_GM);
+  const int tcol = (t % strip) / gsz;
+  tm = first + (t % strip) % gsz;
+  tn = ((t / strip) & 1) ? tiles_n - 1 - tcol : tcol;
+}
 
 // F16: 16-bit words are f16 and the scale exponents ex apply; else bfloat16.
 // Tile order, work list and edge handling are those of gemm_c32_lds_kernel.
